@@ -138,6 +138,28 @@ def test_hessian_accumulate(gpu_lib, t, k, dtype):
     assert np.array_equal(got, got.T)                                     # the same products in the same order
 
 
+@pytest.mark.parametrize("t,k,dtype", [(45, 3466, "bf16"), (33, 3461, "bf16"), (64, 130, "bf16"), (7, 33, "bf16"), (17, 70, "f32"),
+                                       (50, 257, "f32"), (4096, 256, "bf16")])
+def test_hessian_accumulate_tile_edges(gpu_lib, t, k, dtype):
+    """Remainders of the tiles (64 and, on bf16 layers of 3457 features and more, 128 wide) and of the token slices (16 /
+    32), even and odd row strides, against float64.  An entry is a sum of t products, each at most sqrt(H_ii H_jj) in
+    sum of magnitudes: every rounding, and every product the bf16 matrix unit cuts off 24 bits below the largest of its
+    octet, costs at most 2^-24 of that, one per token and one for the batch that is added."""
+    rng = np.random.default_rng([91, t, k])
+    x = calibration_inputs(rng, 2 * t, k) if k < 1000 else rng.standard_normal((2 * t, k))
+    xd = torch.from_numpy(x.astype(np.float32)).to(DEV)
+    if dtype == "bf16":
+        xd = xd.to(torch.bfloat16)
+    x = host(xd.float()).astype(np.float64)
+    wide = torch.full((t, k + 7), 1e6, dtype=xd.dtype, device=DEV)
+    wide[:, :k] = xd[t:]
+    got = host(B.hessian_accumulate(wide[:, :k], B.hessian_accumulate(xd[:t]))).astype(np.float64)
+    want = x.T @ x
+    d = np.sqrt(np.diag(want))
+    assert np.all(np.abs(got - want) <= (2 * t + 1) * 2.0 ** -24 * np.outer(d, d) + 1e-30)
+    assert np.array_equal(got, got.T)
+
+
 @pytest.mark.parametrize("k,reorder,damp", [(128, False, 0.01), (512, True, 0.01), (1024, True, 0.05), (1152, False, 0.01)])
 def test_hessian_inverse_factor(gpu_lib, k, reorder, damp):
     """Dampening + Cholesky (Sec. 3.3) on the GPU (float64 inside) against the oracle's float64 route through the
