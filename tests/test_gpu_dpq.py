@@ -180,6 +180,21 @@ def test_hessian_inverse_factor(gpu_lib, k, reorder, damp):
     assert np.abs(got.T @ got @ hd - np.eye(k)).max() < 1e-3            # float32 entries of U: ~cond * 2^-24
 
 
+@pytest.mark.parametrize("k", [256, 384, 640, 896])
+def test_hessian_inverse_factor_uneven_doublings(gpu_lib, k):
+    """4, 6, 10 and 14 tiles: the last pair of every doubling of the inverse whole, cut off, or left alone.  Tolerance as in
+    test_hessian_inverse_factor: float32 rounding of the result plus a conditioning allowance."""
+    rng = np.random.default_rng([92, k])
+    x = calibration_inputs(rng, 2 * k, k)
+    h = (x.T @ x).astype(np.float32)
+    h = np.maximum(h, h.T)
+    want = o.hessian_inverse_factor_from_h(h, 0.01, None)
+    u, info = B.hessian_inverse_factor(dev(h), 0.01)
+    got = host(u).astype(np.float64)
+    assert int(host(info)[0]) == 0 and np.all(np.tril(got, -1) == 0.0)
+    assert np.all(np.abs(got - want) <= 2.0 ** -23 * np.abs(want) + 1e-9 * np.abs(want).max())
+
+
 def test_hessian_inverse_factor_reports_a_matrix_that_is_not_positive_definite(gpu_lib):
     k = 256
     h = np.eye(k, dtype=np.float32)
