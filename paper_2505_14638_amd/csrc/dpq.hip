@@ -4,11 +4,12 @@
 // Alg. 1 walks along a row: quantize one weight (FP8, then INT4, Eq. 7-9), dequantize it the way inference will
 // (Eq. 10-11), and push the error onto every later weight of the row through the Hessian factor U (Eq. 12; U is the
 // upper Cholesky factor of the inverse Hessian, Sec. 3.3).  Rows are independent, columns strictly sequential.  The
-// work is arranged in blocks of 128 columns: inside a block 32 lanes of one wavefront own one row (each takes
-// the quantization step itself and applies the error to its share of the rest of the block); the columns right of
-// the block receive the block's 128 errors afterwards, in one tiled pass over the matrix.  Every weight still sees the same float32 operations in the same order as in the plain
-// column-by-column statement (w <- w - err_q * U[q, v] for q ascending, product and difference rounded separately),
-// so the integer decisions are reproducible bit for bit; only the time at which an update is applied moves.
+// work is arranged in blocks of 128 columns: inside a block four lanes own a row; the columns right of the block receive
+// the block's 128 errors afterwards, tile by tile.  Every weight still sees the same float32 operations in the same order
+// as in the plain column-by-column statement (w <- w - err_q * U[q, v] for q ascending, product and difference rounded
+// separately), so the integer decisions are reproducible bit for bit; only the time at which an update is applied moves.
+// That rules out the matrix unit (a product there is not rounded by itself): the updates take a multiplication and a
+// subtraction each on the vector unit, 1.75 ms for 4096 x 4096 weights.
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -24,39 +25,54 @@ __device__ __forceinline__ float fp8_value(float t) {
 }
 
 // position i of the reordered tensor holds original column perm[i]: inside a group by descending diagonal, groups
-// by descending maximum; ties keep the lower original index first.  One thread per column.
+// by descending maximum; ties keep the lower original index first.  One thread per column; the maxima of the groups come
+// from the workgroup together, MAXIMA groups at a time (every thread for itself, all K values one after the other: 185 us at
+// K = 4096; together 25).  A maximum is kept as an unsigned integer that orders like the floats, 0 for "nothing but
+// NaN", which no comparison below is true for.
+constexpr int MAXIMA = 1024;
 __global__ void __launch_bounds__(256) gar_permutation_kernel(const float* __restrict__ d, int K, int G, int32_t* __restrict__ perm) {
+    __shared__ uint32_t top[MAXIMA];
+    auto value_of = [](uint32_t key) {
+        return key == 0u ? __uint_as_float(0x7FC00000u) : __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
+    };
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= K) return;
-    const int g = c / G, NG = K / G;
-    const float mine = d[c];
+    const bool mine_exists = c < K;
+    const int g = (mine_exists ? c : 0) / G, NG = K / G;
+    const float mine = d[mine_exists ? c : 0];
     int inside = 0;
-    float gmax = d[g * G];
+    float gmax = d[(int64_t)g * G];
+#pragma unroll 16
     for (int j = 0; j < G; ++j) {
         const float v = d[g * G + j];
         inside += (v > mine) || (v == mine && g * G + j < c);
         gmax = fmaxf(gmax, v);
     }
     int rank = 0;
-    for (int h = 0; h < NG; ++h) {
-        float m = d[h * G];
-        for (int j = 1; j < G; ++j) m = fmaxf(m, d[h * G + j]);
-        rank += (m > gmax) || (m == gmax && h < g);
+    for (int h0 = 0; h0 < NG; h0 += MAXIMA) {
+        const int count = min(MAXIMA, NG - h0);
+        for (int h = threadIdx.x; h < count; h += 256) top[h] = 0u;
+        __syncthreads();
+        for (int e = threadIdx.x; e < count * G; e += 256) {                    // the 64 values of a wavefront lie in one group
+            const float v = d[h0 * G + e];
+            const uint32_t b = __float_as_uint(v);
+            uint32_t key = (v != v) ? 0u : (b & 0x80000000u) ? ~b : b | 0x80000000u;
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) key = max(key, (uint32_t)__shfl_xor((int)key, m));
+            if ((threadIdx.x & 63) == 0) atomicMax(&top[e / G], key);
+        }
+        __syncthreads();
+        for (int h = 0; h < count; ++h) {
+            const float m = value_of(top[h]);
+            rank += (m > gmax) || (m == gmax && h0 + h < g);
+        }
+        __syncthreads();
     }
-    perm[rank * G + inside] = c;
-}
-
-// work[n, i] = w[n, perm[i]] (perm == nullptr: a copy)
-__global__ void __launch_bounds__(256) dpq_gather_kernel(const float* __restrict__ w, const int32_t* __restrict__ perm,
-                                                         int64_t N, int64_t K, float* __restrict__ work) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= N * K) return;
-    const int64_t n = u / K, i = u - n * K;
-    work[u] = w[n * K + (perm ? perm[i] : i)];
+    if (mine_exists) perm[rank * G + inside] = c;
 }
 
 struct DpqArgs {
-    float* work;                  // [N, K] current weights, reordered columns
+    const float* w;               // [N, K] the weights, original column order
+    float* work;                  // [N, K] current weights, reordered columns; a finished block's columns hold its errors
     const float* u;               // [K, K] upper factor, reordered columns
     const float* s_w;
     int per_channel;
@@ -65,7 +81,6 @@ struct DpqArgs {
     uint8_t* codes;               // [N, K], original column order
     float* scales;                // [N, K / G], original group order
     uint8_t* zeros;               // [N, K / G]
-    float* err;                   // [N, 128] errors of the current block
     int mse_grid;                 // candidates of the scale search (Sec. 3.3); <= 1: none
     float shrink_step;            // max_shrink / mse_grid
 };
@@ -77,46 +92,239 @@ __device__ __forceinline__ void group_params(float lo, float hi, float& s, float
     z = fminf(fmaxf(rintf(__fdiv_rn(-lo, s)), 0.0f), 15.0f);
 }
 
-// One block of 128 columns starting at c0.  The DPQ_LPR lanes of a row sit next to each other in one wavefront and
-// share the row's 128 weights through LDS; a wavefront executes its LDS accesses in program order, so a lane's update
-// of a column is in place before every lane of the row reads that column in a later step -- no barrier is needed.
-// All lanes of a row take the (identical) quantization step; lane p updates the columns v with v % DPQ_LPR == p.
-// DPQ_LPR lanes per row: more lanes shorten a step (fewer columns to update per lane) but repeat the quantization
-// arithmetic on every one of them, so many lanes suit few rows and few lanes many rows.
-// The 128 steps are strictly sequential.  STAGE_U: the block's corner of U is staged in LDS once (64 KiB), so that no
-// step waits for a global load -- right when there are few rows and nothing else to run meanwhile; with many rows
-// the loads stay global and many small workgroups per compute unit hide them instead (64 KiB of LDS would leave two).
-template <int DPQ_LPR, bool STAGE_U, int DPQ_THREADS>
-__global__ void __launch_bounds__(DPQ_THREADS) dpq_block_kernel(DpqArgs a, int c0) {
-    constexpr int DPQ_ROWS = DPQ_THREADS / DPQ_LPR;              // rows per workgroup
-    __shared__ float wl[DPQ_BLOCK * DPQ_ROWS];                   // wl[v * DPQ_ROWS + r]: column c0 + v of row r of the workgroup
-    __shared__ float ul[STAGE_U ? DPQ_BLOCK * DPQ_BLOCK : 1];    // ul[q * 128 + v] = U[c0 + q, c0 + v]
-    if (STAGE_U) {
-        for (int idx = threadIdx.x; idx < DPQ_BLOCK * DPQ_BLOCK; idx += DPQ_THREADS)
-            ul[idx] = a.u[(int64_t)(c0 + idx / DPQ_BLOCK) * a.K + c0 + idx % DPQ_BLOCK];
-        __syncthreads();
+// a / b, correctly rounded, from y = RN(1 / b): the estimate a * y is at most two units off, one correction makes it
+// faithful, and a second one rounds it correctly (Markstein's theorem on the final step of a division by a correctly
+// rounded reciprocal).  Five operations, where the general division takes about ten and several mode switches; valid while
+// neither the residuals nor the quotient leave the normal range, which the callers' range checks see to (a zero's sign may
+// differ, which nothing here depends on).
+__device__ __forceinline__ float div_by(float a, float b, float y) {
+    float q = __fmul_rn(a, y);
+    q = __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
+    return __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
+}
+constexpr float DIV_LO = 0x1p-30f, DIV_HI = 0x1p30f;            // divisors
+constexpr uint32_t NUM_LO = 0x21800000u, NUM_SPAN = 0x5D800000u - 0x21800000u;   // bits of 2^-60, up to 2^60: weights
+__device__ __forceinline__ bool plain_divisor(float b) { return fabsf(b) >= DIV_LO && fabsf(b) <= DIV_HI; }
+
+// fp8_value for a finite t
+__device__ __forceinline__ float fp8_value_finite(float t) {
+    return __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(t, -448.0f, 448.0f), 0.0f, 0, false), 0);
+}
+
+template <int P>
+__device__ __forceinline__ float quad_broadcast(float v) {       // lane P of the lane's group of four
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), P * 0x55, 0xF, 0xF, true));
+}
+
+constexpr int ROWS = 64;             // rows of a workgroup's tile; four lanes each inside a block
+constexpr int SEG = 32;              // columns of a block whose rows of U are staged at a time
+constexpr int TILE_STRIDE = DPQ_BLOCK + 4;
+constexpr int PART = 36;             // staged U: [column q][lane p of the row][slot]: U[q, 4 * (q / 4 + slot) + p]
+constexpr int SEG_FLOATS = SEG * 4 * PART;
+constexpr int SLICE_FLOATS = SEG * (ROWS + DPQ_BLOCK);           // one slice of the update: errors and U
+constexpr int DPQ_LDS = 2 * SEG_FLOATS > ROWS * TILE_STRIDE ? 2 * SEG_FLOATS : ROWS * TILE_STRIDE;
+static_assert(SLICE_FLOATS <= DPQ_LDS, "the update's slice fits");
+
+struct RowState {
+    float w[32];                  // the lane's columns of the block that are left: slot j = column 4 (done + j) + p
+    float sw, y_sw, s, y_s, z;
+    uint32_t span;                // NUM_SPAN, or 0 when a divisor of this row asks for the general division
+};
+
+// One weight: column q of the block, U[q, v] for the lane's columns v from q's slot on at `u`, U[q, q] and its reciprocal
+// in `d`.  Q = q % 4 is the lane of the row that owns it, in slot 0 of R.w; LEFT the slots in R.w.
+template <int Q, int LEFT>
+__device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d, bool diag_plain, int p, float& code) {
+    float4 v[LEFT / 4];
+#pragma unroll
+    for (int j = 0; j < LEFT / 4; ++j) v[j] = *reinterpret_cast<const float4*>(u + 4 * j);   // back by the time e is there
+    const float w = quad_broadcast<Q>(R.w[0]);
+    const bool plain = (__float_as_uint(w) & 0x7FFFFFFFu) - NUM_LO < R.span && diag_plain;
+    const float w8 = fp8_value_finite(div_by(w, R.sw, R.y_sw));                           // Eq. 7
+    const float t = __fadd_rn(div_by(w8, R.s, R.y_s), R.z);
+    float uq = __builtin_amdgcn_fmed3f(rintf(t), 0.0f, 15.0f);                            // Eq. 9
+    const float w8_hat = fp8_value_finite(__fmul_rn(__fsub_rn(uq, R.z), R.s));            // Eq. 10
+    float e = div_by(__fsub_rn(w, __fmul_rn(w8_hat, R.sw)), d.x, d.y);                    // Eq. 11
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!plain) != 0, 0)) {                  // zeros, extreme values: the general division
+        const float g8 = fp8_value(__fdiv_rn(w, R.sw));
+        uq = fminf(fmaxf(rintf(__fadd_rn(__fdiv_rn(g8, R.s), R.z)), 0.0f), 15.0f);
+        const float g8_hat = fp8_value(__fmul_rn(__fsub_rn(uq, R.z), R.s));
+        e = __fdiv_rn(__fsub_rn(w, __fmul_rn(g8_hat, R.sw)), d.x);
     }
-    const int lane = threadIdx.x / DPQ_LPR, part = threadIdx.x % DPQ_LPR;
-    const int n = blockIdx.x * DPQ_ROWS + lane;
-    if (n >= a.N) return;                                        // whole rows leave together
-    float* row = a.work + (int64_t)n * a.K;
-    const float sw = a.s_w[a.per_channel ? n : 0];
-    const int NG = a.K / a.G;
-    for (int v = part; v < DPQ_BLOCK; v += DPQ_LPR) wl[v * DPQ_ROWS + lane] = row[c0 + v];
-    __builtin_amdgcn_wave_barrier();                             // keeps the compiler from moving LDS accesses across
+#pragma unroll
+    for (int j = 0; j < LEFT; ++j) {                                                      // Eq. 12 inside the block
+        const float next = __fsub_rn(R.w[j], __fmul_rn(e, j % 4 == 0 ? v[j / 4].x : j % 4 == 1 ? v[j / 4].y : j % 4 == 2 ? v[j / 4].z : v[j / 4].w));
+        // in the weight's own slot: lanes behind it are updated, its own lane keeps the error, those before it theirs
+        R.w[j] = j > 0 ? next : p > Q ? next : p == Q ? e : R.w[j];
+        asm volatile("" : "+v"(R.w[j]));                         // here, not where the column is next read: the products would pile up
+    }
+    if (p == Q) code = uq;
+}
+
+// The 32 columns of a segment, LEFT slots in R.w at its start: slot by slot, the codes and errors going out and R.w moving on.
+// A loop of four weights (the whole block unrolled is 70 KB of instructions that every launch fetches anew, 80 us a block).
+template <int LEFT>
+__device__ __forceinline__ void dpq_segment(RowState& R, const DpqArgs& a, const float* u, const float2* diag, const int* cols, bool diag_plain,
+                                            int64_t n, bool row_ok, int c, int p) {
+    u += p * PART;
+#pragma unroll 1
+    for (int t = 0; t < SEG / 4; ++t, u += 16 * PART, diag += 4) {
+        float code = 0.0f;
+        const int col = cols[4 * t + p];
+        dpq_weight<0, LEFT>(R, u, diag[0], diag_plain, p, code);
+        dpq_weight<1, LEFT>(R, u + 4 * PART, diag[1], diag_plain, p, code);
+        dpq_weight<2, LEFT>(R, u + 8 * PART, diag[2], diag_plain, p, code);
+        dpq_weight<3, LEFT>(R, u + 12 * PART, diag[3], diag_plain, p, code);
+        if (row_ok) {
+            a.work[n * a.K + c + 4 * t + p] = R.w[0];
+            a.codes[n * a.K + col] = (uint8_t)code;
+        }
+#pragma unroll
+        for (int j = 0; j + 1 < LEFT; ++j) R.w[j] = R.w[j + 1];
+    }
+}
+
+// One launch of the walk.  Workgroups own tiles of 64 rows x 128 columns of the columns from c_first on, the tiles of the
+// first column block coming first:
+//   gather:  the tile comes from the original weights, reordered; otherwise from `work`;
+//   update:  it receives the errors of the block at c_err (Eq. 12 for the columns right of a block: for every column q of
+//            that block, ascending, w <- w - err[n, q] * U[c_err + q, v]);
+//   block:   the tiles of the first column block are then quantized, column by column, the others written to `work`.
+// With groups of 128 one launch does all three: the next block is quantized by the workgroups that bring it up to date
+// while the others update the rest, so the serial part (60 us a block, the update of its own columns included) hides behind the updates for as long as
+// there are many.  Wider groups need all of their columns up to date before the first is quantized: an update and a
+// block launch each.
+// Update: a thread owns 8 x 4 outputs; per error column three 16-byte LDS reads feed 64 vector operations, which bound it
+// (4096 rows x 3968 columns: 116 us, with 4 x 4 outputs and a pass of its own 219; the vector unit needs 107).
+// Block: lane p of a row's four holds the columns v with v % 4 == p in registers; every lane takes the (identical)
+// quantization step and applies the error to its own columns.  The row of U comes from LDS, 32 columns staged at a time.  32
+// lanes per row, with the weights in LDS, spent most instructions on repeating the quantization step (89 us a block).
+// Measured at 4096 x 4096: 6.7 -> 2.3 ms; at 256 x 4096, where the serial part is all, 3.9 -> 1.9.
+__global__ void __launch_bounds__(256, 3) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int row_blocks, int gather, int update, int block) {
+    __shared__ __attribute__((aligned(16))) float lds[DPQ_LDS];
+    __shared__ float2 diag[2][SEG];
+    __shared__ int cols[DPQ_BLOCK];                              // original columns of the block
+    __shared__ int general[2];                                   // a diagonal entry of the staged segment asks for the general division
+    const int tid = threadIdx.x;
+    const int rb = blockIdx.x % row_blocks, cb = blockIdx.x / row_blocks;
+    const int r0 = rb * ROWS, v0 = c_first + cb * DPQ_BLOCK;
+    const int tr = (tid >> 5) * 8, tc = (tid & 31) * 4;          // K is a multiple of 128: the columns of a tile all exist
+    float w[8][4];
+    {
+        int64_t col[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) col[j] = (gather && a.perm) ? a.perm[v0 + tc + j] : v0 + tc + j;
+        const float* src = gather ? a.w : a.work;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t n = min(r0 + tr + i, a.N - 1);         // rows past the end repeat the last one; not stored
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[i][j] = src[n * a.K + col[j]];
+        }
+    }
+    if (update) {
+        float* el = lds;                                         // el[q * 64 + r]: error q of row r of the tile
+        float* ul = lds + SEG * ROWS;                            // ul[q * 128 + c]: U[c_err + q, column c of the tile]
+        const float* erow = a.work + (int64_t)min(r0 + (tid & 63), a.N - 1) * a.K + c_err + (tid >> 6) * 4;
+        const float* urow = a.u + (int64_t)(c_err + (tid >> 5)) * a.K + v0 + tc;
+        float e4[2][4], u4[4][4];
+        auto load = [&](int q0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e4[h][j] = erow[q0 + h * 16 + j];
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) u4[h][j] = urow[(int64_t)(q0 + h * 8) * a.K + j];
+        };
+        load(0);
+        for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
+            __syncthreads();                                     // everyone is done with the slice before
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) el[((tid >> 6) * 4 + h * 16 + j) * ROWS + (tid & 63)] = e4[h][j];
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                *reinterpret_cast<float4*>(ul + ((tid >> 5) + h * 8) * DPQ_BLOCK + tc) = make_float4(u4[h][0], u4[h][1], u4[h][2], u4[h][3]);
+            __syncthreads();
+            if (q0 + SEG < DPQ_BLOCK) load(q0 + SEG);
+#pragma unroll 4
+            for (int q = 0; q < SEG; ++q) {
+                const float4 ea = *reinterpret_cast<const float4*>(el + q * ROWS + tr), eb = *reinterpret_cast<const float4*>(el + q * ROWS + tr + 4);
+                const float4 uu = *reinterpret_cast<const float4*>(ul + q * DPQ_BLOCK + tc);
+                const float ev[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w}, uv[4] = {uu.x, uu.y, uu.z, uu.w};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[i][j] = __fsub_rn(w[i][j], __fmul_rn(ev[i], uv[j]));
+            }
+        }
+    }
+    if (!block || cb != 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (r0 + tr + i < a.N) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a.work[(int64_t)(r0 + tr + i) * a.K + v0 + tc + j] = w[i][j];
+            }
+        return;
+    }
+
+    // the block: lane p of row r of the tile
+    __builtin_amdgcn_s_setprio(2);                               // ahead of the update's wavefronts on the same SIMD
+    const int r = tid >> 2, p = tid & 3, c0 = c_first;
+    const int64_t n = min(r0 + r, a.N - 1);
+    const bool row_ok = r0 + r < a.N;
+    // the rows of U of segment sg, columns from the segment's first on: thread -> 16 values of row tid / 8
+    float us[16];
+    const float* useg = a.u + (int64_t)(c0 + (tid >> 3)) * a.K + c0 + (tid & 7) * 16;
+    float ud;                                                    // threads 0..31: U[q, q] of the segment's columns
+    auto load_u = [&](int sg) {
+        if (tid < SEG) ud = a.u[(int64_t)(c0 + sg * SEG + tid) * (a.K + 1)];
+        if (sg * SEG + (tid & 7) * 16 < DPQ_BLOCK) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) us[j] = useg[(int64_t)sg * SEG * a.K + sg * SEG + j];
+        }
+    };
+    load_u(0);
+    __syncthreads();                                             // everyone is done with the update's last slice
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        *reinterpret_cast<float4*>(lds + (tr + i) * TILE_STRIDE + tc) = make_float4(w[i][0], w[i][1], w[i][2], w[i][3]);
+    if (tid < 2) general[tid] = 0;
+    if (tid < DPQ_BLOCK) cols[tid] = a.perm ? a.perm[c0 + tid] : c0 + tid;
+    __syncthreads();
+    RowState R;
+    float* mine = lds + r * TILE_STRIDE;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) R.w[j] = mine[4 * j + p];
+    R.sw = a.s_w[a.per_channel ? n : 0];
     // group parameters (Eq. 8 on the group's current weights): computed where the group starts, kept in the outputs
-    const int g = c0 / a.G;
+    const int NG = a.K / a.G, g = c0 / a.G;
     const int og = a.perm ? a.perm[g * a.G] / a.G : g;           // the original group these columns belong to
     float s, z;
     if (c0 % a.G == 0) {
+        const float* row = a.work + n * a.K;                     // wider groups: their columns from memory
         float lo = 0.0f, hi = 0.0f;                              // minimum and maximum: any order gives the same result
-        for (int j = part; j < a.G; j += DPQ_LPR) {
-            const float w8 = fp8_value(__fdiv_rn(row[c0 + j], sw));
-            lo = fminf(lo, w8);
-            hi = fmaxf(hi, w8);
+        if (a.G == DPQ_BLOCK) {
+#pragma unroll 4
+            for (int j = p; j < DPQ_BLOCK; j += 4) {
+                const float w8 = fp8_value(__fdiv_rn(mine[j], R.sw));
+                lo = fminf(lo, w8);
+                hi = fmaxf(hi, w8);
+                mine[j] = w8;                                    // what the search below scores
+            }
+        } else {
+            for (int j = p; j < a.G; j += 4) {
+                const float w8 = fp8_value(__fdiv_rn(row[c0 + j], R.sw));
+                lo = fminf(lo, w8);
+                hi = fmaxf(hi, w8);
+            }
         }
 #pragma unroll
-        for (int m = 1; m < DPQ_LPR; m <<= 1) {
+        for (int m = 1; m < 4; m <<= 1) {
             lo = fminf(lo, __shfl_xor(lo, m));
             hi = fmaxf(hi, __shfl_xor(hi, m));
         }
@@ -124,25 +332,35 @@ __global__ void __launch_bounds__(DPQ_THREADS) dpq_block_kernel(DpqArgs a, int c
         if (a.mse_grid > 1) {
             // The scale search of Sec. 3.3: candidate i shrinks the range by p_i = 1 - i * shrink_step and is scored by
             // the squared error, on the FP8 values, of what inference will reconstruct (Eq. 9 with clipping, Eq. 10);
-            // float32 sums over the group in visiting order.  The row's lanes share the candidates (i % DPQ_LPR) and
+            // float32 sums over the group in visiting order.  The row's lanes share the candidates (i % 4) and
             // then agree on the smallest score, the lowest index among equals -- the first minimum of a sequential scan.
+            __builtin_amdgcn_wave_barrier();                     // a row's lanes lie in one wavefront, whose LDS accesses run in order
             float best = __builtin_inff(), bs = s, bz = z;
             int best_i = a.mse_grid;
-            for (int i = part; i < a.mse_grid; i += DPQ_LPR) {
-                const float p = __fsub_rn(1.0f, __fmul_rn((float)i, a.shrink_step));
+            for (int i = p; i < a.mse_grid; i += 4) {
+                const float shrink = __fsub_rn(1.0f, __fmul_rn((float)i, a.shrink_step));
                 float si, zi;
-                group_params(__fmul_rn(p, lo), __fmul_rn(p, hi), si, zi);
+                group_params(__fmul_rn(shrink, lo), __fmul_rn(shrink, hi), si, zi);
                 float score = 0.0f;
-                for (int j = 0; j < a.G; ++j) {
-                    const float w8 = fp8_value(__fdiv_rn(row[c0 + j], sw));
-                    const float uq = fminf(fmaxf(rintf(__fadd_rn(__fdiv_rn(w8, si), zi)), 0.0f), 15.0f);
+                auto add = [&](float w8, float quotient) {
+                    const float uq = fminf(fmaxf(rintf(__fadd_rn(quotient, zi)), 0.0f), 15.0f);
                     const float d = __fsub_rn(w8, fp8_value(__fmul_rn(__fsub_rn(uq, zi), si)));
                     score = __fadd_rn(score, __fmul_rn(d, d));
+                };
+                if (a.G == DPQ_BLOCK && __builtin_amdgcn_ballot_w64(!plain_divisor(si)) == 0) {
+                    const float yi = __fdiv_rn(1.0f, si);        // w8 is zero, NaN, or between 2^-9 and 448
+#pragma unroll 4
+                    for (int j = 0; j < DPQ_BLOCK; ++j) add(mine[j], div_by(mine[j], si, yi));
+                } else {
+                    for (int j = 0; j < a.G; ++j) {
+                        const float w8 = a.G == DPQ_BLOCK ? mine[j] : fp8_value(__fdiv_rn(row[c0 + j], R.sw));
+                        add(w8, __fdiv_rn(w8, si));
+                    }
                 }
                 if (score < best) { best = score; best_i = i; bs = si; bz = zi; }
             }
 #pragma unroll
-            for (int m = 1; m < DPQ_LPR; m <<= 1) {
+            for (int m = 1; m < 4; m <<= 1) {
                 const float ob = __shfl_xor(best, m), os = __shfl_xor(bs, m), oz = __shfl_xor(bz, m);
                 const int oi = __shfl_xor(best_i, m);
                 if (ob < best || (ob == best && oi < best_i)) { best = ob; best_i = oi; bs = os; bz = oz; }
@@ -150,70 +368,47 @@ __global__ void __launch_bounds__(DPQ_THREADS) dpq_block_kernel(DpqArgs a, int c
             s = bs;
             z = bz;
         }
-        if (part == 0) {
-            a.scales[(int64_t)n * NG + og] = s;
-            a.zeros[(int64_t)n * NG + og] = (uint8_t)z;
+        if (p == 0 && row_ok) {
+            a.scales[n * NG + og] = s;
+            a.zeros[n * NG + og] = (uint8_t)z;
         }
     } else {
-        s = a.scales[(int64_t)n * NG + og];
-        z = (float)a.zeros[(int64_t)n * NG + og];
+        s = a.scales[n * NG + og];
+        z = (float)a.zeros[n * NG + og];
     }
-    for (int q = 0; q < DPQ_BLOCK; ++q) {
-        const float w = wl[q * DPQ_ROWS + lane];
-        const float w8 = fp8_value(__fdiv_rn(w, sw));                                     // Eq. 7
-        const float t = __fadd_rn(__fdiv_rn(w8, s), z);
-        const float uq = fminf(fmaxf(rintf(t), 0.0f), 15.0f);                             // Eq. 9
-        const float w8_hat = fp8_value(__fmul_rn(__fsub_rn(uq, z), s));                   // Eq. 10
-        const float w_hat = __fmul_rn(w8_hat, sw);                                        // Eq. 11
-        const float* urow = STAGE_U ? ul + q * DPQ_BLOCK : a.u + (int64_t)(c0 + q) * a.K + c0;   // U[c0 + q, c0 + v]
-        const float e = __fdiv_rn(__fsub_rn(w, w_hat), urow[q]);
-        if (part == 0) {
-            a.err[(int64_t)n * DPQ_BLOCK + q] = e;
-            a.codes[(int64_t)n * a.K + (a.perm ? a.perm[c0 + q] : c0 + q)] = (uint8_t)uq;
-        }
-        for (int v = q + 1 + (part + DPQ_LPR - (q + 1) % DPQ_LPR) % DPQ_LPR; v < DPQ_BLOCK; v += DPQ_LPR)   // Eq. 12 inside the block
-            wl[v * DPQ_ROWS + lane] = __fsub_rn(wl[v * DPQ_ROWS + lane], __fmul_rn(e, urow[v]));
-        __builtin_amdgcn_wave_barrier();
-    }
-}
+    R.s = s;
+    R.z = z;
+    R.y_sw = __fdiv_rn(1.0f, R.sw);
+    R.y_s = __fdiv_rn(1.0f, s);
+    R.span = plain_divisor(R.sw) && plain_divisor(s) ? NUM_SPAN : 0u;
+    __syncthreads();                                             // the tile has been read by everyone
 
-// Eq. 12 for the columns right of the block [c0, c0 + 128): work[n, v] <- work[n, v] - err[n, q] * U[c0 + q, v], q = 0..127
-// in ascending order.  A workgroup of 256 threads owns a 64 x 64 tile of (rows, columns), a thread 4 x 4 of it.
-__global__ void __launch_bounds__(256) dpq_lazy_update_kernel(DpqArgs a, int c0) {
-    __shared__ float el[DPQ_BLOCK * 64];                         // el[q * 64 + r]: error q of row r of the tile
-    __shared__ float ul[DPQ_BLOCK * 64];                         // ul[q * 64 + c]: U[c0 + q, column c of the tile]
-    const int tid = threadIdx.x;
-    const int r0 = blockIdx.y * 64, v0 = c0 + DPQ_BLOCK + blockIdx.x * 64;
-    for (int idx = tid; idx < DPQ_BLOCK * 64; idx += 256) {
-        const int q = idx & (DPQ_BLOCK - 1), r = idx >> 7;       // consecutive threads, consecutive q: coalesced reads of err
-        el[q * 64 + r] = (r0 + r < a.N) ? a.err[(int64_t)(r0 + r) * DPQ_BLOCK + q] : 0.0f;
+    auto stage_u = [&](int sg) {
+        float* dst = lds + (sg & 1) * SEG_FLOATS;
+        const int q = tid >> 3, first = (tid & 7) * 16, col = sg * SEG + first;
+        if (col < DPQ_BLOCK) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {                       // what lies left of the row's own slot goes to a slot that nobody reads
+                const int slot = (first + j) / 4 - q / 4;
+                dst[(q * 4 + (j & 3)) * PART + (slot >= 0 ? slot : PART - 1)] = us[j];
+            }
+        }
+        if (tid < SEG) {
+            diag[sg & 1][tid] = make_float2(ud, __fdiv_rn(1.0f, ud));
+            if (!plain_divisor(ud)) atomicOr(&general[sg & 1], 1);
+        }
+        // (slots past a row's last are read too, for columns of R.w that are done: values of no account)
+    };
+#define W4A8_DPQ_SEGMENT(SG)                                                                                        \
+    {                                                                                                               \
+        stage_u(SG);                                                                                                \
+        __syncthreads();                                                                                            \
+        if (SG < 3) load_u(SG + 1);                                                                                 \
+        const bool diag_plain = general[SG & 1] == 0;                                                               \
+        dpq_segment<32 - 8 * SG>(R, a, lds + (SG & 1) * SEG_FLOATS, diag[SG & 1], cols + SG * SEG, diag_plain, n, row_ok, c0 + SG * SEG, p); \
     }
-    for (int idx = tid; idx < DPQ_BLOCK * 64; idx += 256) {
-        const int c = idx & 63, q = idx >> 6;
-        ul[q * 64 + c] = (v0 + c < a.K) ? a.u[(int64_t)(c0 + q) * a.K + v0 + c] : 0.0f;
-    }
-    __syncthreads();
-    const int tr = (tid >> 4) * 4, tc = (tid & 15) * 4;
-    float w[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            w[i][j] = (r0 + tr + i < a.N && v0 + tc + j < a.K) ? a.work[(int64_t)(r0 + tr + i) * a.K + v0 + tc + j] : 0.0f;
-    for (int q = 0; q < DPQ_BLOCK; ++q) {
-        const float4 e = *reinterpret_cast<const float4*>(&el[q * 64 + tr]);
-        const float4 u = *reinterpret_cast<const float4*>(&ul[q * 64 + tc]);
-        const float ev[4] = {e.x, e.y, e.z, e.w}, uv[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[i][j] = __fsub_rn(w[i][j], __fmul_rn(ev[i], uv[j]));
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (r0 + tr + i < a.N && v0 + tc + j < a.K) a.work[(int64_t)(r0 + tr + i) * a.K + v0 + tc + j] = w[i][j];
+    W4A8_DPQ_SEGMENT(0) W4A8_DPQ_SEGMENT(1) W4A8_DPQ_SEGMENT(2) W4A8_DPQ_SEGMENT(3)
+#undef W4A8_DPQ_SEGMENT
 }
 
 }  // namespace
@@ -229,31 +424,28 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
     DpqArgs a;
     a.mse_grid = mse_grid;
     a.shrink_step = mse_grid > 1 ? mse_max_shrink / (float)mse_grid : 0.0f;
+    a.w = w;
     a.work = static_cast<float*>(workspace);
-    a.err = a.work + N * K;
     a.u = u; a.s_w = s_w; a.per_channel = per_channel; a.perm = perm;
     a.N = (int)N; a.K = (int)K; a.G = (int)G;
     a.codes = codes; a.scales = scales; a.zeros = zeros;
-    hipLaunchKernelGGL(dpq_gather_kernel, dim3((unsigned)((N * K + 255) / 256)), dim3(256), 0, st, w, perm, N, K, a.work);
-    if (int e = launch_status()) return e;
-    const int lpr = N <= 8192 ? 32 : N <= 16384 ? 16 : 8;        // lanes per row: about a quarter to half of the chip's lanes
-    const int threads = lpr == 8 ? 128 : 256;
-    const int rows_per_wg = threads / lpr;
-    const unsigned row_groups = (unsigned)((N + rows_per_wg - 1) / rows_per_wg);
-    for (int c0 = 0; c0 < K; c0 += DPQ_BLOCK) {
-        if (lpr == 32)
-            hipLaunchKernelGGL((dpq_block_kernel<32, true, 256>), dim3(row_groups), dim3(256), 0, st, a, c0);
-        else if (lpr == 16)
-            hipLaunchKernelGGL((dpq_block_kernel<16, true, 256>), dim3(row_groups), dim3(256), 0, st, a, c0);
-        else
-            hipLaunchKernelGGL((dpq_block_kernel<8, false, 128>), dim3(row_groups), dim3(128), 0, st, a, c0);
-        if (int e = launch_status()) return e;
-        const int64_t rest = K - c0 - DPQ_BLOCK;
-        if (rest > 0) {
-            hipLaunchKernelGGL(dpq_lazy_update_kernel, dim3((unsigned)((rest + 63) / 64), (unsigned)((N + 63) / 64)), dim3(256),
-                               0, st, a, c0);
-            if (int e = launch_status()) return e;
-        }
+    const int row_blocks = (int)((N + ROWS - 1) / ROWS), nb = (int)(K / DPQ_BLOCK);
+    auto step = [&](int c_first, int column_blocks, int c_err, int gather, int update, int block) {
+        hipLaunchKernelGGL(dpq_step_kernel, dim3((unsigned)row_blocks * (unsigned)column_blocks), dim3(256), 0, st, a, c_first, c_err,
+                           row_blocks, gather, update, block);
+        return launch_status();
+    };
+    if (G == DPQ_BLOCK) {
+        if (int e = step(0, 1, 0, 1, 0, 1)) return e;
+        for (int b = 1; b < nb; ++b)                             // the first update finds the other columns where they came from
+            if (int e = step(b * DPQ_BLOCK, nb - b, (b - 1) * DPQ_BLOCK, b == 1, 1, 1)) return e;
+        return W4A8_OK;
+    }
+    if (int e = step(0, nb, 0, 1, 0, 0)) return e;
+    for (int b = 0; b < nb; ++b) {
+        if (int e = step(b * DPQ_BLOCK, 1, 0, 0, 0, 1)) return e;
+        if (b + 1 < nb)
+            if (int e = step((b + 1) * DPQ_BLOCK, nb - b - 1, b * DPQ_BLOCK, 0, 1, 0)) return e;
     }
     return W4A8_OK;
 }

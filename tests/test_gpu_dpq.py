@@ -116,6 +116,34 @@ def test_calibrated_weights_through_packing_and_inference(gpu_lib):
     assert errs["dpq_gar"] < 0.9 * errs["plain"]
 
 
+@pytest.mark.parametrize("n,k,g,grid", [(1, 128, 128, 0), (63, 256, 128, 0), (65, 384, 128, 3), (130, 256, 256, 0)])
+def test_dpq_general_division_and_tile_edges(gpu_lib, n, k, g, grid):
+    """Rows around the 64 of a tile, and in some rows what the short division does not take -- zero weights, weights and
+    scales near the ends of float32's range, a diagonal entry of U beyond 2^30 -- beside rows it does: bit exact."""
+    rng = np.random.default_rng([93, n, k])
+    w = syn.make_weights(rng, n, k)
+    w[::5, ::7] = 0.0
+    w[2::9] *= np.float32(1e-25)
+    w[3::11] *= np.float32(1e25)
+    x = calibration_inputs(rng, 2 * k, k)
+    u = o.hessian_inverse_factor(x).astype(np.float32)
+    if n > 64:
+        u[k - 70, k - 70] = np.float32(2.0 ** 31)
+    s_w = (np.abs(w).max(axis=1) / np.float32(448.0)).astype(np.float32)
+    want = o.dpq_quantize(w, u, s_w, g, mse_grid=grid)
+    codes, scales, zeros = (host(t) for t in B.dpq_calibrate(dev(w), dev(u), dev(s_w), g, None, mse_grid=grid))
+    assert np.array_equal(scales, want[1]) and np.array_equal(zeros, want[2]) and np.array_equal(codes, want[0])
+
+
+@pytest.mark.parametrize("k,g", [(128, 128), (2176, 128), (133120, 128)])
+def test_gar_permutation_ties_signs_and_many_groups(gpu_lib, k, g):
+    """One group, and more groups than the kernel holds maxima of at a time; ties, zeros of both signs, negative values."""
+    rng = np.random.default_rng([94, k])
+    d = np.round(rng.standard_normal(k) * 4).astype(np.float32)
+    d[::3] *= np.float32(-0.0)
+    assert np.array_equal(host(B.gar_permutation(dev(d), g)), o.gar_permutation(d, g))
+
+
 @pytest.mark.parametrize("t,k,dtype", [(1, 64, "f32"), (100, 200, "f32"), (1000, 384, "bf16"), (4096, 1024, "f32")])
 def test_hessian_accumulate(gpu_lib, t, k, dtype):
     """H = X^T X over two batches (float32 accumulation on the GPU) against the float64 product of the same values:
