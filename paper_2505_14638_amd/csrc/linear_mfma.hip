@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(512, (KS * MF > 16 || MF * TPW > 16) ? 2 : 4) 
         AsymTable atab[TPW];                                     // asymmetric format: the next chunk's code - zero_point bytes
 #pragma unroll
         for (int j = 0; j < TPW; ++j)
-            atab[j] = ASYM2 ? asym_two_level_table(zp[j], next.s[j]) : ASYM ? asym_table(zp[j]) : AsymTable{{0u, 0u, 0u, 0u}};
+            atab[j] = ASYM2 ? asym_two_level_table_shared(zp[j], next.s[j], kq) : ASYM ? asym_table_shared(zp[j], kq) : AsymTable{{0u, 0u, 0u, 0u}};
         if (c < C) {
             // The MFMA steps run at raised wavefront priority, the head of a pass (copies) and its end (wait, barrier)
             // at the default one: a wavefront that has MFMAs to issue then wins arbitration over one that is waiting
@@ -316,8 +316,8 @@ __global__ void __launch_bounds__(512, (KS * MF > 16 || MF * TPW > 16) ? 2 : 4) 
 #pragma unroll
         for (int j = 0; j < TPW; ++j)
             wa.op[j] = TWO    ? slot_to_operand_two_level<true>(raw0[j], two_level_table(wa.s[j]))
-                       : ASYM2 ? slot_to_operand_asym(raw0[j], asym_two_level_table(zp0[j], wa.s[j]))
-                       : ASYM  ? slot_to_operand_asym(raw0[j], asym_table(zp0[j]))
+                       : ASYM2 ? slot_to_operand_asym(raw0[j], asym_two_level_table_shared(zp0[j], wa.s[j], kq))
+                       : ASYM  ? slot_to_operand_asym(raw0[j], asym_table_shared(zp0[j], kq))
                               : slot_to_operand<true>(raw0[j]);
     }
     lds_dma_wait_all();
@@ -456,10 +456,24 @@ void launch_one(const LinearArgs& a, dim3 grid, int grid_m, int grid_n, hipStrea
 
 }  // namespace
 
+namespace {
+
+// Microseconds a workgroup of the second tiling takes for a tile, constant + per 128-deep chunk: 512 x 128 tiles (0: not
+// used), 256 x 256, 256 x 128, and four-wavefront 256 x 128 tiles alone on a compute unit and two at a time; the share of a
+// round that a last round of at most 256 of those costs after full ones; and the PFLOP/s the first tiling is priced at.
+struct TileTimes {
+    double tall, tall_c, square, square_c, half, half_c, alone, alone_c, shared, shared_c, tail, first_rate;
+};
+constexpr TileTimes PLAIN_TIMES = {0.0, 0.0, 6.0, 1.66, 5.0, 1.08, 5.0, 1.28, 5.0, 1.875, 0.5, 1.35};       // code-exact, powers of two
+constexpr TileTimes TWO_LEVEL_TIMES = {8.0, 1.48, 10.0, 1.48, 2.0, 1.11, 8.0, 1.20, 8.0, 1.82, 0.5, 1.35};
+constexpr TileTimes ASYM_TIMES = {6.0, 1.82, 10.0, 1.82, 3.0, 1.37, 6.0, 1.66, 5.0, 2.35, 0.65, 1.4};
+constexpr TileTimes ASYM_TWO_TIMES = {7.0, 1.62, 8.0, 1.65, 3.0, 1.23, 6.0, 1.36, 6.0, 1.94, 0.5, 1.35};
+
+}  // namespace
+
 // Launch shape of the many-token kernels for a layer; requested values of mf / ks / tpw other than 0 are kept.
 // cfg2d >= 0 on return: the layer goes to the second tiling (linear_mfma2d.hip) with that workgroup tile.
-//  - In the code-exact and power-of-two modes the second tiling (a 2-D grid of wavefronts over 256-token tiles,
-//    expansion shared through LDS, persistent workgroups) competes with the first on estimated time.  A persistent
+//  - The second tiling (a 2-D grid of wavefronts over tiles of 256 or 512 tokens, expansion shared through LDS, persistent workgroups) competes with the first on estimated time.  A persistent
 //    workgroup needs a fixed time per tile, so what a grid costs is rounds x time per tile, and the last, partly filled
 //    round costs as much as a full one: 256 x 256 tiles (one workgroup per compute unit, 256 at a time), 256 x 128 tiles
 //    with eight wavefronts (256 at a time) or with four (two workgroups per compute unit, 512 at a time; a tile takes
@@ -469,6 +483,12 @@ void launch_one(const LinearArgs& a, dim3 grid, int grid_m, int grid_n, hipStrea
 //    at 0.265 C + flops / 1.35 PFLOP/s.  Against the rule this replaces (256 x 256 or
 //    four-wavefront 256 x 128 tiles once they number 200): 640 tokens on gate|up 125 -> 104 us, 3072 / 4096 tokens on
 //    QKV 113 / 120 -> 101 / 108, 2048 tokens on the O projection 47 -> 42, 192...256 tokens on gate|up 48 -> 42.
+//  - The two-level and the asymmetric formats spend more on a band's expansion (7 operations per four weights instead of 4,
+//    and a table per group), so their tiles take other times, and 512 x 128 tiles, which expand half as many bands per
+//    MFMA, are the fastest of all where they fill the chip: gate|up at 2048 tokens, quantization included, on 512 x 128 /
+//    256 x 256 / four-wavefront 256 x 128 tiles / first tiling: asymmetric 258 / 265 / 272 / 277 us, asymmetric two-level
+//    234 / 243 / 240 / 250, two-level 222 / 232 / 228 / 232.  The plain formats gain nothing from them (239 / 242 / 239,
+//    at 8192 tokens 924 / 894 / 944): their expansion hides behind the FMAs, and their list is without.
 //  - First tiling: tall token blocks amortize the nibble expansion over more MFMAs; two bands per wavefront halve the
 //    LDS reads per MFMA (the activation operand is reused); K-splits shorten the dependent chain of passes (each waits
 //    for the copies of the next) when the grid is too small to fill the chip, at the price of a wider activation block
@@ -478,20 +498,28 @@ bool mfma_launch_shape(int64_t M, int64_t K, int64_t N, int mode, int& mf, int& 
     cfg2d = -1;
     const int C = (int)(K / 128);
     const int n_tiles = (int)((N + 15) / 16);
-    if (mf == 0 && ks == 0 && tpw == 0 && (mode == MODE_CODE_EXACT || mode == MODE_POW2 || mode == MODE_TWO_LEVEL)) {
-        const int64_t tm = (M + 255) / 256, t1 = tm * ((N + 255) / 256), t2 = tm * ((N + 127) / 128);
+    if (mf == 0 && ks == 0 && tpw == 0) {
+        const TileTimes& t = mode == MODE_ASYM        ? ASYM_TIMES
+                             : mode == MODE_ASYM_TWO  ? ASYM_TWO_TIMES
+                             : mode == MODE_TWO_LEVEL ? TWO_LEVEL_TIMES
+                                                      : PLAIN_TIMES;
+        const int64_t tm = (M + 255) / 256, t0 = (M + 511) / 512 * ((N + 127) / 128), t1 = tm * ((N + 255) / 256), t2 = tm * ((N + 127) / 128);
         const double c = (double)C;
-        const double e1 = (double)((t1 + 255) / 256) * (6.0 + 1.66 * c);
-        const double e2 = (double)((t2 + 255) / 256) * (5.0 + 1.08 * c);
+        const double e0 = (double)((t0 + 255) / 256) * (t.tall + t.tall_c * c);
+        const double e1 = (double)((t1 + 255) / 256) * (t.square + t.square_c * c);
+        const double e2 = (double)((t2 + 255) / 256) * (t.half + t.half_c * c);
         const int64_t full = t2 / 512, rem = t2 % 512;
-        const double shared = 5.0 + 1.875 * c;                   // a tile while two workgroups share the compute unit
+        const double shared = t.shared + t.shared_c * c;         // a tile while two workgroups share the compute unit
         // the last, partly filled round: alone on their units the workgroups run faster, and after full rounds they start
-        // it while others still finish theirs (measured: about half a shared round then)
-        const double e4 = (double)full * shared + (rem == 0 ? 0.0 : rem > 256 ? shared : full > 0 ? 0.5 * shared : 5.0 + 1.28 * c);
-        const double first = 0.265 * c + 2.0 * (double)M * (double)K * (double)N / 1.35e9;
-        const double best = e1 < e2 ? (e1 < e4 ? e1 : e4) : (e2 < e4 ? e2 : e4);
+        // it while others still finish theirs (measured: about half a shared round then, 0.65 where the FMAs and the longer
+        // expansion come together)
+        const double e4 = (double)full * shared + (rem == 0 ? 0.0 : rem > 256 ? shared : full > 0 ? t.tail * shared : t.alone + t.alone_c * c);
+        const double first = 0.265 * c + 2.0 * (double)M * (double)K * (double)N / (t.first_rate * 1e9);
+        double best = e1 < e2 ? (e1 < e4 ? e1 : e4) : (e2 < e4 ? e2 : e4);
+        const bool tall = t.tall_c > 0.0 && e0 < best;
+        if (tall) best = e0;
         if (best < first) {
-            cfg2d = best == e1 ? 1 : best == e2 ? 2 : 4;
+            cfg2d = tall ? 0 : best == e1 ? 1 : best == e2 ? 2 : 4;
             return true;
         }
     }

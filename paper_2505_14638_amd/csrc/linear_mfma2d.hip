@@ -35,6 +35,10 @@
 // and stored as 4-byte pieces; the four bands of a wavefront complete 128-byte lines.  No LDS, no barriers.
 // The -8 pattern of the sign-magnitude nibbles comes out of the fast expansion as minus zero; the wavefronts that read a
 // band put it right in their registers on chunks whose group scale carries the packer's mark.
+// Asymmetric formats: the wavefront that expands a band forms the sixteen bytes its nibbles stand for, four lanes sharing the
+// work (asym_table_shared), once per band and chunk for the whole tile.  The first tiling, where every wavefront does that
+// for 16 channels and 256 tokens, took 278 us (1.73 PFLOP/s) for 2048 tokens on a 4096 -> 28672 layer in the two-level
+// reading, quantization included; this one takes 233 (2.06).
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -83,14 +87,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     // and operand reads at the head of a chunk fall into the other's MFMA steps; they keep ONE stage of weight operands,
     // which costs a second barrier per chunk (all operand registers read before the next chunk's operands are written).
     constexpr int B_STAGES = WAVES == 8 ? 2 : 1;
-    static_assert(MODE == MODE_CODE_EXACT || MODE == MODE_POW2 || MODE == MODE_TWO_LEVEL, "modes built for this tiling");
     constexpr bool POW2 = MODE == MODE_POW2;
     // Two-level reading (Eq. 6-11 taken literally): `scales` are FP8-domain group scales, the weight operand is
     // nearest_E4M3(code * s8[n, g]) -- formed by the wavefront that expands the band, which therefore loads the scales of
     // the bands it expands, not of those it multiplies with -- the sum over all of K stays in the matrix unit and the
     // output is scaled by s_x * w_out[n] (w_out[0] when per_channel is 0).
     constexpr bool TWO = MODE == MODE_TWO_LEVEL;
-    constexpr bool SUM_IN_MFMA = POW2 || TWO;                    // no FMAs in the loop
+    // Asymmetric formats: `scales` are the 80-byte records; the zero-points belong to the expansion, the group scales to
+    // the multiplying wavefronts (MODE_ASYM) or, two-level, to the expansion as well.
+    constexpr bool ASYM2 = MODE == MODE_ASYM_TWO, ASYM = MODE == MODE_ASYM || ASYM2;
+    constexpr bool OUT_SCALED = TWO || ASYM2;                    // the operand carries the group scale
+    constexpr bool SUM_IN_MFMA = POW2 || OUT_SCALED;             // no FMAs in the loop
+    constexpr int REC = ASYM ? ASYM_RECORD_BYTES : 64;           // bytes of scales (and zero-points) per band and group
     constexpr int BM = 16 * WM * WGM, BN = 16 * WN * WGN;
     constexpr int NBAND = WN * WGN;                              // weight bands of the workgroup tile
     constexpr int EPW = WN / WGM;                                // bands a wavefront expands per chunk
@@ -131,9 +139,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
 
     // state of the unit whose loads are being issued (the main loop's unit)
     int m0 = 0, bn = 0, split = 0, c_begin = 0, c_end = C;
-    const uint8_t* sbase[WN];                                    // scales of the wavefront's bands: + g * 64 + i * 4
+    const uint8_t* sbase[WN];                                    // scales of the wavefront's bands: + g * REC + i * 4
     const uint8_t* ebase[EPW];                                   // nibbles of the bands it expands: + c * 1024 + lane * 16
-    const uint8_t* esbase[EPW];                                  // two-level mode: their scales, + g * 64 + i * 4
+    const uint8_t* esbase[EPW];                                  // two-level and asymmetric modes: their scales, + g * REC + i * 4 (zero-points: + 64 + i)
     const uint8_t* xrow0 = x8;
     uint32_t xoff[DPW];                                          // lane's offset of page q from the tile's first row
     const uint32_t woff = lane * 16, soff = i * 4;
@@ -156,13 +164,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             const int t = min(bn * NBAND + wn * WN + j, n_tiles - 1);   // bands past the end reload the last one; not stored
-            sbase[j] = reinterpret_cast<const uint8_t*>(scales) + (int64_t)t * NG * 64;
+            sbase[j] = reinterpret_cast<const uint8_t*>(scales) + (int64_t)t * NG * REC;
         }
 #pragma unroll
         for (int t = 0; t < EPW; ++t) {
             const int tt = min(bn * NBAND + wn * WN + wm * EPW + t, n_tiles - 1);
             ebase[t] = packed + (int64_t)tt * C * 1024;
-            esbase[t] = reinterpret_cast<const uint8_t*>(scales) + (int64_t)tt * NG * 64;
+            esbase[t] = reinterpret_cast<const uint8_t*>(scales) + (int64_t)tt * NG * REC;
         }
         xrow0 = x8 + (int64_t)m0 * ldx8;
 #pragma unroll
@@ -185,19 +193,24 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     struct Set {
         float s[WN];                                             // group scales of the wavefront's bands
         u32x4 raw[EPW];                                          // nibbles of the bands it expands, one chunk further on
-        float es[EPW];                                           // two-level mode: the group scales that go with them
+        float es[EPW];                                           // two-level modes: the group scales that go with them
+        uint32_t ez[EPW];                                        // asymmetric modes: the zero-points
     };
     auto load_scales = [&](Set& S, int c) {
-        if (TWO) return;                                         // the multiplying wavefronts need no scales there
+        if (OUT_SCALED) return;                                  // the multiplying wavefronts need no scales there
 #pragma unroll
-        for (int j = 0; j < WN; ++j) S.s[j] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(sbase[j] + (int64_t)(c / cpg) * 64) + soff);
+        for (int j = 0; j < WN; ++j) S.s[j] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(sbase[j] + (int64_t)(c / cpg) * REC) + soff);
     };
     auto load_raw = [&](Set& S, int c) {
 #pragma unroll
         for (int t = 0; t < EPW; ++t) S.raw[t] = *reinterpret_cast<const W4A8_GLOBAL u32x4*>(uniform(ebase[t] + (int64_t)c * 1024) + woff);
-        if (TWO) {
+        if (OUT_SCALED) {
 #pragma unroll
-            for (int t = 0; t < EPW; ++t) S.es[t] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(esbase[t] + (int64_t)(c / cpg) * 64) + soff);
+            for (int t = 0; t < EPW; ++t) S.es[t] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(esbase[t] + (int64_t)(c / cpg) * REC) + soff);
+        }
+        if (ASYM) {
+#pragma unroll
+            for (int t = 0; t < EPW; ++t) S.ez[t] = uniform(esbase[t] + (int64_t)(c / cpg) * REC + 64)[(uint32_t)i];
         }
     };
     // the finished operand of expanded band t (registers 4h .. 4h+3) into stage `buf`
@@ -214,7 +227,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     auto chunk = [&](int c, Set& cur, Set& nxt) {
         const int buf = (c - c_begin) & 1;
         // what the previous chunk loaded is touched here, straight after the wait for all loads at that chunk's end
-        if (!TWO) {
+        if (!OUT_SCALED) {
 #pragma unroll
             for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(cur.s[j]));
         }
@@ -226,6 +239,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             for (int t = 0; t < EPW; ++t) {
                 asm volatile("" : "+v"(cur.es[t]));
                 tab[t] = two_level_table(cur.es[t]);
+            }
+        }
+        AsymTable atab[EPW];                                     // asymmetric modes: the bytes of the sixteen nibbles
+        if (ASYM) {
+#pragma unroll
+            for (int t = 0; t < EPW; ++t) {
+                asm volatile("" : "+v"(cur.ez[t]));
+                if (ASYM2) asm volatile("" : "+v"(cur.es[t]));
+                atab[t] = ASYM2 ? asym_two_level_table_shared(cur.ez[t], cur.es[t], kq) : asym_table_shared(cur.ez[t], kq);
             }
         }
         const int cn = min(c + 1, c_end - 1);                    // after the last chunk: copied again, never read
@@ -252,7 +274,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
         }
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
-            if (!TWO && any_marked(cur.s[j])) {                  // wave-uniform, rare: the band's group holds a -8
+            if (!OUT_SCALED && !ASYM && any_marked(cur.s[j])) {                  // wave-uniform, rare: the band's group holds a -8
 #pragma unroll
                 for (int e = 0; e < 8; ++e) bop[j][e] = (int)sm_fix_minus_eight((uint32_t)bop[j][e]);
             }
@@ -281,7 +303,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             // the copies of the next chunk's activations, one every few steps of the first half of the chunk
             if constexpr (st % DMA_EVERY == 0 && st / DMA_EVERY < DPW) stage_page(cn, buf ^ 1, st / DMA_EVERY);
             if (POW2) acc[f][j] = mfma_16x16x128_e4m3_scaled(xop, bop[j], acc[f][j], E8M0_ONE, e8m0_of(cur.s[j]));
-            if (TWO) acc[f][j] = mfma_16x16x128_e4m3(xop, bop[j], acc[f][j]);
+            if (OUT_SCALED) acc[f][j] = mfma_16x16x128_e4m3(xop, bop[j], acc[f][j]);
             const v4f p = SUM_IN_MFMA ? v4f{0.f, 0.f, 0.f, 0.f} : mfma_16x16x128_e4m3(xop, bop[j], v4f{0.f, 0.f, 0.f, 0.f});
             if constexpr (!SUM_IN_MFMA && st > 1) {
                 fold(std::integral_constant<int, (st - 2) / WN>{}, std::integral_constant<int, (st - 2) % WN>{}, p_prev2);
@@ -298,13 +320,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
                 const uint32_t src = cur.raw[t][d];
                 uint32_t o;
                 if (TWO) o = (e & 1) ? two_level_half_fast<4>(src, tab[t]) : two_level_half_fast<0>(src, tab[t]);
+                else if (ASYM) o = (e & 1) ? asym_half<4>(src, atab[t]) : asym_half<0>(src, atab[t]);
                 else o = (e & 1) ? sm_half_to_e4m3_fast<4>(src) : sm_half_to_e4m3_fast<0>(src);
                 keep_here(o);
                 eop[t][e] = o;
                 if (e == 3) publish(buf ^ 1, t, 0, eop[t][0], eop[t][1], eop[t][2], eop[t][3]);
                 if (e == 7) publish(buf ^ 1, t, 1, eop[t][4], eop[t][5], eop[t][6], eop[t][7]);
             }
-            constexpr int ALU = ((SUM_IN_MFMA || st < 2) ? 0 : 4) + (EXPAND ? 4 : 0);
+            constexpr int ALU = ((SUM_IN_MFMA || st < 2) ? 0 : 4) + (EXPAND ? (ASYM ? 7 : 4) : 0);
             if (j == 0 && f + 1 < WM) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads of the next block
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // this step's MFMA
             __builtin_amdgcn_sched_group_barrier(0x002, ALU, 0);                          // ALU work independent of it
@@ -337,22 +360,28 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     // the compiler puts in front of their first uses leave the copies alone).
     Set sa, sb;
     u32x4 raw0[EPW];
-    float es0[EPW];                                              // two-level mode: scales of chunk 0's bands
+    float es0[EPW];                                              // two-level modes: scales of chunk 0's bands
+    uint32_t ez0[EPW];                                           // asymmetric modes: their zero-points
     auto start_issue = [&]() {
 #pragma unroll
         for (int q = 0; q < DPW; ++q) stage_page(c_begin, 0, q);
 #pragma unroll
         for (int t = 0; t < EPW; ++t)
             raw0[t] = *reinterpret_cast<const W4A8_GLOBAL u32x4*>(uniform(ebase[t] + (int64_t)c_begin * 1024) + woff);
-        if (TWO) {
+        if (OUT_SCALED) {
 #pragma unroll
-            for (int t = 0; t < EPW; ++t) es0[t] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(esbase[t] + (int64_t)(c_begin / cpg) * 64) + soff);
+            for (int t = 0; t < EPW; ++t) es0[t] = *reinterpret_cast<const W4A8_GLOBAL float*>(uniform(esbase[t] + (int64_t)(c_begin / cpg) * REC) + soff);
+        }
+        if (ASYM) {
+#pragma unroll
+            for (int t = 0; t < EPW; ++t) ez0[t] = uniform(esbase[t] + (int64_t)(c_begin / cpg) * REC + 64)[(uint32_t)i];
         }
         load_scales(sa, c_begin);
 #pragma unroll
         for (int t = 0; t < EPW; ++t) {
             sa.raw[t] = u32x4{0u, 0u, 0u, 0u};
             sa.es[t] = 0.0f;
+            sa.ez[t] = 0u;
         }
         if (c_begin + 1 < c_end) load_raw(sa, c_begin + 1);
     };
@@ -361,7 +390,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
 #pragma unroll
         for (int t = 0; t < EPW; ++t) {
             const uint4 r = make_uint4(raw0[t][0], raw0[t][1], raw0[t][2], raw0[t][3]);
-            const v8i o = TWO ? slot_to_operand_two_level<true>(r, two_level_table(es0[t])) : slot_to_operand<false>(r);
+            const v8i o = TWO     ? slot_to_operand_two_level<true>(r, two_level_table(es0[t]))
+                          : ASYM2 ? slot_to_operand_asym(r, asym_two_level_table_shared(ez0[t], es0[t], kq))
+                          : ASYM  ? slot_to_operand_asym(r, asym_table_shared(ez0[t], kq))
+                                  : slot_to_operand<false>(r);
             publish(0, t, 0, (uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]);
             publish(0, t, 1, (uint32_t)o[4], (uint32_t)o[5], (uint32_t)o[6], (uint32_t)o[7]);
         }
@@ -391,7 +423,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             float so[WN];                                            // output scale of the lane's channel of band j
 #pragma unroll
             for (int j = 0; j < WN; ++j)
-                so[j] = TWO ? sx * w_out[per_channel ? min(n_wave + j * 16 + i, N - 1) : 0] : sx;
+                so[j] = OUT_SCALED ? sx * w_out[per_channel ? min(n_wave + j * 16 + i, N - 1) : 0] : sx;
 #pragma unroll
             for (int f = f0; f < f1; ++f) {
 #pragma unroll
@@ -565,6 +597,8 @@ void launch_cfg(const LinearArgs& a, dim3 grid, int grid_m, int grid_n, int grou
     } else {
         if (a.mode == MODE_POW2) W4A8_MFMA2D(MODE_POW2);
         else if (a.mode == MODE_TWO_LEVEL) W4A8_MFMA2D(MODE_TWO_LEVEL);
+        else if (a.mode == MODE_ASYM) W4A8_MFMA2D(MODE_ASYM);
+        else if (a.mode == MODE_ASYM_TWO) W4A8_MFMA2D(MODE_ASYM_TWO);
         else W4A8_MFMA2D(MODE_CODE_EXACT);
     }
 #undef W4A8_MFMA2D
@@ -597,8 +631,7 @@ int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, 
                          const float* scales, int64_t N, int32_t G, void* y, w4a8_dtype ydt, int64_t ldy, int cfg,
                          int group_m, int workgroups, int mode, const float* y_scale, hipStream_t st, int ksplit,
                          void* workspace, const float* w_out, int per_channel) {
-    if (mode != MODE_CODE_EXACT && mode != MODE_POW2 && mode != MODE_TWO_LEVEL) return W4A8_ERR_DTYPE;
-    if (mode == MODE_TWO_LEVEL && (!w_out || ksplit > 1 || ((int)ydt != W4A8_F32 && (int)ydt != W4A8_BF16))) return W4A8_ERR_DTYPE;
+    if ((mode == MODE_TWO_LEVEL || mode == MODE_ASYM_TWO) && (!w_out || ksplit > 1 || ((int)ydt != W4A8_F32 && (int)ydt != W4A8_BF16))) return W4A8_ERR_DTYPE;
     if (((int)ydt == YDT_E4M3 || (int)ydt == YDT_SILU_E4M3) && (mode != MODE_CODE_EXACT || !y_scale)) return W4A8_ERR_DTYPE;
     if ((int)ydt == YDT_SILU_E4M3 && N % 32 != 0) return W4A8_ERR_SHAPE;
     int bm, bn;

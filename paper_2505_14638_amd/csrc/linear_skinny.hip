@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(max_threads(MT * NT, MODE == MODE_ASYM || MODE
                 const MagTable tab = two_level_table(s);
                 wop = m8 ? slot_to_operand_two_level<true>(L.w[j], tab) : slot_to_operand_two_level<false>(L.w[j], tab);
             } else if (ASYM2) {
-                wop = slot_to_operand_asym(L.w[j], asym_two_level_table(L.z[j], s));
+                wop = slot_to_operand_asym(L.w[j], asym_two_level_table_shared(L.z[j], s, kq));
             } else if (ASYM) {
                 wop = slot_to_operand_half_offset(L.w[j]);       // code - 7.5
             } else {

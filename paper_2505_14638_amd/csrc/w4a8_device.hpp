@@ -190,6 +190,29 @@ __device__ __forceinline__ AsymTable asym_two_level_table(uint32_t z, float s8) 
     return T;
 }
 
+// The same two tables, formed by the wavefront together: z and s8 belong to a channel, which four lanes of a wavefront hold
+// (kq = lane / 16 = 0..3), so each of them forms the one dword t[kq], the half-wave and row swaps of the vector unit hand
+// it to the other three.  About 25 operations a lane instead of 75.  Every lane of the wavefront has to take part.
+__device__ __forceinline__ AsymTable asym_table_from_rows(uint32_t own) {
+    const auto halves = __builtin_amdgcn_permlane32_swap(own, own, false, false);    // rows 0 1 0 1 and 2 3 2 3
+    const auto even = __builtin_amdgcn_permlane16_swap(halves[0], halves[0], false, false);
+    const auto odd = __builtin_amdgcn_permlane16_swap(halves[1], halves[1], false, false);
+    return AsymTable{{(uint32_t)even[0], (uint32_t)even[1], (uint32_t)odd[0], (uint32_t)odd[1]}};
+}
+
+// kq 0, 1: codes 8 + 4 kq and up, kq 2, 3: codes 15 - 4 kq and down; the differences are small integers, exact in any order
+__device__ __forceinline__ AsymTable asym_table_shared(uint32_t z, int kq) {
+    const float first = (float)((kq < 2 ? 8 + 4 * kq : 15 - 4 * kq) - (int)(z & 15u)), step = kq < 2 ? 1.0f : -1.0f;
+    const uint32_t own = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(first, first + step, 0, false);
+    return asym_table_from_rows((uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(first + 2.0f * step, first + 3.0f * step, (int)own, true));
+}
+
+__device__ __forceinline__ AsymTable asym_two_level_table_shared(uint32_t z, float s8, int kq) {
+    const float first = (float)((kq < 2 ? 8 + 4 * kq : 15 - 4 * kq) - (int)(z & 15u)), step = kq < 2 ? 1.0f : -1.0f;
+    const uint32_t own = cvt2(first * s8, (first + step) * s8, 0u, false);
+    return asym_table_from_rows(cvt2((first + 2.0f * step) * s8, (first + 3.0f * step) * s8, own, true));
+}
+
 // E4M3 bytes of the half-integers h = +-(m + 0.5) of the four nibbles at bit offset SHIFT of the bytes of w.
 template <int SHIFT>
 __device__ __forceinline__ uint32_t asym_half_offset(uint32_t w) {

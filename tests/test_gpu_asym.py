@@ -229,3 +229,34 @@ def test_two_level_exact_integer_case_bit_for_bit_and_per_tensor_scale(gpu_lib, 
     y32t = host(B.linear_asym_two_level(dev(x8), sx_dev(0.5), packed, params, dev(np.full(1, 0.25, np.float32)), n, g,
                                         out_dtype=torch.float32))
     assert np.array_equal(y32t, (0.5 * 0.25 * acc).astype(np.float32))
+
+
+# ---- the second tiling of the many-token kernel, which the asymmetric formats take on large grids -------------------
+@pytest.mark.parametrize("two_level", [False, True])
+@pytest.mark.parametrize("m,k,n,g", [(300, 4096, 28700, 128), (500, 4096, 28700, 4096), (1030, 256, 24580, 128), (2048, 384, 5003, 384)])
+def test_second_tiling_against_the_few_token_kernel(gpu_lib, m, k, n, g, two_level):
+    """Ragged widths and token counts on grids that take 256 x 128, 512 x 128 and four-wavefront tiles, groups of one and
+    of several chunks.  Reference: the few-token kernel, 32 tokens at a time, which the oracle tests above cover; both
+    accumulate in float32 and differ in the order of K only, so each is within the layer's bound of the exact result:
+    |y - ref| <= 2 * 2e-3 * max(|ref|, rms / 4), rms the layer's own output (A / 64 of the bound, which is not formed here)."""
+    rng = np.random.default_rng([50, m, k, n, two_level])
+    gen = torch.Generator(device=DEV).manual_seed(int(rng.integers(1 << 30)))
+    x8 = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), sx_dev(0.01))
+    u = torch.randint(0, 16, (n, k), generator=gen, device=DEV, dtype=torch.uint8)
+    z = torch.randint(0, 16, (n, k // g), generator=gen, device=DEV, dtype=torch.uint8)
+    s = torch.rand((n, k // g), generator=gen, device=DEV) + 0.5
+    w_out = torch.rand(n, generator=gen, device=DEV) + 0.5
+    packed, params = B.pack_weights_asym(u, g, s, z)
+
+    def layer(x, dtype):
+        if two_level:
+            return B.linear_asym_two_level(x, sx_dev(0.01), packed, params, w_out, n, g, out_dtype=dtype)
+        return B.linear_asym(x, sx_dev(0.01), packed, params, n, g, out_dtype=dtype)
+
+    y32, y16 = layer(x8, torch.float32), layer(x8, torch.bfloat16)
+    ref = torch.cat([layer(x8[r : r + 32], torch.float32) for r in range(0, m, 32)])
+    bound = 4e-3 * torch.maximum(ref.abs(), ref.square().mean().sqrt() / 4)
+    worst = float(((y32 - ref).abs() / bound).max())
+    print(f"  asym second tiling {m}x{k}x{n} g{g} two_level={two_level}: worst err/bound {worst:.3e}", flush=True)
+    assert worst <= 1.0
+    assert torch.equal(y16, y32.to(torch.bfloat16))
