@@ -370,7 +370,6 @@ __global__ void __launch_bounds__(512, (KS * MF > 16 || MF * TPW > 16) ? 2 : 4) 
     constexpr int VEC = SILU ? 16 : 16 / sizeof(SlabT);          // outputs per 16-byte store
     constexpr int UPR = (SILU ? BN / 2 : BN) / VEC;              // 16-byte units per row
     const int n_block = bn * BN;
-    const bool vec_ok = (ldy % VEC == 0) && (reinterpret_cast<uintptr_t>(y) % 16 == 0);
 #pragma unroll
     for (int f0 = 0; f0 < MF; f0 += FR) {
         if (kg == 0) {
@@ -407,8 +406,8 @@ __global__ void __launch_bounds__(512, (KS * MF > 16 || MF * TPW > 16) ? 2 : 4) 
                                 silu_mul_f32(bf16_bits_to_f32(g[e + t]), bf16_bits_to_f32(g[16 + e + t]))));
                         w[e / 4] = cvt2(h[2] / yq, h[3] / yq, cvt2(h[0] / yq, h[1] / yq, 0u, false), true);
                     }
-                    if (vec_ok && n_out + 16 <= N / 2) {
-                        *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+                    if (n_out + 16 <= N / 2) {
+                        store_16_unaligned(dst, make_uint4(w[0], w[1], w[2], w[3]));
                     } else {
                         for (int e = 0; e < 16 && n_out + e < N / 2; ++e) dst[e] = (uint8_t)(w[e / 4] >> (8 * (e % 4)));
                     }
@@ -418,8 +417,8 @@ __global__ void __launch_bounds__(512, (KS * MF > 16 || MF * TPW > 16) ? 2 : 4) 
                 if (row < (MF - f0) * 16 && m < M && n < N) {
                     OutT* dst = y + (int64_t)m * ldy + n;
                     const OutT* src = slab + row * RS + col;
-                    if (vec_ok && n + VEC <= N) {
-                        *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+                    if (n + VEC <= N) {
+                        store_16_unaligned(dst, *reinterpret_cast<const uint4*>(src));
                     } else {
                         for (int e = 0; e < VEC && n + e < N; ++e) dst[e] = src[e];
                     }

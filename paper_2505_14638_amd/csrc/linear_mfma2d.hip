@@ -417,7 +417,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             constexpr int SEGS = ROW_B / 16, ROWS_PER_STORE = 64 / SEGS, STORES = 16 / ROWS_PER_STORE;
             static_assert(WAVES * 16 * RSB <= (B_STAGES == 2 ? STAGE : A_STAGE), "the wavefronts' slabs fit stage 1");
             uint8_t* const slab = lds + STAGE + wave * (16 * RSB);
-            const bool vec_ok = (ldy * EB) % 16 == 0 && reinterpret_cast<uintptr_t>(yo) % 16 == 0;
             const int n_wave = n_block + wn * WN * 16;               // first channel of the wavefront's bands
             const int seg = lane % SEGS, srow = lane / SEGS;
             float so[WN];                                            // output scale of the lane's channel of band j
@@ -455,8 +454,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
                     const int m = em0 + (wm * WM + f) * 16 + row, n = n_wave + seg * (16 / EB);
                     if (m < M && n < N) {
                         OutT* dst = yo + (int64_t)m * ldy + n;
-                        if (vec_ok && n + 16 / EB <= N) {
-                            *reinterpret_cast<uint4*>(dst) = w;
+                        if (n + 16 / EB <= N) {
+                            store_16_unaligned(dst, w);
                         } else {
                             const uint32_t e4[4] = {w.x, w.y, w.z, w.w};
                             for (int e = 0; e < 16 / EB && n + e < N; ++e) {
@@ -474,7 +473,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             SlabT* slab = reinterpret_cast<SlabT*>(lds + STAGE);
             constexpr int VEC = SILU ? 16 : 16 / sizeof(SlabT);  // outputs per 16-byte store
             constexpr int UPR = (SILU ? BN / 2 : BN) / VEC;      // 16-byte units per row
-            const bool vec_ok = (ldy % VEC == 0) && (reinterpret_cast<uintptr_t>(y) % 16 == 0);
 #pragma unroll
             for (int f = f0; f < f1; ++f) {
 #pragma unroll
@@ -502,8 +500,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
                                         silu_mul_f32(bf16_bits_to_f32(g[e + t]), bf16_bits_to_f32(g[16 + e + t]))));
                                 w[e / 4] = cvt2(h[2] / yq, h[3] / yq, cvt2(h[0] / yq, h[1] / yq, 0u, false), true);
                             }
-                            if (vec_ok && n_out + 16 <= N / 2) {
-                                *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+                            if (n_out + 16 <= N / 2) {
+                                store_16_unaligned(dst, make_uint4(w[0], w[1], w[2], w[3]));
                             } else {
                                 for (int e = 0; e < 16 && n_out + e < N / 2; ++e) dst[e] = (uint8_t)(w[e / 4] >> (8 * (e % 4)));
                             }
@@ -513,8 +511,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
                         if (m < M && n < N) {
                             OutT* dst = y + (int64_t)m * ldy + n;
                             const OutT* src = reinterpret_cast<const OutT*>(slab) + row * RS + col;
-                            if (vec_ok && n + VEC <= N) {
-                                *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+                            if (n + VEC <= N) {
+                                store_16_unaligned(dst, *reinterpret_cast<const uint4*>(src));
                             } else {
                                 for (int e = 0; e < VEC && n + e < N; ++e) dst[e] = src[e];
                             }

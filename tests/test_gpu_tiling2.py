@@ -186,3 +186,46 @@ def test_linear_with_workspace_at_k_8192(gpu_lib):
     y32 = host(B.linear(x8_d, sx_d, packed, scales, n, g, B.LAYOUT_TILED, out_dtype=torch.float32, workspace=ws))
     y16 = bf16_bits(B.linear(x8_d, sx_d, packed, scales, n, g, B.LAYOUT_TILED, out_dtype=torch.bfloat16, workspace=ws))
     check_outputs(y32, y16, ref, a, "K = 8192 with workspace")
+
+
+# ------------------------------------------------------------------------------------- rows that no 16-byte store is aligned to
+def into_odd_rows(m, n, dtype, off, pad):
+    """A buffer of odd row stride whose payload starts `off` elements in, filled with a byte pattern; (buffer, payload view)."""
+    size = torch.empty(0, dtype=dtype).element_size()
+    buf = torch.full((m, (n + pad) * size), 0x5A, dtype=torch.uint8, device=DEV).view(dtype)
+    return buf, buf[:, off : off + n]
+
+
+@pytest.mark.parametrize("path,p0,p1", [(2, t, 0) for t in TILES] + [(1, 16, 1), (1, 8, 2), (1, 4, 4)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, path, p0, p1, dtype):
+    """Rows at element-aligned addresses hold the bits that 16-byte aligned ones do (the last band ragged: element by
+    element), and what lies around them stays as it was."""
+    m, k, n, g = 130, 1024, 203, 128
+    x8, s_x, packed, scales, _, _ = realistic([79, m, k, n], m, k, n, g)
+    x8_d, sx_d = dev(x8), dev(np.array([s_x]))
+    want = torch.empty((m, 256), dtype=dtype, device=DEV)[:, :n]
+    B.linear_variant(x8_d, sx_d, packed, scales, n, g, want, path, p0, p1)
+    for off, pad in ((0, 0), (1, 2), (3, 6)):
+        buf, out = into_odd_rows(m, n, dtype, off, pad)
+        before = buf.clone()
+        B.linear_variant(x8_d, sx_d, packed, scales, n, g, out, path, p0, p1)
+        assert torch.equal(out, want), f"offset {off}"
+        out.copy_(before[:, off : off + n])
+        assert torch.equal(buf.view(torch.uint8), before.view(torch.uint8)), f"written outside the rows, offset {off}"
+
+
+@pytest.mark.parametrize("m,n", [(100, 480), (600, 8224)])       # first and second tiling
+def test_fp8_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, m, n):
+    k, g = 1024, 128
+    x8, s_x, packed, scales, _, _ = realistic([80, m, k, n], m, k, n, g)
+    x8_d, sx_d, next_s = dev(x8), dev(np.array([s_x])), dev(np.array([0.02], np.float32))
+    for call, width in ((B.linear_fp8_out, n), (B.linear_silu_mul_fp8_out, n // 2)):
+        size = n if width == n else n // 2
+        want = call(x8_d, sx_d, packed, scales, size, g, next_s, out=torch.empty((m, width), dtype=torch.uint8, device=DEV))
+        buf, out = into_odd_rows(m, width, torch.uint8, 5, 9)
+        before = buf.clone()
+        call(x8_d, sx_d, packed, scales, size, g, next_s, out=out)
+        assert torch.equal(out, want)
+        out.copy_(before[:, 5 : 5 + width])
+        assert torch.equal(buf, before)
