@@ -12,13 +12,15 @@
 //     deep: the trailing matrix is read and written once per pair) from every tile to the right.  What a step waits for is
 //     the next diagonal tile, so the workgroup that updates it goes on to factor and invert it, while the others still
 //     work on the rest of the matrix;
-//   inversion X = L^-1, doubling: the diagonal tiles' inverses are there, and a pair of inverted blocks X11, X22 of s tiles
-//     makes one of 2 s with X21 = -X22 (L21 X11): two launches per doubling, every tile of the block at once.
+//   inversion X = L^-1, by forward substitution in the same launches, one pair of columns behind:  X[k, :] = L_kk^-1 R[k, :]
+//     with R = I minus the products of the rows above.  Once X[k, :] and X[k + 1, :] are there, all rows of R below take their
+//     products (128 deep) in the launch that updates the single column k + 3, which waits for its diagonal tile and
+//     leaves the chip idle otherwise.
 // Every step is one launch over independent tiles, so no kernel waits on another workgroup.
 // Measured at 4096 features, against 64-deep updates on scalar FMAs, a diagonal tile in a launch of its own (112 us each) and
-// an inversion row by row: 11.4 -> 2.75 ms.  The chain of diagonal tiles bounds the factorization (64 times 25 us for the
-// launch that updates, factors and inverts one, about 4 us for the panel; the largest trailing update takes 57), the
-// matrix unit the inversion (the last doubling 2 x 176 us, 50 TFLOP/s).
+// an inversion row by row: 11.4 -> 2.75 ms; with the inversion inside the factorization's launches instead of after them
+// (twelve launches that double the inverted blocks, 630 us): 2.41 ms.  The chain of diagonal tiles bounds it (64 times 25 us for
+// the launch that updates, factors and inverts one, about 5 us for the panel; the largest trailing update takes 57).
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -107,7 +109,7 @@ __device__ __forceinline__ double inv_sqrt(double d) {
 }
 
 // Diagonal tile kb, whose lower triangle lies in `t` (row stride LDT): a[kb, kb] <- its lower Cholesky factor L (zeros
-// above the diagonal); dinv[kb] <- V = L^-1, row-major 64 x 64 (zeros above the diagonal).  A pivot that is not positive is
+// above the diagonal); dinv[kb], row-major 64 x 64, and x[kb, kb] <- V = L^-1 (zeros above the diagonal).  A pivot that is not positive is
 // reported through *info (1 + its index in the reversed order, first failure only); the results are then not finite.
 // This is the serial part of the factorization: 64 pivots, each waiting for the one before.  Four panels of 16 columns;
 // one wavefront factors a panel with a row per lane and its 16 columns in registers, the column just finished reaching
@@ -116,7 +118,7 @@ __device__ __forceinline__ double inv_sqrt(double d) {
 // four on the matrix unit.  V is put together from the inverses of the four 16 x 16
 // diagonal blocks, doubling twice; V's block (i, j) lies in the place of the tile's block (j, i), which L does not use.
 __device__ __forceinline__ void factor_tile(double* t, double* vd, double* __restrict__ a, int n, int kb, double* __restrict__ dinv,
-                                            int32_t* __restrict__ info) {
+                                            double* __restrict__ x, int32_t* __restrict__ info) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
     auto blk = [&](int r, int c) { return t + r * 16 * LDT + c * 16; };
@@ -239,6 +241,7 @@ __device__ __forceinline__ void factor_tile(double* t, double* vd, double* __res
         if (br == bc) v = vd[br * VD + (rr & 15) * 18 + (cc & 15)];
         else if (br > bc) v = blk(bc, br)[(rr & 15) * LDT + (cc & 15)];
         dv[idx] = v;
+        x[((int64_t)kb * TB + rr) * n + (int64_t)kb * TB + cc] = v;
     }
 }
 
@@ -314,34 +317,59 @@ __device__ __forceinline__ void each_element(v4d (&acc)[2][2], F&& f) {
 }
 
 // the first diagonal tile
-__global__ void __launch_bounds__(256) factor_first_kernel(double* __restrict__ a, int n, double* __restrict__ dinv, int32_t* __restrict__ info) {
+__global__ void __launch_bounds__(256) factor_first_kernel(double* __restrict__ a, int n, double* __restrict__ dinv, double* __restrict__ x,
+                                                           int32_t* __restrict__ info) {
     __shared__ __attribute__((aligned(16))) double lds[LDS_DOUBLES];
     for (int idx = threadIdx.x; idx < TB * TB; idx += 256) {
         const int r = idx >> 6, c = idx & 63;
         lds[r * LDT + c] = (c <= r) ? a[(int64_t)r * n + c] : 0.0;
     }
     __syncthreads();
-    factor_tile(lds, lds + TB * LDT, a, n, 0, dinv, info);
+    factor_tile(lds, lds + TB * LDT, a, n, 0, dinv, x, info);
 }
 
-// a[i, kb] <- a[i, kb] * (L_kk^-1)^T for the tiles i = kb + 1 + blockIdx.x below the diagonal tile
-__global__ void __launch_bounds__(256) scale_panel_kernel(double* a, int n, int kb, const double* dinv) {
+// Workgroups 0 .. panel - 1: a[i, kb] <- a[i, kb] * (L_kk^-1)^T for the tiles i = kb + 1 + blockIdx.x below the diagonal tile.
+// The others: X[kx, j] = L_kx,kx^-1 R[kx, j], j = 0, 1, .., in the place of R.
+__global__ void __launch_bounds__(256) scale_panel_kernel(double* a, double* x, int n, int kb, int panel, int kx, const double* dinv) {
     __shared__ __attribute__((aligned(16))) double lds[2 * SLICE];
-    const int i = kb + 1 + blockIdx.x;
-    double* tile = a + ((int64_t)i * TB) * n + (int64_t)kb * TB;
+    const int b = blockIdx.x;
     v4d acc[2][2] = {};
-    // B(k, c) = V(c, k) = dinv[c * 64 + k]
-    const double* dv = dinv + (int64_t)kb * TB * TB;
-    tile_mac<true>(acc, tile, n, [&](int k0) { return dv + k0; }, TB, TB, lds);
+    double* tile;
+    if (b < panel) {
+        tile = a + ((int64_t)(kb + 1 + b) * TB) * n + (int64_t)kb * TB;
+        // B(k, c) = V(c, k) = dinv[c * 64 + k]
+        const double* dv = dinv + (int64_t)kb * TB * TB;
+        tile_mac<true>(acc, tile, n, [&](int k0) { return dv + k0; }, TB, TB, lds);
+    } else {
+        tile = x + ((int64_t)kx * TB) * n + (int64_t)(b - panel) * TB;
+        tile_mac<false>(acc, dinv + (int64_t)kx * TB * TB, TB, [&](int k0) { return tile + (int64_t)k0 * n; }, n, TB, lds);
+    }
     each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
 }
 
-// a[i, j] -= sum over q in [kb, kb + depth / 64) of a[i, q] a[j, q]^T.  columns = 1: the tiles i >= j0 of tile column j0;
-// otherwise all tiles j0 <= j <= i.  Workgroup 0 has the tile (j0, j0), and factors it.
-__global__ void __launch_bounds__(256) trailing_update_kernel(double* a, int n, int kb, int depth, int j0, int columns, double* dinv,
-                                                              int32_t* info) {
+// Workgroups 0 .. trailing - 1: a[i, j] -= sum over q in [kb, kb + depth / 64) of a[i, q] a[j, q]^T.  columns = 1: the tiles
+// i >= j0 of tile column j0; otherwise all tiles j0 <= j <= i.  Workgroup 0 has the tile (j0, j0), and factors it.
+// The others: rows i0, i0 + 1, .. of the inversion, x_cols tiles each: R[i, j] -= sum over q in [xq, xq + xn) of L[i, q] X[q, j]
+// (X[q, j] is zero for q < j; R[i, j] for j >= xq has not been touched before and starts at zero).
+__global__ void __launch_bounds__(256) trailing_update_kernel(double* a, double* x, int n, int kb, int depth, int j0, int columns, int trailing,
+                                                              int xq, int xn, int i0, int x_cols, double* dinv, int32_t* info) {
     __shared__ __attribute__((aligned(16))) double lds[LDS_DOUBLES];
     const int b = blockIdx.x;
+    if (b >= trailing) {
+        const int i = i0 + (b - trailing) / x_cols, j = (b - trailing) % x_cols, q = max(xq, j);
+        double* tile = x + ((int64_t)i * TB) * n + (int64_t)j * TB;
+        const double* bp = x + ((int64_t)q * TB) * n + (int64_t)j * TB;
+        v4d acc[2][2] = {}, old[2][2] = {};
+        if (j < xq) each_element(old, [&](int r, int c, double& v) { v = tile[(int64_t)r * n + c]; });
+        tile_mac<false>(acc, a + ((int64_t)i * TB) * n + (int64_t)q * TB, n, [&](int k0) { return bp + (int64_t)k0 * n; }, n,
+                        (xq + xn - q) * TB, lds);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) acc[u][v] = old[u][v] - acc[u][v];
+        each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
+        return;
+    }
     int ti = b, tj = 0;
     if (columns != 1) {                                          // row ti, column tj of the triangle of tiles, row by row
         ti = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
@@ -357,49 +385,15 @@ __global__ void __launch_bounds__(256) trailing_update_kernel(double* a, int n, 
     // B(k, c) = a[j, q](c, k)
     tile_mac<true>(acc, a + ((int64_t)i * TB) * n + (int64_t)kb * TB, n, [&](int k0) { return bp + k0; }, n, depth, lds);
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = old[x][y] - acc[x][y];
+        for (int v = 0; v < 2; ++v) acc[u][v] = old[u][v] - acc[u][v];
     if (b == 0) {
         each_element(acc, [&](int r, int c, double v) { lds[r * LDT + c] = (c <= r) ? v : 0.0; });
         __syncthreads();
-        factor_tile(lds, lds + TB * LDT, a, n, j0, dinv, info);
+        factor_tile(lds, lds + TB * LDT, a, n, j0, dinv, x, info);
     } else {
         each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
-    }
-}
-
-// x[k, k] <- L_kk^-1 for every diagonal tile
-__global__ void __launch_bounds__(256) place_diagonal_kernel(double* __restrict__ x, int n, const double* __restrict__ dinv) {
-    const int k = blockIdx.x;
-    for (int idx = threadIdx.x; idx < TB * TB; idx += 256)
-        x[((int64_t)k * TB + (idx >> 6)) * n + (int64_t)k * TB + (idx & 63)] = dinv[(int64_t)k * TB * TB + idx];
-}
-
-// One doubling of the inverse.  Pair p = blockIdx.z has its tiles [b, b + s) and [b + s, min(b + 2 s, nb)), b = 2 s p,
-// inverted already; for the tile row i and column j of the block between them, the longest sums first:
-//   FIRST:   T[i, j] = sum over k >= j of L[b + s + i, b + k] X[b + k, b + j], kept in the tile (b + j, b + s + i) of a,
-//            above the diagonal, where L has nothing;
-//   else:    X[b + s + i, b + j] = -sum over k <= i of X[b + s + i, b + s + k] T[k, j].
-template <bool FIRST>
-__global__ void __launch_bounds__(256) join_inverses_kernel(double* a, double* x, int n, int s) {
-    __shared__ __attribute__((aligned(16))) double lds[2 * SLICE];
-    const int b = 2 * s * blockIdx.z, nb = n / TB;
-    const int j = FIRST ? blockIdx.y : blockIdx.x, i = FIRST ? blockIdx.x : s - 1 - (int)blockIdx.y;
-    if (b + s + i >= nb) return;                                 // the last pair may be cut off
-    v4d acc[2][2] = {};
-    if (FIRST) {
-        const double* bp = x + ((int64_t)(b + j) * TB) * n + (int64_t)(b + j) * TB;
-        tile_mac<false>(acc, a + ((int64_t)(b + s + i) * TB) * n + (int64_t)(b + j) * TB, n, [&](int k0) { return bp + (int64_t)k0 * n; }, n,
-                        (s - j) * TB, lds);
-        double* t = a + ((int64_t)(b + j) * TB) * n + (int64_t)(b + s + i) * TB;
-        each_element(acc, [&](int r, int c, double v) { t[(int64_t)r * n + c] = v; });
-    } else {
-        const double* bp = a + ((int64_t)(b + j) * TB) * n + (int64_t)(b + s) * TB;
-        tile_mac<false>(acc, x + ((int64_t)(b + s + i) * TB) * n + (int64_t)(b + s) * TB, n,
-                        [&](int k0) { return bp + (int64_t)(k0 % TB) * n + (k0 / TB) * TB; }, n, (i + 1) * TB, lds);
-        double* t = x + ((int64_t)(b + s + i) * TB) * n + (int64_t)(b + j) * TB;
-        each_element(acc, [&](int r, int c, double v) { t[(int64_t)r * n + c] = -v; });
     }
 }
 
@@ -425,25 +419,28 @@ int launch_hessian_inverse_factor(const float* h, int64_t K, double damp, const 
     double* scalars = dinv + K * TB;
     hipLaunchKernelGGL(damp_term_kernel, dim3(1), dim3(256), 0, st, h, n, damp, scalars, info);
     hipLaunchKernelGGL(gather_reversed_kernel, dim3(n), dim3(256), 0, st, h, perm, n, scalars, a);
-    hipLaunchKernelGGL(factor_first_kernel, dim3(1), dim3(256), 0, st, a, n, dinv, info);
+    hipLaunchKernelGGL(factor_first_kernel, dim3(1), dim3(256), 0, st, a, n, dinv, x, info);
     if (int e = launch_status()) return e;
+    // panel of column kb (`panel` tiles); row kx of the inverse
+    auto scale = [&](int kb, int panel, int kx) {
+        if (panel + kx > 0) hipLaunchKernelGGL(scale_panel_kernel, dim3(panel + kx), dim3(256), 0, st, a, x, n, kb, panel, kx, dinv);
+    };
+    // `trailing` tiles from column j0 on; rows i0 .. i0 + rows - 1 of R, tiles 0 .. cols - 1, take the rows xq .. xq + xn - 1 of X
+    auto update = [&](int kb, int depth, int j0, int columns, int trailing, int xq, int xn, int i0, int rows, int cols) {
+        if (trailing + rows * cols > 0)
+            hipLaunchKernelGGL(trailing_update_kernel, dim3(trailing + rows * cols), dim3(256), 0, st, a, x, n, kb, depth, j0, columns,
+                               trailing, xq, xn, i0, cols, dinv, info);
+    };
     for (int kb = 0; kb < nb; kb += 2) {
         const int below = nb - kb - 1, m = below - 1;            // tiles below column kb's diagonal tile, and column kb + 1's
-        hipLaunchKernelGGL(scale_panel_kernel, dim3(below), dim3(256), 0, st, a, n, kb, dinv);
-        hipLaunchKernelGGL(trailing_update_kernel, dim3(below), dim3(256), 0, st, a, n, kb, TB, kb + 1, 1, dinv, info);
-        if (m > 0) {
-            hipLaunchKernelGGL(scale_panel_kernel, dim3(m), dim3(256), 0, st, a, n, kb + 1, dinv);
-            hipLaunchKernelGGL(trailing_update_kernel, dim3(m * (m + 1) / 2), dim3(256), 0, st, a, n, kb, 2 * TB, kb + 2, m, dinv, info);
-        }
+        scale(kb, below, kb > 0 ? kb - 1 : 0);                   // and X[kb - 1, :], the second row of the pair before
+        // and the products of that pair's rows of X, for all rows below it
+        update(kb, TB, kb + 1, 1, below, kb - 2, 2, kb, kb > 0 ? nb - kb : 0, kb);
+        scale(kb + 1, m, kb);                                    // and X[kb, :]
+        update(kb, 2 * TB, kb + 2, m, m * (m + 1) / 2, kb, 1, kb + 1, 1, kb + 1);   // and its products for row kb + 1
         if (int e = launch_status()) return e;
     }
-    hipLaunchKernelGGL(place_diagonal_kernel, dim3(nb), dim3(256), 0, st, x, n, dinv);
-    for (int s = 1; s < nb; s *= 2) {
-        const dim3 grid(s, s, (nb + 2 * s - 1) / (2 * s));
-        hipLaunchKernelGGL(join_inverses_kernel<true>, grid, dim3(256), 0, st, a, x, n, s);
-        hipLaunchKernelGGL(join_inverses_kernel<false>, grid, dim3(256), 0, st, a, x, n, s);
-        if (int e = launch_status()) return e;
-    }
+    scale(0, 0, nb - 1);                                         // X[nb - 1, :]
     hipLaunchKernelGGL(write_factor_kernel, dim3(n), dim3(256), 0, st, x, n, u);
     return launch_status();
 }

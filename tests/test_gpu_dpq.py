@@ -209,8 +209,8 @@ def test_hessian_inverse_factor(gpu_lib, k, reorder, damp):
 
 
 @pytest.mark.parametrize("k", [256, 384, 640, 896])
-def test_hessian_inverse_factor_uneven_doublings(gpu_lib, k):
-    """4, 6, 10 and 14 tiles: the last pair of every doubling of the inverse whole, cut off, or left alone.  Tolerance as in
+def test_hessian_inverse_factor_few_pairs_of_tile_columns(gpu_lib, k):
+    """4, 6, 10 and 14 tiles: the inverse, one pair of tile columns behind the factorization, starts and ends.  Tolerance as in
     test_hessian_inverse_factor: float32 rounding of the result plus a conditioning allowance."""
     rng = np.random.default_rng([92, k])
     x = calibration_inputs(rng, 2 * k, k)
