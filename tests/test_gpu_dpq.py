@@ -116,10 +116,13 @@ def test_calibrated_weights_through_packing_and_inference(gpu_lib):
     assert errs["dpq_gar"] < 0.9 * errs["plain"]
 
 
-@pytest.mark.parametrize("n,k,g,grid", [(1, 128, 128, 0), (63, 256, 128, 0), (65, 384, 128, 3), (130, 256, 256, 0)])
+@pytest.mark.parametrize("n,k,g,grid", [(1, 128, 128, 0), (63, 256, 128, 0), (65, 384, 128, 3), (130, 256, 256, 0), (130, 256, 256, 20),
+                                        (65, 384, 128, 20), (3, 256, 256, 300), (9, 384, 384, 100), (70, 512, 256, 2),
+                                        (2079, 256, 128, 13), (2080, 256, 128, 13)])
 def test_dpq_general_division_and_tile_edges(gpu_lib, n, k, g, grid):
     """Rows around the 64 of a tile, and in some rows what the short division does not take -- zero weights, weights and
-    scales near the ends of float32's range, a diagonal entry of U beyond 2^30 -- beside rows it does: bit exact."""
+    scales near the ends of float32's range, a diagonal entry of U beyond 2^30 -- beside rows it does: bit exact.  The search
+    in a launch of its own (wide groups; more than 12 candidates and fewer than 160 rows for each) and beside the walk."""
     rng = np.random.default_rng([93, n, k])
     w = syn.make_weights(rng, n, k)
     w[::5, ::7] = 0.0
@@ -133,6 +136,32 @@ def test_dpq_general_division_and_tile_edges(gpu_lib, n, k, g, grid):
     want = o.dpq_quantize(w, u, s_w, g, mse_grid=grid)
     codes, scales, zeros = (host(t) for t in B.dpq_calibrate(dev(w), dev(u), dev(s_w), g, None, mse_grid=grid))
     assert np.array_equal(scales, want[1]) and np.array_equal(zeros, want[2]) and np.array_equal(codes, want[0])
+
+
+@pytest.mark.parametrize("g", [128, 1024])
+def test_scale_search_takes_less_time_than_the_walk(gpu_lib, g):
+    """100 candidates on 256 rows: 1.2 times the calibration without a search at either group size, 4 and 11 times with four
+    lanes scoring a row's candidates; with 32 lanes it was 2.1."""
+    n, k = 256, 1024
+    gen = torch.Generator(device=DEV).manual_seed(95)
+    w = torch.randn((n, k), generator=gen, device=DEV)
+    u = torch.triu(torch.randn((k, k), generator=gen, device=DEV) * 0.02, 1) + torch.eye(k, device=DEV)
+    s_w = w.abs().amax(dim=1) / 448.0
+
+    def ms(grid):
+        times = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            B.dpq_calibrate(w, u, s_w, g, None, mse_grid=grid)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return sorted(times)[3]
+
+    without, searched = ms(0), ms(100)
+    print(f"  groups of {g}: {without:.3f} ms without, {searched:.3f} ms with 100 candidates", flush=True)
+    assert searched < 2.0 * without
 
 
 @pytest.mark.parametrize("k,g", [(128, 128), (2176, 128), (133120, 128)])
