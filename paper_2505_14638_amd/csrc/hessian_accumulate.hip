@@ -13,11 +13,14 @@
 //     chain this replaces 3.8e-6.
 //   - float32 activations: 32x32x2 float32 MFMA, which takes its two products in order, each one a correctly rounded
 //     FMA -- the same chain per element, and the same bits, as a scalar loop over the tokens.
-// Measured at 8192 tokens x 4096 features, against 64 x 64 tiles of scalar FMAs over both triangles: bf16 4190 -> 340 us
-// (LDS reads of the operands bound it: two 16-byte reads per MFMA pair), float32 4040 -> 1390 us (the float32 matrix
+// Measured at 8192 tokens x 4096 features, against 64 x 64 tiles of scalar FMAs over both triangles: bf16 4190 -> 355 us
+// (LDS reads of the operands bound it: two 16-byte reads per MFMA pair), float32 4040 -> 1410 us (the float32 matrix
 // unit's rate, 153 TFLOP/s measured, takes 900).  The finer tiles even out the load where there are few: a launch is done
 // when the compute unit with the most tiles is.  bf16 takes 128 x 128 tiles from 400 of them on (276 of them at 2944
 // features 279 us, where 64 x 64 take about 220; 528 of them at 4096 features 339 us, 64 x 64 about 430), float32 always 64 x 64.
+// On few tokens reading and writing H is most of the time, which the finer tiles spread better: up to 512 tokens 64 x 64 (128 x
+// 128 / 64 x 64 tiles: 16 tokens x 5120 features 69 / 39 us, 512 tokens 92 / 64, 4096 features 54 / 48, 14336 features 696 / 637);
+// rows that are not aligned for 4-byte loads up to 32 tokens only (32 tokens x 4096 features 42 / 41, 64 tokens 46 / 47).
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -244,7 +247,7 @@ int launch_hessian_accumulate(const void* x, w4a8_dtype dt, int64_t T, int64_t K
     }
     const bool vec = addr % 4 == 0 && ldx % 2 == 0 && K % 2 == 0;
     const int64_t n = (K + 127) / 128;
-    if (n * (n + 1) / 2 >= 400) return launch_tile<uint16_t, 128>(static_cast<const uint16_t*>(x), T, K, ldx, vec, h, st);
+    if (n * (n + 1) / 2 >= 400 && T > (vec ? 512 : 32)) return launch_tile<uint16_t, 128>(static_cast<const uint16_t*>(x), T, K, ldx, vec, h, st);
     return launch_tile<uint16_t, 64>(static_cast<const uint16_t*>(x), T, K, ldx, vec, h, st);
 }
 
