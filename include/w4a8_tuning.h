@@ -43,12 +43,27 @@ int w4a8_linear_two_level_variant(const uint8_t* x8_dev, int64_t M, int64_t K, i
                                   int64_t ldy, int32_t tile, int32_t group_m_workgroups, void* stream);
 
 /*
+ * w4a8_linear_asym (w_out_scales_dev NULL) or w4a8_linear_asym_two_level on a launch shape chosen by the caller: path 1 or 2,
+ * param0 and param1 as in w4a8_linear_variant; arguments otherwise as in the layer's call.  For tests and tuning sweeps.
+ */
+int w4a8_linear_asym_variant(const uint8_t* x8_dev, int64_t M, int64_t K, int64_t ldx8, const float* x_scale_dev,
+                             const uint8_t* packed_dev, const void* params_dev, const float* w_out_scales_dev,
+                             int32_t per_channel, int64_t N, int32_t group_size, void* y_dev, w4a8_dtype y_dtype, int64_t ldy,
+                             int32_t path, int32_t param0, int32_t param1, void* stream);
+
+/*
  * The launch shape w4a8_linear chooses by itself for these sizes (tiled layout, bf16 output), in the terms of
  * w4a8_linear_variant: shape4[0] = path (0, 1 or 2; 3 = the second tiling with K ranges across workgroups, taken only
  * when the caller hands w4a8_linear a workspace -- with_workspace != 0), shape4[1] = param0, shape4[2] = param1,
  * shape4[3] = K ranges (path 3, else 0).  shape4 is HOST memory, four int32.  Nothing is launched.
  */
 int w4a8_linear_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t with_workspace, int32_t* shape4);
+
+/*
+ * The same for the layers of every weight format, which need no workspace: format 0 = w4a8_linear, 1 = w4a8_linear_two_level,
+ * 2 = w4a8_linear_asym, 3 = w4a8_linear_pow2, 4 = w4a8_linear_asym_two_level (W4A8_ERR_DTYPE otherwise).
+ */
+int w4a8_linear_format_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t format, int32_t* shape4);
 
 /*
  * The launch shape of the few-token kernel (path 0 above) for one of the forms that run on it, M <= 64:

@@ -36,6 +36,7 @@ SIGNATURES = {
     "w4a8_linear_variant": (_c_i32, [_c_vp, _c_i64, _c_i64, _c_i64, _c_vp, _c_vp, _c_vp, _c_i64, _c_i32, _c_vp,
                                      _c_i32, _c_i64, _c_i32, _c_i32, _c_i32, _c_vp]),
     "w4a8_linear_launch_shape": (_c_i32, [_c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_vp]),
+    "w4a8_linear_format_launch_shape": (_c_i32, [_c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_vp]),
     "w4a8_linear_few_token_shape": (_c_i32, [_c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_vp]),
     "w4a8_linear_splitk_variant": (_c_i32, [_c_vp, _c_i64, _c_i64, _c_i64, _c_vp, _c_vp, _c_vp, _c_i64, _c_i32, _c_vp,
                                             _c_i32, _c_i64, _c_i32, _c_i32, _c_vp, _c_sz, _c_vp]),
@@ -51,6 +52,8 @@ SIGNATURES = {
     "w4a8_pack_weights_asym": (_c_i32, [_c_vp, _c_i32, _c_vp, _c_vp, _c_i64, _c_i64, _c_i32, _c_vp, _c_vp, _c_vp]),
     "w4a8_linear_asym": (_c_i32, [_c_vp, _c_i64, _c_i64, _c_i64, _c_vp, _c_vp, _c_vp, _c_i64, _c_i32, _c_vp, _c_i32,
                                   _c_i64, _c_vp]),
+    "w4a8_linear_asym_variant": (_c_i32, [_c_vp, _c_i64, _c_i64, _c_i64, _c_vp, _c_vp, _c_vp, _c_vp, _c_i32, _c_i64, _c_i32,
+                                          _c_vp, _c_i32, _c_i64, _c_i32, _c_i32, _c_i32, _c_vp]),
     "w4a8_dequant_weights_asym": (_c_i32, [_c_vp, _c_vp, _c_i64, _c_i64, _c_i32, _c_vp, _c_vp]),
     "w4a8_linear_asym_two_level": (_c_i32, [_c_vp, _c_i64, _c_i64, _c_i64, _c_vp, _c_vp, _c_vp, _c_vp, _c_i32, _c_i64,
                                             _c_i32, _c_vp, _c_i32, _c_i64, _c_vp]),
@@ -221,6 +224,17 @@ def linear_launch_shape(m: int, k: int, n: int, group_size: int, with_workspace:
     return tuple(int(v) for v in out)
 
 
+FORMATS = {"code_exact": 0, "two_level": 1, "asym": 2, "pow2": 3, "asym_two_level": 4}
+
+
+def linear_format_launch_shape(m: int, k: int, n: int, group_size: int, fmt: str):
+    """(path, param0, param1, 0) of the launch the layer of a weight format chooses for these sizes."""
+    out = (ctypes.c_int32 * 4)()
+    _check(lib().w4a8_linear_format_launch_shape(m, k, n, group_size, FORMATS[fmt], ctypes.addressof(out)),
+           "w4a8_linear_format_launch_shape")
+    return tuple(int(v) for v in out)
+
+
 FEW_TOKEN_FORMS = {"linear": 0, "fp8_out": 1, "silu_mul_fp8_out": 2, "quantize_in": 3, "quantize_in_fp8_out": 4}
 
 
@@ -372,6 +386,19 @@ def dequant_weights_asym(packed: torch.Tensor, params: torch.Tensor, n: int, k: 
     _check(fn(packed.data_ptr(), params.data_ptr(), n, k, group_size, w8.data_ptr(), _stream()),
            "w4a8_dequant_weights_asym")
     return w8
+
+
+def linear_asym_variant(x8, x_scale, packed, params, w_out_scales, n, group_size, out, path: int, param0: int, param1: int = 0):
+    """w4a8_linear_asym_variant: the asymmetric layer (w_out_scales None) or its two-level reading on a chosen launch shape."""
+    m, k = x8.shape
+    per_channel = 1 if w_out_scales is not None and w_out_scales.numel() > 1 else 0
+    assert w_out_scales is None or (w_out_scales.numel() in (1, n) and w_out_scales.dtype == torch.float32)
+    _check(lib().w4a8_linear_asym_variant(x8.data_ptr(), m, k, x8.stride(0) if m > 1 else max(k, x8.stride(0)),
+                                          x_scale.data_ptr(), packed.data_ptr(), params.data_ptr(),
+                                          None if w_out_scales is None else w_out_scales.data_ptr(), per_channel, n, group_size,
+                                          out.data_ptr(), _dtype_code(out), out.stride(0) if m > 1 else max(n, out.stride(0)),
+                                          path, param0, param1, _stream()), "w4a8_linear_asym_variant")
+    return out
 
 
 def linear_asym_two_level(x8, x_scale, packed, params8, w_out_scales, n, group_size, out=None, out_dtype=torch.bfloat16):

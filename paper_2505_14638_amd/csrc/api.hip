@@ -278,28 +278,21 @@ int w4a8_linear_variant(const uint8_t* x8_dev, int64_t M, int64_t K, int64_t ldx
     return W4A8_ERR_SHAPE;
 }
 
-int w4a8_linear_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t with_workspace, int32_t* shape4) {
+// The launch shape of a layer of format `mode` without a workspace, in the terms of w4a8_linear_launch_shape.
+static int format_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int mode, int32_t* shape4) {
     if (!shape4) return W4A8_ERR_NULL;
     if (M < 1 || M > DIM_MAX) return W4A8_ERR_SHAPE;
     if (int e = check_weight_shape(N, K, group_size, W4A8_LAYOUT_TILED)) return e;
     shape4[0] = shape4[1] = shape4[2] = shape4[3] = 0;
-    if (takes_skinny_path(M, K, N) && !(with_workspace && prefers_split_k(M, K, N))) {
+    if (takes_skinny_path(M, K, N)) {
         int nt = 0, waves = 0, depth = 0;
-        if (!skinny_launch_shape(M, K, N, W4A8_BF16, MODE_CODE_EXACT, 0, nt, waves, depth)) return W4A8_ERR_SHAPE;
+        if (!skinny_launch_shape(M, K, N, W4A8_BF16, mode, 0, nt, waves, depth)) return W4A8_ERR_SHAPE;
         shape4[1] = nt;
         shape4[2] = waves | (depth << 8);
         return W4A8_OK;
     }
-    int cfg = 0, ksplit = 0;
-    if (with_workspace) mfma2d_choose_ksplit(M, K, N, cfg, ksplit);
-    if (ksplit > 1) {
-        shape4[0] = 3;
-        shape4[1] = cfg;
-        shape4[3] = ksplit;
-        return W4A8_OK;
-    }
     int mf = 0, ks = 0, tpw = 0, cfg2d = -1;
-    if (!mfma_launch_shape(M, K, N, MODE_CODE_EXACT, mf, ks, tpw, cfg2d)) return W4A8_ERR_SHAPE;
+    if (!mfma_launch_shape(M, K, N, mode, mf, ks, tpw, cfg2d)) return W4A8_ERR_SHAPE;
     if (cfg2d >= 0) {
         shape4[0] = 2;
         shape4[1] = cfg2d;
@@ -309,6 +302,24 @@ int w4a8_linear_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size
         shape4[2] = ks | (tpw << 8);
     }
     return W4A8_OK;
+}
+
+int w4a8_linear_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t with_workspace, int32_t* shape4) {
+    if (int e = format_launch_shape(M, K, N, group_size, MODE_CODE_EXACT, shape4)) return e;
+    int cfg = 0, ksplit = 0;
+    if (with_workspace && (!takes_skinny_path(M, K, N) || prefers_split_k(M, K, N))) mfma2d_choose_ksplit(M, K, N, cfg, ksplit);
+    if (ksplit > 1) {
+        shape4[0] = 3;
+        shape4[1] = cfg;
+        shape4[2] = 0;
+        shape4[3] = ksplit;
+    }
+    return W4A8_OK;
+}
+
+int w4a8_linear_format_launch_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t format, int32_t* shape4) {
+    if (format < MODE_CODE_EXACT || format > MODE_ASYM_TWO) return W4A8_ERR_DTYPE;
+    return format_launch_shape(M, K, N, group_size, format, shape4);
 }
 
 int w4a8_linear_few_token_shape(int64_t M, int64_t K, int64_t N, int32_t group_size, int32_t form, int32_t* shape3) {
@@ -488,6 +499,28 @@ int w4a8_linear_asym_two_level(const uint8_t* x8_dev, int64_t M, int64_t K, int6
                                     0, 0, 0, w_out_scales_dev, per_channel, MODE_ASYM_TWO, nullptr, st);
     return launch_linear_mfma_tiled(x8_dev, M, K, ldx8, x_scale_dev, packed_dev, params, N, group_size, y_dev, y_dtype, ldy,
                                     0, 0, 0, w_out_scales_dev, per_channel, MODE_ASYM_TWO, nullptr, st);
+}
+
+int w4a8_linear_asym_variant(const uint8_t* x8_dev, int64_t M, int64_t K, int64_t ldx8, const float* x_scale_dev,
+                             const uint8_t* packed_dev, const void* params_dev, const float* w_out_scales_dev,
+                             int32_t per_channel, int64_t N, int32_t group_size, void* y_dev, w4a8_dtype y_dtype, int64_t ldy,
+                             int32_t path, int32_t param0, int32_t param1, void* stream) {
+    const float* params = static_cast<const float*>(params_dev);
+    if (!valid_dtype(y_dtype)) return W4A8_ERR_DTYPE;
+    if (int e = check_linear(x8_dev, M, K, ldx8, x_scale_dev, packed_dev, params, N, group_size, W4A8_LAYOUT_TILED, y_dev,
+                             y_dtype, ldy))
+        return e;
+    if (reinterpret_cast<uintptr_t>(w_out_scales_dev) % 4) return W4A8_ERR_ALIGN;
+    if (per_channel != 0 && per_channel != 1) return W4A8_ERR_DTYPE;
+    if ((path != 1 && path != 2) || param0 < 0 || param1 < 0) return W4A8_ERR_SHAPE;
+    if (M == 0) return W4A8_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int mode = w_out_scales_dev ? MODE_ASYM_TWO : MODE_ASYM;
+    if (path == 1)
+        return launch_linear_mfma_tiled(x8_dev, M, K, ldx8, x_scale_dev, packed_dev, params, N, group_size, y_dev, y_dtype, ldy,
+                                        param0, param1 & 0xFF, param1 >> 8, w_out_scales_dev, per_channel, mode, nullptr, st);
+    return launch_linear_mfma2d(x8_dev, M, K, ldx8, x_scale_dev, packed_dev, params, N, group_size, y_dev, y_dtype, ldy, param0,
+                                param1 & 0xFF, param1 >> 8, mode, nullptr, st, 1, nullptr, w_out_scales_dev, per_channel);
 }
 
 static int dequant_asym(const uint8_t* packed_dev, const void* params_dev, int64_t N, int64_t K, int32_t group_size,

@@ -325,6 +325,37 @@ def test_launch_shape_is_built_and_consistent_for_every_size(L):
     assert n_checked == 6 * 7 * 23
 
 
+def test_launch_shapes_of_every_format(L):
+    """Always a built combination, the few-token kernel where w4a8_linear takes it, and for the code-exact format
+    w4a8_linear's own choice."""
+    first_tiling = {(16, 1, 1), (8, 1, 1), (8, 2, 1), (4, 1, 1), (4, 2, 1), (4, 4, 1)}
+    for fmt in B.FORMATS:
+        for k in (128, 1024, 4096, 14336, 28672):
+            for n in (16, 100, 4096, 6144, 28672):
+                for m in (1, 17, 33, 48, 64, 65, 128, 300, 640, 2048, 8192, 20000):
+                    path, p0, p1, ranges = B.linear_format_launch_shape(m, k, n, 128, fmt)
+                    plain = B.linear_launch_shape(m, k, n, 128)
+                    assert ranges == 0 and (path == 0) == (plain[0] == 0) and path in (0, 1, 2)
+                    assert path != 1 or (p0, p1 & 0xFF, p1 >> 8) in first_tiling
+                    assert path != 2 or p0 in ((0, 1, 2, 4) if fmt in ("two_level", "asym", "asym_two_level") else (1, 2, 4))
+                    assert fmt != "code_exact" or (path, p0, p1, ranges) == plain
+    assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, 5, P) == 4
+    assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, -1, P) == 4
+    assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, 2, None) == 1
+
+
+@pytest.mark.parametrize("m,k,n,want", [
+    (4096, 4096, 6144, (2, 2)),        # 256 x 128 of the second tiling 117 us; 512 x 128 125, first tiling 121
+    (3072, 28672, 8192, (2, 2)),       # 749; 812, 774
+    (5120, 14336, 4096, (2, 2)),       # 375; 409, 379
+    (1536, 4096, 6144, (2, 0)),        # 512 x 128 62 us; first tiling 72
+    (2048, 4096, 28672, (2, 0)),
+    (128, 4096, 6144, (1, 4)),         # 14 us; the second tiling 39 at the least
+])
+def test_asymmetric_layers_take_the_tile_that_measures_fastest(L, m, k, n, want):
+    assert B.linear_format_launch_shape(m, k, n, 128, "asym")[:2] == want
+
+
 def test_linear_quantize_in_fp8_out_validation(L):
     f = L.w4a8_linear_quantize_in_fp8_out
     # x, x_dtype, M, K, ldx, x_scale, packed, w_scales, N, G, y_scale, y8, ldy8, x8_out, stream
