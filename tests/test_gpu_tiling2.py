@@ -215,11 +215,15 @@ def test_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, path, p0, p1, dtype):
         assert torch.equal(buf.view(torch.uint8), before.view(torch.uint8)), f"written outside the rows, offset {off}"
 
 
-@pytest.mark.parametrize("m,n", [(100, 480), (600, 8224)])       # first and second tiling
-def test_fp8_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, m, n):
-    k, g = 1024, 128
-    x8, s_x, packed, scales, _, _ = realistic([80, m, k, n], m, k, n, g)
-    x8_d, sx_d, next_s = dev(x8), dev(np.array([s_x])), dev(np.array([0.02], np.float32))
+@pytest.mark.parametrize("m,k,n,path", [(100, 1024, 480, 1), (600, 1024, 8224, 1), (700, 1024, 16416, 2), (1000, 2048, 6176, 2)])
+def test_fp8_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, m, k, n, path):
+    """The E4M3 and the SiLU*mul output of either tiling (256 x 256 and 256 x 128 tiles of the second)."""
+    g = 128
+    assert B.linear_launch_shape(m, k, n, g)[0] == path
+    gen = torch.Generator(device=DEV).manual_seed(80)
+    sx_d, next_s = dev(np.array([0.01], np.float32)), dev(np.array([0.02], np.float32))
+    x8_d = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), sx_d)
+    packed, scales = B.pack_weights(torch.randn((n, k), generator=gen, device=DEV) * 0.02, g, B.LAYOUT_TILED)
     for call, width in ((B.linear_fp8_out, n), (B.linear_silu_mul_fp8_out, n // 2)):
         size = n if width == n else n // 2
         want = call(x8_d, sx_d, packed, scales, size, g, next_s, out=torch.empty((m, width), dtype=torch.uint8, device=DEV))
