@@ -232,13 +232,84 @@ def test_two_level_exact_integer_case_bit_for_bit_and_per_tensor_scale(gpu_lib, 
 
 
 # ---- the second tiling of the many-token kernel, which the asymmetric formats take on large grids -------------------
+TILES = (0, 1, 2, 3, 4, 5)
+
+
+def run_tile(x8, s_x, u, s, z, w_out, g, tile, p1=0, path=2):
+    """(float32, bf16 bits) of the layer on a launch shape, a tile of the second tiling; w_out None: the plain reading."""
+    m, n = x8.shape[0], u.shape[0]
+    packed, params = B.pack_weights_asym(dev(u), g, dev(s), dev(z))
+    y32 = torch.full((m, n), float("nan"), dtype=torch.float32, device=DEV)
+    y16 = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    for y in (y32, y16):
+        B.linear_asym_variant(dev(x8), sx_dev(s_x), packed, params, None if w_out is None else dev(w_out), n, g, y, path, tile, p1)
+    return host(y32), host(y16.view(torch.int16)).view(np.uint16)
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("two_level", [False, True])
+@pytest.mark.parametrize("m,k,n,g,p1", [(300, 1024, 520, 512, 0), (513, 256, 144, 256, 0), (70, 128, 20, 128, 0),
+                                        # persistent grids of 8 and 16 workgroups: several tiles per workgroup
+                                        (700, 384, 1100, 128, 1 | (8 << 8)), (1300, 640, 600, 128, 3 | (16 << 8))])
+def test_every_tile_of_the_second_tiling(gpu_lib, tile, two_level, m, k, n, g, p1):
+    """1, 2, 3, 5 and 8 chunks of K, groups of one or more of them, ragged tokens and channels: the bits of the first tiling with
+    K unsplit, which feeds the matrix unit the same operands in the same order, and within its own error of the oracle: it drops
+    what lies more than 14 bits below the largest of eight products, at most 7 * 2^-14 of the sum of magnitudes A (the
+    float32 roundings of at most 8 chunks and the scales, 2^-20 * A, are beside that nothing).  With one outlier channel in
+    50, as here, 4e-5 * A is met; the tests above hold the first tiling to 3.1e-5 * A on milder inputs."""
+    rng = np.random.default_rng([51, m, k, n])
+    w = syn.make_weights(rng, n, k)
+    x = syn.make_activations(rng, m, k, 0.02, 20.0)
+    s_x = syn.static_act_scale(x)
+    x8 = o.quantize_act(x, s_x)
+    if two_level:
+        u, z, s, s_w = literal_inputs(w, g)
+        ref, want8 = o.linear_ref_asym_paper_literal(x8, s_x, u, z, s, s_w, g)
+        a = float(np.float32(s_x)) * (np.abs(o.e4m3_decode(x8)) @ np.abs(o.e4m3_decode(want8)).T) * s_w.astype(np.float64)[None, :]
+    else:
+        u, s, z = o.asym_quantize_weights(w, g)
+        s_w = None
+        ref, a = o.linear_ref_asym(x8, s_x, u, z, s, g)
+    y32, y16 = run_tile(x8, s_x, u, s, z, s_w, g, tile, p1)
+    first, _ = run_tile(x8, s_x, u, s, z, s_w, g, 16, 1 | (1 << 8), path=1)
+    worst = float((np.abs(y32 - ref) / a).max())
+    print(f"  asym, second tiling, tile {tile}, two_level={two_level}, {m}x{k}x{n} g{g}: worst err/A {worst:.3e}", flush=True)
+    assert np.array_equal(y32, first)
+    assert worst <= 7 * 2.0 ** -14 + 2.0 ** -20
+    assert np.array_equal(y16, o.round_to_bf16_bits(y32.astype(np.float64)))
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("two_level", [False, True])
+def test_exact_integer_case_on_every_tile(gpu_lib, tile, two_level):
+    """Small-integer activations and power-of-two scales: float32 sums are exact in any order, the output is the integer
+    product bit for bit.  Every zero-point occurs; five chunks, three tokens and eleven channels past the tiles."""
+    rng = np.random.default_rng([52, two_level])
+    m, k, n, g = 515, 640, 267, 128
+    ng = k // g
+    xi = rng.integers(-4, 5, size=(m, k))
+    x8 = o.e4m3_encode(xi.astype(np.float32))
+    u = rng.integers(0, 16, size=(n, k), dtype=np.uint8)
+    z = rng.integers(0, 16, size=(n, ng), dtype=np.uint8)
+    e = rng.integers(-1, 3, size=(n, ng))
+    w_out = np.ldexp(1.0, rng.integers(-3, 2, size=n)).astype(np.float32) if two_level else None
+    d = u.reshape(n, ng, g).astype(np.int64) - z[:, :, None].astype(np.int64)
+    part = np.einsum("mgk,ngk->mng", xi.reshape(m, ng, g).astype(np.int64), d)
+    want = 0.5 * (part * np.ldexp(1.0, e)[None]).sum(axis=2) * (w_out[None, :] if two_level else 1.0)
+    y32, _ = run_tile(x8, 0.5, u, np.ldexp(1.0, e).astype(np.float32), z, w_out, g, tile)
+    assert len(np.unique(z)) == 16
+    assert np.array_equal(y32, want.astype(np.float32))
+
+
 @pytest.mark.parametrize("two_level", [False, True])
 @pytest.mark.parametrize("m,k,n,g", [(300, 4096, 28700, 128), (500, 4096, 28700, 4096), (1030, 256, 24580, 128), (2048, 384, 5003, 384)])
 def test_second_tiling_against_the_few_token_kernel(gpu_lib, m, k, n, g, two_level):
-    """Ragged widths and token counts on grids that take 256 x 128, 512 x 128 and four-wavefront tiles, groups of one and
-    of several chunks.  Reference: the few-token kernel, 32 tokens at a time, which the oracle tests above cover; both
-    accumulate in float32 and differ in the order of K only, so each is within the layer's bound of the exact result:
+    """Ragged widths and token counts on large grids, on the tiles the layer takes there (512 x 128 of the second tiling at
+    K = 4096), groups of one and of several chunks.  Reference: the few-token kernel, 32 tokens at a time, which the oracle
+    tests above cover.  Both accumulate in float32, in different orders of K, and the few-token kernel's plain reading
+    multiplies code - 7.5 and adds (7.5 - zero-point) * sum x, so each is within the layer's bound of the exact result:
     |y - ref| <= 2 * 2e-3 * max(|ref|, rms / 4), rms the layer's own output (A / 64 of the bound, which is not formed here)."""
+    assert k < 4096 or B.linear_format_launch_shape(m, k, n, g, "asym_two_level" if two_level else "asym")[:2] == (2, 0)
     rng = np.random.default_rng([50, m, k, n, two_level])
     gen = torch.Generator(device=DEV).manual_seed(int(rng.integers(1 << 30)))
     x8 = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), sx_dev(0.01))
