@@ -218,6 +218,18 @@ def test_hessian_accumulate_tile_edges(gpu_lib, t, k, dtype):
     assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("t,k", [(50, 70), (3, 128)])
+def test_hessian_accumulate_float32_is_a_chain_of_fmas(gpu_lib, t, k):
+    """float32 activations: every entry is the bits of one FMA per token, in their order.  Integers below 2^15: a product and
+    its sum with an accumulator below 2^37 are exact in float64, so rounding that once to float32 is the FMA."""
+    rng = np.random.default_rng([96, t, k])
+    x = rng.integers(-(1 << 15) + 1, 1 << 15, size=(t, k)).astype(np.float32)
+    want = np.zeros((k, k), np.float32)
+    for row in x.astype(np.float64):
+        want = (want.astype(np.float64) + np.outer(row, row)).astype(np.float32)
+    assert np.array_equal(host(B.hessian_accumulate(dev(x))), want)
+
+
 def test_hessian_accumulate_of_few_tokens_takes_no_longer_in_bf16(gpu_lib):
     """Reading and writing H is most of the time: 39 us for either type on 5120 features; on 128 x 128 tiles bf16 took 69."""
     k = 5120
