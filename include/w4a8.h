@@ -309,7 +309,8 @@ int w4a8_dequant_weights_asym_two_level(const uint8_t* packed_dev, const void* p
  *   codes_dev     out: unsigned 4-bit codes, one per byte, [N, K] in the original column order
  *   scales8_dev   out: float32 [N, K/group_size], the per-group scales of Eq. 8 (FP8 domain), with their original groups
  *   zeros_dev     out: bytes [N, K/group_size], the per-group zero-points of Eq. 8
- *   workspace_dev w4a8_dpq_workspace_bytes(N, K) bytes, 16-byte aligned
+ *   workspace_dev w4a8_dpq_workspace_bytes(N, K) bytes, 16-byte aligned: the current weights, N * K floats, and N * 128
+ *                 floats that are reserved (nothing reads or writes them)
  * Per group, at its start (on the group's current weights, the range extended to contain zero):
  *   W8 = val(nearest_E4M3(W / s_w)),  s = (max W8 - min W8) / 15 (1 if that is 0),  z = round(-min W8 / s);
  * per weight, in visiting order: w8 = val(nearest_E4M3(w / s_w)) (Eq. 7); u = clamp(round(w8 / s + z), 0, 15) (Eq. 9);

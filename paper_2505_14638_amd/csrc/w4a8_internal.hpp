@@ -82,8 +82,8 @@ int launch_linear_mfma_tiled(const uint8_t* x8, int64_t M, int64_t K, int64_t ld
                              int mode, const float* y_scale, hipStream_t st);
 // Second tiling of the many-token kernel (2-D grid of wavefronts, expansion shared through LDS, persistent workgroups).
 // cfg: a tile of mfma2d_tile; group_m = token blocks per super-column of the block order (0: chosen); workgroups = size of
-// the persistent grid (0: one per compute unit); mode: MODE_CODE_EXACT, MODE_POW2 or MODE_TWO_LEVEL (w_out, per_channel as
-// in the first tiling; float32 / bf16 outputs, no split of K); ksplit > 1: K is multiplied in that
+// the persistent grid (0: one per compute unit); mode: a WeightMode, the two-level ones with w_out and per_channel as in the
+// first tiling (float32 / bf16 outputs, no split of K); ksplit > 1: K is multiplied in that
 // many ranges by different workgroups, their float32 partial sums go through `workspace` (mfma2d_splitk_bytes).
 bool mfma2d_tile(int cfg, int& bm, int& bn);
 
@@ -128,7 +128,7 @@ int launch_gar_permutation(const float* hdiag, int64_t K, int32_t G, int32_t* pe
 size_t hessian_factor_workspace_bytes(int64_t K);
 int launch_hessian_inverse_factor(const float* h, int64_t K, double damp, const int32_t* perm, void* workspace, float* u,
                                   int32_t* info, hipStream_t st);
-// workspace: (N * K + N * 128) floats
+// workspace: N * K floats, the current weights
 int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int per_channel, const int32_t* perm,
                          int64_t N, int64_t K, int32_t G, uint8_t* codes, float* scales, uint8_t* zeros, void* workspace,
                          int mse_grid, float mse_max_shrink, hipStream_t st);
