@@ -603,7 +603,7 @@ def calibration(dev):
         y = B.linear_asym_two_level(rows, s_x, packed, params, s_w, n, G, out_dtype=torch.float32)
         err[name] = float(((y.double() - ref) ** 2).sum())
     return {"metric": "Hessian X^T X, its factor U, then GAR + DPQ (Alg. 1), on a 4096 x 4096 layer with 8192 calibration tokens",
-            "hessian_ms": round(hessian_ms, 2), "hessian_tflops_f32": round(2.0 * t * k * k / hessian_ms / 1e9, 1),
+            "hessian_ms": round(hessian_ms, 2), "hessian_tflops_f32": round(t * k * (k + 1.0) / hessian_ms / 1e9, 1),   # H is symmetric: one triangle is multiplied
             "factor_ms": round(factor_ms, 2),
             "calibrate_ms": round(ms, 2),
             "calibrate_with_scale_search_ms": round(ms_mse, 2),
