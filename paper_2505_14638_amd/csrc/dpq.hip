@@ -229,11 +229,14 @@ enum BlockStep { NO_BLOCK = 0, PARAMS_HERE = 1, PARAMS_GIVEN = 2 };
 // to date in a launch before that.  Wider groups need all of their columns up to date before the first is quantized: an
 // update and a block launch each.
 // Update: a thread owns 8 x 4 outputs; per error column three 16-byte LDS reads feed 64 vector operations, which bound it
-// (4096 rows x 3968 columns: 116 us, with 4 x 4 outputs and a pass of its own 219; the vector unit needs 107).
+// (4096 rows x 3968 columns: 112 us, with 4 x 4 outputs and a pass of its own 219; the vector unit needs 107).
 // Block: lane p of a row's four holds the columns v with v % 4 == p in registers; every lane takes the (identical)
 // quantization step and applies the error to its own columns.  The row of U comes from LDS, 32 columns staged at a time.  32
 // lanes per row, with the weights in LDS, spent most instructions on repeating the quantization step (89 us a block).
 // Measured at 4096 x 4096: 6.7 -> 2.3 ms; at 256 x 4096, where the serial part is all, 3.9 -> 1.9.
+// Three workgroups to a compute unit leave 168 registers, which spills 47 of them, all outside the loops over columns: once
+// per launch and 32 columns.  With two and no spills 256 x 4096 takes 1.79 ms instead of 1.90 and 4096 x 4096 2.32 instead of
+// 2.26, 16384 x 4096 7.13 instead of 6.38.
 __global__ void __launch_bounds__(256, 3) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int row_blocks, int gather, int update, int block,
                                                           int ready) {
     __shared__ __attribute__((aligned(16))) float lds[DPQ_LDS];

@@ -19,8 +19,9 @@
 // Every step is one launch over independent tiles, so no kernel waits on another workgroup.
 // Measured at 4096 features, against 64-deep updates on scalar FMAs, a diagonal tile in a launch of its own (112 us each) and
 // an inversion row by row: 11.4 -> 2.75 ms; with the inversion inside the factorization's launches instead of after them
-// (twelve launches that double the inverted blocks, 630 us): 2.41 ms.  The chain of diagonal tiles bounds it (64 times 25 us for
-// the launch that updates, factors and inverts one, about 5 us for the panel; the largest trailing update takes 57).
+// (twelve launches that double the inverted blocks, 630 us): 2.41 ms (2.41 to 2.6 over the runs since).  The chain of diagonal tiles bounds it: 22 to 24 us to
+// load, factor and invert one, in 64 launches that take 23 us at the least (38 with the rows of the inverse beside it, 59 with the
+// largest trailing update), and 5.7 us for each panel.
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -114,7 +115,7 @@ __device__ __forceinline__ double inv_sqrt(double d) {
 // This is the serial part of the factorization: 64 pivots, each waiting for the one before.  Four panels of 16 columns;
 // one wavefront factors a panel with a row per lane and its 16 columns in registers, the column just finished reaching
 // the other lanes by v_readlane, so that a pivot costs neither a barrier nor a trip through LDS (112 us a tile
-// with two barriers, a square root and a division per pivot, about 20 now); the trailing blocks are then updated by all
+// with two barriers, a square root and a division per pivot, 22 to 24 now); the trailing blocks are then updated by all
 // four on the matrix unit.  V is put together from the inverses of the four 16 x 16
 // diagonal blocks, doubling twice; V's block (i, j) lies in the place of the tile's block (j, i), which L does not use.
 __device__ __forceinline__ void factor_tile(double* t, double* vd, double* __restrict__ a, int n, int kb, double* __restrict__ dinv,

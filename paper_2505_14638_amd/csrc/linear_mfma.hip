@@ -475,6 +475,8 @@ constexpr TileTimes TWO_LEVEL_TIMES = {8.0, 1.48, 10.0, 1.48, 2.0, 1.11, 8.0, 1.
 // tiles chose 512 x 128 tiles where those are slower than the others: 4096 tokens on 4096 -> 6144 125 us (256 x 128 tiles 117),
 // 3072 on 28672 -> 8192 812 (749), 5120 on 14336 -> 4096 409 (375); 1.2 % in the mean, 15 % at most.
 constexpr TileTimes ASYM_TIMES = {5.8, 1.76, 7.93, 1.79, 4.75, 1.06, 5.67, 1.56, 7.48, 2.03, 0.69, 6.38, 0.11, 1.45, 5.75, 1.24, 8.36, 2.09, 0.59};
+// These and the two-level ones were chosen on sweeps of five layers; over the sizes above the choice is 1.1 and 1.3 % slower than
+// the best in the mean, a quarter at most (small grids, where the first tiling is taken and 256 x 128 tiles are faster).
 constexpr TileTimes ASYM_TWO_TIMES = {7.0, 1.62, 8.0, 1.65, 3.0, 1.23, 6.0, 1.36, 6.0, 1.94, 0.5, 0.0, 0.265, 1.35};
 
 // `tiles` tiles, two to a compute unit
@@ -530,10 +532,11 @@ bool first_tiling_shape(int64_t M, int64_t K, int64_t N, int& mf, int& ks, int& 
 //    QKV 113 / 120 -> 101 / 108, 2048 tokens on the O projection 47 -> 42, 192...256 tokens on gate|up 48 -> 42.
 //  - The two-level and the asymmetric formats spend more on a band's expansion (7 operations per four weights instead of 4,
 //    and a table per group), so their tiles take other times, and 512 x 128 tiles, which expand half as many bands per
-//    MFMA, are the fastest of all where they fill the chip: gate|up at 2048 tokens, quantization included, on 512 x 128 /
-//    256 x 256 / four-wavefront 256 x 128 tiles / first tiling: asymmetric 258 / 265 / 272 / 277 us, asymmetric two-level
-//    234 / 243 / 240 / 250, two-level 222 / 232 / 228 / 232.  The plain formats gain nothing from them (239 / 242 / 239,
-//    at 8192 tokens 924 / 894 / 944): their expansion hides behind the FMAs, and their list is without.
+//    MFMA, are among the fastest where they fill the chip: gate|up at 2048 tokens on 512 x 128 / 256 x 256 / 256 x 128 /
+//    four-wavefront 256 x 128 tiles / first tiling: asymmetric 254 / 262 / 271 / 257 / 267 us, asymmetric two-level 227 / 238 /
+//    247 / 226 / 237, two-level 229 / 259 / 254 / 251.  The plain formats gain nothing from them (512 x 128 / 256 x 256 /
+//    four-wavefront tiles, quantization included: 239 / 242 / 239, at 8192 tokens 924 / 894 / 944): their expansion hides
+//    behind the FMAs, and their list is without.
 //  - First tiling: tall token blocks amortize the nibble expansion over more MFMAs; two bands per wavefront halve the
 //    LDS reads per MFMA (the activation operand is reused); K-splits shorten the dependent chain of passes (each waits
 //    for the copies of the next) when the grid is too small to fill the chip, at the price of a wider activation block
