@@ -344,6 +344,17 @@ def test_launch_shapes_of_every_format(L):
     assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, 2, None) == 1
 
 
+def test_linear_asym_variant_validation(L):
+    def call(path=2, p0=0, p1=0, M=8, w_out=None, per_channel=0, x8=P, ydt=B.BF16, ldx8=256):
+        return L.w4a8_linear_asym_variant(x8, M, 256, ldx8, P, P, P, w_out, per_channel, 64, 128, P, ydt, 64, path, p0, p1, None)
+
+    assert call(M=0) == 0 and call(M=0, path=1, w_out=P, per_channel=1) == 0
+    assert call(path=0) == 2 and call(path=3) == 2 and call(p0=-1) == 2 and call(p1=-1) == 2
+    assert call(p0=6) == 2 and call(path=1, p0=5) == 2                          # no such tile, no such token block
+    assert call(w_out=P + 2) == 6 and call(per_channel=2) == 4 and call(ydt=2) == 4
+    assert call(x8=None) == 1 and call(x8=P + 8) == 6 and call(ldx8=128) == 2
+
+
 @pytest.mark.parametrize("m,k,n,want", [
     (4096, 4096, 6144, (2, 2)),        # 256 x 128 of the second tiling 117 us; 512 x 128 125, first tiling 121
     (3072, 28672, 8192, (2, 2)),       # 749; 812, 774

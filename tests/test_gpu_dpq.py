@@ -138,6 +138,22 @@ def test_dpq_general_division_and_tile_edges(gpu_lib, n, k, g, grid):
     assert np.array_equal(scales, want[1]) and np.array_equal(zeros, want[2]) and np.array_equal(codes, want[0])
 
 
+def test_scale_search_launches_with_columns_beside_the_walk(gpu_lib):
+    """2100 rows x 2560 features, 20 candidates, in reordered columns: the launch before a search brings 15 blocks of columns up
+    to date, the others go with the walk.  Rows are independent: some of them against the oracle, bit for bit."""
+    rng = np.random.default_rng(97)
+    n, k, g = 2100, 2560, 128
+    w = syn.make_weights(rng, n, k)
+    u = (np.triu(rng.standard_normal((k, k)) * 0.02, 1) + np.diag(rng.uniform(0.5, 1.5, size=k))).astype(np.float32)
+    s_w = (np.abs(w).max(axis=1) / np.float32(448.0)).astype(np.float32)
+    perm = o.gar_permutation(rng.random(k).astype(np.float32), g)
+    got = B.dpq_calibrate(dev(w), dev(u), dev(s_w), g, dev(perm.astype(np.int32)), mse_grid=20, mse_max_shrink=0.7)
+    rows = np.array([0, 63, 64, 1000, 2099])
+    want = o.dpq_quantize(w[rows], u, s_w[rows], g, perm=perm, mse_grid=20, mse_max_shrink=0.7)
+    for a, b in zip(got, want):
+        assert np.array_equal(host(a)[rows], b)
+
+
 def median_ms(call):
     times = []
     for _ in range(9):
