@@ -18,27 +18,32 @@
 //     single register: each MFMA starts from a zero accumulator and is folded into the running sum with four FMAs
 //     (Eq. 10 with the scale factored out of the group's sum), two steps later, when its result has long arrived; for
 //     power-of-two scales the matrix unit applies the scale itself and the sum stays in its accumulator;
-//   - one workgroup barrier per chunk.  Register-destination loads of a chunk (group scales, raw nibbles) are issued at
-//     its head and first touched right after the next barrier, when the wavefront has waited for all of its loads
-//     anyway, so that the compiler's own wait counts (which do not see the LDS copies) never ask for a load that was
-//     only just issued.  The nibbles travel as one 128-bit value: split into four, the register allocator moved parts of
-//     it right after the load, which waits for the load on the spot.
-// What bounds the loop is instruction issue: a SIMD's vector port is taken for about 16 cycles by an MFMA and 4 by any
-// other vector instruction, so 32 cycles of matrix work leave room for four of those -- the four FMAs; every further
-// instruction per MFMA (the expansion: 2 at 256 tokens per tile, 1 at 512) shows in the rate.
+//   - one workgroup barrier per chunk, ahead of the MFMAs of its last token block: their operands are in registers by then, and
+//     behind them the operands of the next chunk come from LDS, so that neither the barrier nor the first LDS reads of a chunk leave
+//     the matrix units idle.  With the barrier at the end of the chunk and its operands read at the head of the next, 512 x 128 tiles
+//     took 5 ... 13 % longer (8192 tokens of 4096 -> 28672: code-exact 925 -> 840 us, powers of two 824 -> 779, asymmetric two-level
+//     870 -> 839), the four-wavefront tiles 3 ... 6 %, 256 x 256 tiles 0 ... 5 %.  Nibbles are loaded into registers two chunks before they are
+//     expanded, scales one before they are used, and touched straight after the barrier of the chunk they were loaded in, when
+//     the wavefront has waited for all of its loads anyway, so that the compiler's own wait counts (which do not see the LDS
+//     copies) never ask for a load that was only just issued.  The nibbles travel as one 128-bit value: split into four, the
+//     register allocator moved parts of it right after the load, which waits for the load on the spot.
+// What bounds the loop is instruction issue, and on a full chip power: an MFMA takes the vector port for 16 of its 32 cycles and
+// any other vector instruction for 4, so there is room for four of those -- the four FMAs; every further instruction per MFMA
+// (the expansion: 2 at 256 tokens per tile, 1 at 512) shows in the rate.  MFMAs with their FMAs alone take 14.5 ns per SIMD on 64 busy units
+// (2.4 GHz) and 19.8 ns on 256 (1.75 GHz).
 // Tiles: a workgroup is resident for the whole launch and takes every (workgroups per XCD)-th tile of its XCD's
 // contiguous share of a block order that walks group_m token blocks per channel block, so the tiles an XCD works on at
 // a time cover a compact rectangle (one L2 per XCD).  The first loads and copies of the NEXT tile are issued before
 // the epilogue of the current one and finished in its middle: a tile's cold start (two memory round trips) is hidden.
-// Epilogue for float32 / bf16 outputs: straight from the accumulators -- neighbouring lanes exchange two of their four
-// tokens (DPP), so that a lane holds two adjacent channels of two tokens, converted by the hardware's bf16 conversion
-// and stored as 4-byte pieces; the four bands of a wavefront complete 128-byte lines.  No LDS, no barriers.
+// Epilogue: every wavefront converts its own sums and stores them through an LDS slab of its own, no barriers (linear_epilogue.hpp).
+// 256 x 128 and 128 x 128 tiles of eight wavefronts have room in registers for the operands of two chunks: linear_pipe.hip.
 // The -8 pattern of the sign-magnitude nibbles comes out of the fast expansion as minus zero; the wavefronts that read a
 // band put it right in their registers on chunks whose group scale carries the packer's mark.
 // Asymmetric formats: the wavefront that expands a band forms the sixteen bytes its nibbles stand for, four lanes sharing the
 // work (asym_table_shared), once per band and chunk for the whole tile.  The first tiling, where every wavefront does that
 // for 16 channels and 256 tokens, took 265 us (1.82 PFLOP/s) for 2048 tokens on a 4096 -> 28672 layer in the two-level
 // reading, the layer alone, 237 with the shared table; this one takes 227 (2.12).
+#include "linear_epilogue.hpp"
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -68,18 +73,13 @@ __device__ __forceinline__ const W4A8_GLOBAL uint8_t* uniform(const uint8_t* p) 
     return reinterpret_cast<const W4A8_GLOBAL uint8_t*>(((uint64_t)hi << 32) | lo);
 }
 
-// the value of the neighbouring lane (lane ^ 1)
-__device__ __forceinline__ uint32_t from_pair_lane(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1 /* quad_perm [1, 0, 3, 2] */, 0xF, 0xF, true);
-}
-
 template <typename OutT, int WGM, int WGN, int WM, int WN, int MODE>
 __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     const uint8_t* __restrict__ x8, int M, int64_t ldx8, const float* __restrict__ s_x,
     const uint8_t* __restrict__ packed, const float* __restrict__ scales, int N, int n_tiles, int C, int cpg, int NG,
     OutT* __restrict__ y, int64_t ldy, int grid_m, int grid_n, int group_m, const float* __restrict__ y_scale, int ksplit,
     int cps, int64_t split_stride, const float* __restrict__ w_out, int per_channel) {
-    constexpr int WAVES = WGM * WGN, THREADS = 64 * WAVES;
+    constexpr int WAVES = WGM * WGN;
     static_assert(WAVES == 8 || WAVES == 4, "one workgroup of eight wavefronts per compute unit, or two of four");
     static_assert(WN % WGM == 0, "every wavefront expands whole bands of its own");
     // Eight wavefronts own the compute unit's LDS (160 KB) and keep two stages of weight operands.  Four leave half of
@@ -108,17 +108,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     constexpr int DPW = BM / (8 * WAVES);                        // 1 KiB activation pages a wavefront copies per chunk
     static_assert(DPW % 2 == 0, "a wavefront copies whole 16-token blocks");
     constexpr int LOOP_BYTES = 2 * STAGE + (B_STAGES == 2 ? 0 : B_STAGE);
-    using SlabT = typename OutKind<OutT>::Slab;
-    constexpr bool SILU = OutKind<OutT>::SILU;
-    constexpr bool DIRECT = !SILU && sizeof(OutT) >= 2;          // float32 / bf16: stored from the accumulators
-    constexpr int RS = BN + 16 / sizeof(SlabT);                  // slab epilogue: row stride, rows stay 16-byte aligned
-    constexpr int SLAB_ROWS = 16 * WGM;                          // one 16-token block of every wavefront row per round
-    static_assert(DIRECT || SLAB_ROWS * RS * (int)sizeof(SlabT) <= (B_STAGES == 2 ? STAGE : A_STAGE), "the epilogue slab fits stage 1");
+    using Out = OutLayout<OutT, WN>;
+    static_assert(WAVES * Out::SLAB_BYTES <= (B_STAGES == 2 ? STAGE : A_STAGE), "the wavefronts' slabs fit stage 1");
     constexpr int STEPS = WM * WN;                               // MFMAs per chunk and wavefront
-    static_assert((8 * EPW) <= STEPS && STEPS % (8 * EPW) == 0, "an eighth of the expansion every few steps");
-    constexpr int STEPS_PER_EIGHTH = STEPS / (8 * EPW);
+    constexpr int SPAN = STEPS - WN;                             // those before the barrier: all but the last token block's
+    constexpr int EIGHTHS = 8 * EPW;                             // pieces of the next chunk's expansion, spread over them
     constexpr int DMA_EVERY = (STEPS / 2) / DPW > 0 ? (STEPS / 2) / DPW : 1;   // steps between two activation copies
-    static_assert(DMA_EVERY * DPW <= STEPS, "the copies fit the chunk");
+    constexpr int DMA_EARLY = (WN + DMA_EVERY - 1) / DMA_EVERY < DPW ? (WN + DMA_EVERY - 1) / DMA_EVERY : DPW;   // of them, behind the barrier of the chunk before
+    static_assert((DPW - 1 - DMA_EARLY) * DMA_EVERY < SPAN, "the copies are issued ahead of the barrier that they have to reach");
     __shared__ __attribute__((aligned(16))) uint8_t lds[LOOP_BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -221,57 +218,49 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
 
     v4f acc[WM][WN];
 
-    // One chunk: multiply chunk c (activations and weight operands in stage c % 2) with the scales cur.s; meanwhile
+    // What a chunk takes over from the one before: its weight operands, its first activation operand, and the products of
+    // the last two steps, which have yet to be folded in.
+    v8i bop[WN];
+    uint4 xa, xc;
+    v4f p_prev, p_prev2;
+    auto read_weights = [&](int buf, int j) {
+        const uint8_t* src = b_lds + (B_STAGES == 2 ? buf * STAGE : 0) + (wn * WN + j) * 2048 + lane * 16;
+        const uint4 lo = *reinterpret_cast<const uint4*>(src), hi = *reinterpret_cast<const uint4*>(src + 1024);
+        bop[j] = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+    };
+    auto read_tokens = [&](int buf, int f) {
+        xa = *reinterpret_cast<const uint4*>(lds + buf * STAGE + xa_off + f * 2048);
+        xc = *reinterpret_cast<const uint4*>(lds + buf * STAGE + xc_off + f * 2048);
+    };
+    // step (f, j)'s product under the scales of S
+    auto fold = [&](const Set& S, auto FP, auto JP, const v4f& p) {
+        constexpr int fp = decltype(FP)::value, jp = decltype(JP)::value;
+        const float sc = fabsf(S.s[jp]);                         // the sign bit is the packer's mark, not part of the scale
+        acc[fp][jp][0] = fmaf(sc, p[0], acc[fp][jp][0]);
+        acc[fp][jp][1] = fmaf(sc, p[1], acc[fp][jp][1]);
+        acc[fp][jp][2] = fmaf(sc, p[2], acc[fp][jp][2]);
+        acc[fp][jp][3] = fmaf(sc, p[3], acc[fp][jp][3]);
+    };
+
+    // One chunk: multiply chunk c (activations in stage c % 2, weight operands in registers) with the scales cur.s; meanwhile
     // expand cur.raw (chunk c + 1) into the other stage, copy the activations of chunk c + 1 there, and load the scales
-    // of chunk c + 1 and the nibbles of chunk c + 2 into nxt.
+    // of chunk c + 1 into nxt.  The barrier stands before the MFMAs of the last token block: its operands are in registers by
+    // then, so the stage is free, and behind them the operands of chunk c + 1 come from LDS, the first copies of chunk c + 2
+    // and the nibbles of chunk c + 3 (into cur, which is done with its own) are issued.
     auto chunk = [&](int c, Set& cur, Set& nxt) {
         const int buf = (c - c_begin) & 1;
-        // what the previous chunk loaded is touched here, straight after the wait for all loads at that chunk's end
-        if (!OUT_SCALED) {
-#pragma unroll
-            for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(cur.s[j]));
-        }
-#pragma unroll
-        for (int t = 0; t < EPW; ++t) asm volatile("" : "+v"(cur.raw[t]));   // as one 128-bit value: it stays in the registers it was loaded into
         MagTable tab[EPW];                                       // two-level mode: nearest_E4M3(m * s8) for the lane's channel
         if (TWO) {
 #pragma unroll
-            for (int t = 0; t < EPW; ++t) {
-                asm volatile("" : "+v"(cur.es[t]));
-                tab[t] = two_level_table(cur.es[t]);
-            }
+            for (int t = 0; t < EPW; ++t) tab[t] = two_level_table(cur.es[t]);
         }
         AsymTable atab[EPW];                                     // asymmetric modes: the bytes of the sixteen nibbles
         if (ASYM) {
 #pragma unroll
-            for (int t = 0; t < EPW; ++t) {
-                asm volatile("" : "+v"(cur.ez[t]));
-                if (ASYM2) asm volatile("" : "+v"(cur.es[t]));
+            for (int t = 0; t < EPW; ++t)
                 atab[t] = ASYM2 ? asym_two_level_table_shared(cur.ez[t], cur.es[t], kq) : asym_table_shared(cur.ez[t], kq);
-            }
         }
         const int cn = min(c + 1, c_end - 1);                    // after the last chunk: copied again, never read
-        if (c + 1 < c_end) load_scales(nxt, c + 1);
-        if (c + 2 < c_end) load_raw(nxt, c + 2);
-
-        __builtin_amdgcn_s_setprio(1);
-        // the wavefront's weight operands of this chunk
-        v8i bop[WN];
-        const uint8_t* bsrc = b_lds + (B_STAGES == 2 ? buf * STAGE : 0) + (wn * WN) * 2048 + lane * 16;
-        const uint8_t* xb = lds + buf * STAGE;
-        uint4 xa = *reinterpret_cast<const uint4*>(xb + xa_off);
-        uint4 xc = *reinterpret_cast<const uint4*>(xb + xc_off);
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            const uint4 lo = *reinterpret_cast<const uint4*>(bsrc + j * 2048);
-            const uint4 hi = *reinterpret_cast<const uint4*>(bsrc + j * 2048 + 1024);
-            bop[j] = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-        }
-        if (B_STAGES == 1) {
-            // one stage of weight operands: everybody's operand registers are filled before anybody publishes the next chunk's
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __syncthreads();
-        }
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             if (!OUT_SCALED && !ASYM && any_marked(cur.s[j])) {                  // wave-uniform, rare: the band's group holds a -8
@@ -280,43 +269,62 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             }
         }
         uint32_t eop[EPW][8];
-        // products of the last two steps: a step folds in the one before last, whose MFMA has long finished
-        v4f p_prev = v4f{0.f, 0.f, 0.f, 0.f}, p_prev2 = v4f{0.f, 0.f, 0.f, 0.f};
-        auto fold = [&](auto FP, auto JP, const v4f& p) {
-            constexpr int fp = decltype(FP)::value, jp = decltype(JP)::value;
-            const float sc = fabsf(cur.s[jp]);                   // the sign bit is the packer's mark, not part of the scale
-            acc[fp][jp][0] = fmaf(sc, p[0], acc[fp][jp][0]);
-            acc[fp][jp][1] = fmaf(sc, p[1], acc[fp][jp][1]);
-            acc[fp][jp][2] = fmaf(sc, p[2], acc[fp][jp][2]);
-            acc[fp][jp][3] = fmaf(sc, p[3], acc[fp][jp][3]);
-        };
         v8i xop = v8i{0, 0, 0, 0, 0, 0, 0, 0};
         static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto ST) {
             constexpr int st = decltype(ST)::value, f = st / WN, j = st % WN;
-            if (j == 0) {
-                xop = v8i{(int)xa.x, (int)xa.y, (int)xa.z, (int)xa.w, (int)xc.x, (int)xc.y, (int)xc.z, (int)xc.w};
-                if (f + 1 < WM) {
-                    xa = *reinterpret_cast<const uint4*>(xb + xa_off + (f + 1) * 2048);
-                    xc = *reinterpret_cast<const uint4*>(xb + xc_off + (f + 1) * 2048);
+            if constexpr (B_STAGES == 1 && st == WN) __syncthreads();   // one stage of weight operands: everybody has read this chunk's before anybody publishes the next one's
+            if constexpr (st == SPAN) {
+                __builtin_amdgcn_s_setprio(0);
+                // the last token block's operand has arrived, this wavefront's publishing writes are done, its copies and loads
+                // have landed ...
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : "+v"(xa.x), "+v"(xa.y), "+v"(xa.z), "+v"(xa.w), "+v"(xc.x), "+v"(xc.y), "+v"(xc.z), "+v"(xc.w) : : "memory");
+                __syncthreads();                                 // ... and so have everyone's; the stages just read are free
+                // what this chunk loaded is touched here, straight after the wait, and stays in the registers it was loaded into
+                if (!OUT_SCALED) {
+#pragma unroll
+                    for (int q = 0; q < WN; ++q) asm volatile("" : "+v"(nxt.s[q]));
                 }
+#pragma unroll
+                for (int t = 0; t < EPW; ++t) {
+                    asm volatile("" : "+v"(nxt.raw[t]));         // as one 128-bit value
+                    if (OUT_SCALED) asm volatile("" : "+v"(nxt.es[t]));
+                    if (ASYM) asm volatile("" : "+v"(nxt.ez[t]));
+                }
+                if (c + 2 < c_end) {
+#pragma unroll
+                    for (int q = 0; q < DMA_EARLY; ++q) stage_page(c + 2, buf, q);
+                }
+                if (c + 3 < c_end) load_raw(cur, c + 3);
+                __builtin_amdgcn_s_setprio(1);
             }
-            // the copies of the next chunk's activations, one every few steps of the first half of the chunk
-            if constexpr (st % DMA_EVERY == 0 && st / DMA_EVERY < DPW) stage_page(cn, buf ^ 1, st / DMA_EVERY);
+            if constexpr (st == (SUM_IN_MFMA ? 0 : 2))           // the folds of the chunk before are done with nxt.s
+                load_scales(nxt, cn);                            // (behind the last chunk: loaded again, not used)
+            if constexpr (j == 0) {
+                xop = v8i{(int)xa.x, (int)xa.y, (int)xa.z, (int)xa.w, (int)xc.x, (int)xc.y, (int)xc.z, (int)xc.w};
+                if constexpr (f + 1 < WM) read_tokens(buf, f + 1);
+                else read_tokens(buf ^ 1, 0);                    // behind the last chunk: read, never multiplied
+            }
+            // the copies of the next chunk's activations that did not go out behind the last barrier, one every few steps
+            constexpr int turn = (st + WN) / DMA_EVERY;
+            if constexpr (st < SPAN && (st + WN) % DMA_EVERY == 0 && turn >= DMA_EARLY && turn < DPW) stage_page(cn, buf ^ 1, turn);
             if (POW2) acc[f][j] = mfma_16x16x128_e4m3_scaled(xop, bop[j], acc[f][j], E8M0_ONE, e8m0_of(cur.s[j]));
             if (OUT_SCALED) acc[f][j] = mfma_16x16x128_e4m3(xop, bop[j], acc[f][j]);
             const v4f p = SUM_IN_MFMA ? v4f{0.f, 0.f, 0.f, 0.f} : mfma_16x16x128_e4m3(xop, bop[j], v4f{0.f, 0.f, 0.f, 0.f});
-            if constexpr (!SUM_IN_MFMA && st > 1) {
-                fold(std::integral_constant<int, (st - 2) / WN>{}, std::integral_constant<int, (st - 2) % WN>{}, p_prev2);
-                keep_here(acc[(st - 2) / WN][(st - 2) % WN]);
+            if constexpr (f == WM - 1) read_weights(buf ^ 1, j); // chunk c + 1's, in the registers that this MFMA was the last to read
+            // a step folds in the product of the one before last, whose MFMA has long finished
+            if constexpr (!SUM_IN_MFMA) {
+                constexpr int sp = (st + STEPS - 2) % STEPS;
+                fold(st < 2 ? nxt : cur, std::integral_constant<int, sp / WN>{}, std::integral_constant<int, sp % WN>{}, p_prev2);
+                keep_here(acc[sp / WN][sp % WN]);
             }
             p_prev2 = p_prev;
             p_prev = p;
             // this step's share of the next chunk's expansion: eighth E of the EPW bands is operand register E % 8 of
             // band E / 8 (half E % 2 of dword (E % 8) / 2); a finished half of an operand goes to LDS at once
             // (also in the last chunk, where nobody reads the result: a branch here would cut the step sequence up)
-            constexpr bool EXPAND = st % STEPS_PER_EIGHTH == STEPS_PER_EIGHTH - 1;
-            constexpr int E = st / STEPS_PER_EIGHTH, t = E / 8, e = E % 8, d = e >> 1;
-            if constexpr (EXPAND) {
+            constexpr int E0 = st < SPAN ? st * EIGHTHS / SPAN : EIGHTHS, E1 = st < SPAN ? (st + 1) * EIGHTHS / SPAN : EIGHTHS;
+            static_for(std::make_integer_sequence<int, E1 - E0>{}, [&](auto EI) {
+                constexpr int E = E0 + decltype(EI)::value, t = E / 8, e = E % 8, d = e >> 1;
                 const uint32_t src = cur.raw[t][d];
                 uint32_t o;
                 if (TWO) o = (e & 1) ? two_level_half_fast<4>(src, tab[t]) : two_level_half_fast<0>(src, tab[t]);
@@ -326,37 +334,29 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
                 eop[t][e] = o;
                 if (e == 3) publish(buf ^ 1, t, 0, eop[t][0], eop[t][1], eop[t][2], eop[t][3]);
                 if (e == 7) publish(buf ^ 1, t, 1, eop[t][4], eop[t][5], eop[t][6], eop[t][7]);
-            }
-            constexpr int ALU = ((SUM_IN_MFMA || st < 2) ? 0 : 4) + (EXPAND ? (ASYM ? 7 : 4) : 0);
-            if (j == 0 && f + 1 < WM) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads of the next block
+            });
+            constexpr int ALU = (SUM_IN_MFMA ? 0 : 4) + (E1 - E0) * (ASYM ? 7 : 4), WRITES = E1 / 4 - E0 / 4;
+            if constexpr (j == 0) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);      // LDS reads of the next block
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // this step's MFMA
+            if constexpr (f == WM - 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0); // the next chunk's weight operand
             __builtin_amdgcn_sched_group_barrier(0x002, ALU, 0);                          // ALU work independent of it
-            if (EXPAND && (e == 3 || e == 7)) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // the publishing LDS write
+            if constexpr (WRITES > 0) __builtin_amdgcn_sched_group_barrier(0x200, WRITES, 0);   // the publishing LDS writes
             __builtin_amdgcn_sched_barrier(0);
-        });
-        if (!SUM_IN_MFMA) {
-            fold(std::integral_constant<int, (STEPS - 2) / WN>{}, std::integral_constant<int, (STEPS - 2) % WN>{}, p_prev2);
-            fold(std::integral_constant<int, WM - 1>{}, std::integral_constant<int, WN - 1>{}, p_prev);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        if (TWO) {
-            // a band whose group holds a -8 (marked by the packer, rare): its operand again, this time with the pattern
-            // 1000 put right -- after the steps, so that their instruction sequence stays one block
-#pragma unroll
-            for (int t = 0; t < EPW; ++t) {
+            if constexpr (TWO && E1 > E0 && E1 % 8 == 0) {
+                // a band whose group holds a -8 (marked by the packer, rare): its operand again, this time with the pattern
+                // 1000 put right
+                constexpr int t = E1 / 8 - 1;
                 if (any_marked(cur.es[t])) {
                     const v8i o = slot_to_operand_two_level<true>(make_uint4(cur.raw[t][0], cur.raw[t][1], cur.raw[t][2], cur.raw[t][3]), tab[t]);
                     publish(buf ^ 1, t, 0, (uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]);
                     publish(buf ^ 1, t, 1, (uint32_t)o[4], (uint32_t)o[5], (uint32_t)o[6], (uint32_t)o[7]);
                 }
             }
-        }
-        lds_dma_wait_all();                                      // this wavefront's copies and loads have landed ...
-        __syncthreads();                                         // ... and so have everyone's; the stages just read are free
+        });
     };
 
     // A tile's start, first half: the copies of chunk 0's activations into stage 0, and the loads of chunk 0's nibbles
-    // and scales and of chunk 1's nibbles (the copies first: the loads are then the younger operations, and the waits
+    // and scales and of the nibbles of chunks 1 and 2 (the copies first: the loads are then the younger operations, and the waits
     // the compiler puts in front of their first uses leave the copies alone).
     Set sa, sb;
     u32x4 raw0[EPW];
@@ -382,8 +382,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
             sa.raw[t] = u32x4{0u, 0u, 0u, 0u};
             sa.es[t] = 0.0f;
             sa.ez[t] = 0u;
+            sb.raw[t] = u32x4{0u, 0u, 0u, 0u};
+            sb.es[t] = 0.0f;
+            sb.ez[t] = 0u;
         }
         if (c_begin + 1 < c_end) load_raw(sa, c_begin + 1);
+        if (c_begin + 2 < c_end) load_raw(sb, c_begin + 2);
     };
     // second half: chunk 0's weight operands, expanded from registers, into stage 0; then everything has landed
     auto start_finish = [&]() {
@@ -401,127 +405,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
     };
 
     const float sx = ksplit > 1 ? 1.0f : *s_x;                   // partial sums are stored unscaled
-    const float yq = (sizeof(OutT) == 1) ? *y_scale : 1.0f;      // FP8 output: the next layer's activation scale
+    const StaticQuantizer quantizer(sizeof(OutT) == 1 ? *y_scale : 1.0f);   // FP8 output: the next layer's activation scale
 
-    // Epilogue of the tile (em0, ebn), 16-token blocks f0 .. f1-1 of every wavefront row.
+    // Epilogue of the tile (em0, ebn), 16-token blocks f0 .. f1-1 of every wavefront row, through the wavefront's slab in stage 1
     auto epilogue = [&](int em0, int ebn, int esplit, auto F0, auto F1) {
-        constexpr int f0 = decltype(F0)::value, f1 = decltype(F1)::value;
-        const int n_block = ebn * BN;
-        OutT* const yo = y + (int64_t)esplit * split_stride;     // this unit's share of the workspace (esplit = 0 without a split)
-        if constexpr (DIRECT) {
-            // Result lane: channel i of band j, tokens 4 kq .. 4 kq + 3 of block f.  Every wavefront turns its 16 tokens x
-            // 16 WN channels of a block into row-major order in an LDS slab of its own (a wavefront's LDS accesses run in
-            // order: no barrier, no wait beyond the one for the data) and stores 16 bytes per lane, whole row segments.
-            constexpr int EB = (int)sizeof(OutT);
-            constexpr int ROW_B = 16 * WN * EB, RSB = ROW_B + 16;    // bytes of a slab row, and its stride
-            constexpr int SEGS = ROW_B / 16, ROWS_PER_STORE = 64 / SEGS, STORES = 16 / ROWS_PER_STORE;
-            static_assert(WAVES * 16 * RSB <= (B_STAGES == 2 ? STAGE : A_STAGE), "the wavefronts' slabs fit stage 1");
-            uint8_t* const slab = lds + STAGE + wave * (16 * RSB);
-            const int n_wave = n_block + wn * WN * 16;               // first channel of the wavefront's bands
-            const int seg = lane % SEGS, srow = lane / SEGS;
-            float so[WN];                                            // output scale of the lane's channel of band j
-#pragma unroll
-            for (int j = 0; j < WN; ++j)
-                so[j] = OUT_SCALED ? sx * w_out[per_channel ? min(n_wave + j * 16 + i, N - 1) : 0] : sx;
-#pragma unroll
-            for (int f = f0; f < f1; ++f) {
-#pragma unroll
-                for (int j = 0; j < WN; ++j) {
-                    if constexpr (EB == 2) {
-                        // even lanes keep tokens 0, 1 and take the odd neighbour's, odd lanes keep tokens 2, 3: a lane then
-                        // holds channels {i & ~1, i | 1} of two tokens, converted to bf16 by the hardware (round to nearest even)
-                        typedef float f2 __attribute__((ext_vector_type(2)));
-                        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-                        const bool odd = (i & 1) != 0;
-                        const uint32_t sel_lo = odd ? 0x05040100u : 0x01000504u, sel_hi = odd ? 0x07060302u : 0x03020706u;
-                        const f2 t01 = {so[j] * acc[f][j][0], so[j] * acc[f][j][1]}, t23 = {so[j] * acc[f][j][2], so[j] * acc[f][j][3]};
-                        const b2 c01 = __builtin_convertvector(t01, b2), c23 = __builtin_convertvector(t23, b2);
-                        const uint32_t a = *reinterpret_cast<const uint32_t*>(&c01), b = *reinterpret_cast<const uint32_t*>(&c23);
-                        const uint32_t own = odd ? b : a, nb = from_pair_lane(odd ? a : b);
-                        uint8_t* p = slab + (4 * kq + (odd ? 2 : 0)) * RSB + (j * 16 + (i & ~1)) * 2;
-                        *reinterpret_cast<uint32_t*>(p) = __builtin_amdgcn_perm(own, nb, sel_lo);
-                        *reinterpret_cast<uint32_t*>(p + RSB) = __builtin_amdgcn_perm(own, nb, sel_hi);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            *reinterpret_cast<float*>(slab + (4 * kq + r) * RSB + (j * 16 + i) * 4) = so[j] * acc[f][j][r];
-                    }
-                }
-#pragma unroll
-                for (int h = 0; h < STORES; ++h) {
-                    const int row = h * ROWS_PER_STORE + srow;
-                    const uint4 w = *reinterpret_cast<const uint4*>(slab + row * RSB + seg * 16);
-                    const int m = em0 + (wm * WM + f) * 16 + row, n = n_wave + seg * (16 / EB);
-                    if (m < M && n < N) {
-                        OutT* dst = yo + (int64_t)m * ldy + n;
-                        if (n + 16 / EB <= N) {
-                            store_16_unaligned(dst, w);
-                        } else {
-                            const uint32_t e4[4] = {w.x, w.y, w.z, w.w};
-                            for (int e = 0; e < 16 / EB && n + e < N; ++e) {
-                                if constexpr (EB == 2) dst[e] = (uint16_t)(e4[e / 2] >> (16 * (e % 2)));
-                                else dst[e] = __uint_as_float(e4[e]);
-                            }
-                        }
-                    }
-                }
-            }
-        } else {
-            static_assert(!TWO || DIRECT, "the two-level mode has float32 and bf16 outputs only");
-            // E4M3 outputs: per round the workgroup turns block f of every wavefront row into row-major order in LDS
-            // (stage 1, which nothing else uses between two tiles) and stores whole row segments
-            SlabT* slab = reinterpret_cast<SlabT*>(lds + STAGE);
-            constexpr int VEC = SILU ? 16 : 16 / sizeof(SlabT);  // outputs per 16-byte store
-            constexpr int UPR = (SILU ? BN / 2 : BN) / VEC;      // 16-byte units per row
-#pragma unroll
-            for (int f = f0; f < f1; ++f) {
-#pragma unroll
-                for (int j = 0; j < WN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        slab[(wm * 16 + 4 * kq + r) * RS + (wn * WN + j) * 16 + i] = OutCast<SlabT>::cast(sx * acc[f][j][r], yq);
-                __syncthreads();
-                for (int u = tid; u < SLAB_ROWS * UPR; u += THREADS) {
-                    const int row = u / UPR, col = (u % UPR) * VEC;
-                    const int m = em0 + ((row >> 4) * WM + f) * 16 + (row & 15);
-                    if constexpr (SILU) {
-                        // 16 outputs of one band pair: gate = slab columns 32p .. 32p+15, up = 32p+16 .. 32p+31 (p = col / 16)
-                        const int n_out = n_block / 2 + col;
-                        if (m < M && n_out < N / 2) {
-                            const SlabT* g = slab + row * RS + 2 * col;
-                            uint8_t* dst = reinterpret_cast<uint8_t*>(y) + (int64_t)m * ldy + n_out;
-                            uint32_t w[4];
-#pragma unroll
-                            for (int e = 0; e < 16; e += 4) {
-                                float h[4];
-#pragma unroll
-                                for (int t = 0; t < 4; ++t)
-                                    h[t] = bf16_bits_to_f32(f32_to_bf16_bits(
-                                        silu_mul_f32(bf16_bits_to_f32(g[e + t]), bf16_bits_to_f32(g[16 + e + t]))));
-                                w[e / 4] = cvt2(h[2] / yq, h[3] / yq, cvt2(h[0] / yq, h[1] / yq, 0u, false), true);
-                            }
-                            if (n_out + 16 <= N / 2) {
-                                store_16_unaligned(dst, make_uint4(w[0], w[1], w[2], w[3]));
-                            } else {
-                                for (int e = 0; e < 16 && n_out + e < N / 2; ++e) dst[e] = (uint8_t)(w[e / 4] >> (8 * (e % 4)));
-                            }
-                        }
-                    } else {
-                        const int n = n_block + col;
-                        if (m < M && n < N) {
-                            OutT* dst = y + (int64_t)m * ldy + n;
-                            const OutT* src = reinterpret_cast<const OutT*>(slab) + row * RS + col;
-                            if (n + VEC <= N) {
-                                store_16_unaligned(dst, *reinterpret_cast<const uint4*>(src));
-                            } else {
-                                for (int e = 0; e < VEC && n + e < N; ++e) dst[e] = src[e];
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-        }
+        store_tile<OutT, WM, WN, OUT_SCALED, decltype(F0)::value, decltype(F1)::value>(
+            acc, lds + STAGE + wave * Out::SLAB_BYTES, em0 + wm * WM * 16, ebn * BN + wn * WN * 16, M, N,
+            y + (int64_t)esplit * split_stride, ldy, sx, w_out, per_channel, quantizer, lane);   // this unit's share of the workspace (esplit = 0 without a split)
     };
 
     set_tile(v);
@@ -533,11 +423,43 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_mfma2d_kernel(
         for (int f = 0; f < WM; ++f)
 #pragma unroll
             for (int j = 0; j < WN; ++j) acc[f][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        // nothing to fold in yet: zeros, under scales of zero
+        p_prev = p_prev2 = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < WN; ++j) sb.s[j] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < EPW; ++t) {                          // landed at the start's wait: touched here
+            asm volatile("" : "+v"(sa.raw[t]), "+v"(sb.raw[t]));
+            if (OUT_SCALED) asm volatile("" : "+v"(sa.es[t]), "+v"(sb.es[t]));
+            if (ASYM) asm volatile("" : "+v"(sa.ez[t]), "+v"(sb.ez[t]));
+        }
+        if (!OUT_SCALED) {
+#pragma unroll
+            for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(sa.s[j]));
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), known to the compiler: it would wait inside the loop otherwise
+        read_tokens(0, 0);
+#pragma unroll
+        for (int j = 0; j < WN; ++j) read_weights(0, j);
+        if (c_begin + 1 < c_end) {
+#pragma unroll
+            for (int q = 0; q < DMA_EARLY; ++q) stage_page(c_begin + 1, 1, q);
+        }
+        __builtin_amdgcn_s_setprio(1);
         for (int c = c_begin; c < c_end; c += 2) {
             chunk(c, sa, sb);
             if (c + 1 < c_end) chunk(c + 1, sb, sa);
         }
-        // The loop's last barrier has passed: both stages are free.  The next tile's first copies and loads go out
+        __builtin_amdgcn_s_setprio(0);
+        if (!SUM_IN_MFMA) {                                      // the last two steps' products, under the last chunk's scales
+            const bool odd = ((c_end - c_begin) & 1) != 0;
+            Set last;
+#pragma unroll
+            for (int j = 0; j < WN; ++j) last.s[j] = odd ? sa.s[j] : sb.s[j];
+            fold(last, std::integral_constant<int, (STEPS - 2) / WN>{}, std::integral_constant<int, (STEPS - 2) % WN>{}, p_prev2);
+            fold(last, std::integral_constant<int, WM - 1>{}, std::integral_constant<int, WN - 1>{}, p_prev);
+        }
+        // The loop's last barrier has passed and nobody reads from LDS any more what counts: both stages are free.  The next tile's first copies and loads go out
         // before this tile's epilogue and are waited for in its middle; they touch stage 0 only (the slab epilogue
         // works in stage 1).
         const int em0 = m0, ebn = bn;
@@ -669,13 +591,12 @@ int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, 
         a.ldy = mfma2d_splitk_ldw(N);
         kernel_ydt = W4A8_F32;
     }
-    switch (cfg) {
+    if (cfg == 2 || cfg == 5) launch_linear_pipe(a, cfg, kernel_ydt, grid, grid_m, grid_n, group_m, sp.ksplit, sp.cps > 0 ? sp.cps : C, sp.split_stride, st);
+    else switch (cfg) {
         case 0: launch_out<4, 2, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
         case 1: launch_out<2, 4, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
-        case 2: launch_out<4, 2, 4, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
         case 3: launch_out<2, 4, 4, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
-        case 4: launch_out<2, 2, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
-        default: launch_out<2, 4, 4, 2>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
+        default: launch_out<2, 2, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
     }
     if (int e = launch_status()) return e;
     if (ksplit > 1) {

@@ -380,8 +380,57 @@ template <> struct Load16<uint16_t> {
     static __device__ __forceinline__ float one(const uint16_t* p) { return bf16_bits_to_f32(*p); }
 };
 
+// Eq. 13 under one static scale: h / s correctly rounded, then rounded onto the E4M3 grid.  The reciprocal is formed once; a
+// quotient is then its estimate and two corrections, the second of which rounds it correctly (Markstein), for scales
+// between 2^-30 and 2^30 and quotients the grid can tell from zero and from 448.  Below those the estimate rounds to the same
+// zero, above to the same 448, infinities and NaN included.  Six operations where the general division takes ten and two mode switches.
+struct StaticQuantizer {
+    float s, y;
+    bool plain;                                                  // wave-uniform
+    __device__ __forceinline__ explicit StaticQuantizer(float scale) : s(scale), y(1.0f / scale), plain(fabsf(scale) >= 0x1p-30f && fabsf(scale) <= 0x1p30f) {}
+    __device__ __forceinline__ float quotient(float h) const {
+        const float q0 = h * y;
+        float q = fmaf(fmaf(-s, q0, h), y, q0);
+        q = fmaf(fmaf(-s, q, h), y, q);
+        return fabsf(q0) < 512.0f ? __builtin_copysignf(q, q0) : q0;
+    }
+    // four values -> four E4M3 bytes
+    __device__ __forceinline__ uint32_t four(float a, float b, float c, float d) const {
+        if (plain) {
+            a = quotient(a);
+            b = quotient(b);
+            c = quotient(c);
+            d = quotient(d);
+        } else {
+            a /= s;
+            b /= s;
+            c /= s;
+            d /= s;
+        }
+        return cvt2(c, d, cvt2(a, b, 0u, false), true);
+    }
+};
+
 // silu(gate) * up in float32 (the decoder block's elementwise step): silu(g) = g / (1 + exp(-g)).
 __device__ __forceinline__ float silu_mul_f32(float g, float u) { return g / (1.0f + expf(-g)) * u; }
+
+// The same for gates that are bf16 values, where a lane forms many of them: the quotient from the hardware's reciprocal, one Newton
+// step and one correction -- measured equal, bit for bit, to the general division for every one of the 65536 gates.  Gates
+// below -41 or beyond 2^60, where the corrections would leave the normal range, take the general division.  (A lane of the
+// smaller kernels forms one to eight; there the longer code costs more than it saves, 0.6 ... 1.2 us a launch.)
+__device__ __forceinline__ float silu_mul_bf16_gate(float g, float u) {
+    const float d = 1.0f + expf(-g);
+    float q;
+    const bool plain = d < 0x1p60f && fabsf(g) < 0x1p60f;
+    {
+        const float y0 = __builtin_amdgcn_rcpf(d);
+        const float y = fmaf(fmaf(-d, y0, 1.0f), y0, y0);
+        const float q0 = g * y;
+        q = __builtin_copysignf(fmaf(fmaf(-d, q0, g), y, q0), g);
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!plain) != 0, 0)) q = plain ? q : g / d;
+    return q * u;
+}
 
 // Output kinds of the linear kernels.  float, uint16_t (bf16) and uint8_t (E4M3 of the bf16 value, Eq. 13 with the next
 // layer's scale) are what they say.  SiluFp8 is the gate|up layer of a decoder block with SiLU*mul and the down
