@@ -32,11 +32,6 @@ constexpr int XCDS = 8;
 constexpr int GROUP_M = 8;          // token blocks per super-column of the block order
 constexpr int WAVES = 8;
 
-// Built workgroup shapes {token blocks, K-split groups, bands per wavefront}, in the launcher's order of preference
-// (the last one is considered first, under its own condition).
-#define W4A8_MFMA_SHAPES 7
-#define W4A8_MFMA_SHAPE_LIST {{16, 1, 1}, {8, 1, 1}, {8, 2, 1}, {4, 1, 1}, {4, 2, 1}, {4, 4, 1}, {16, 1, 2}}
-
 template <int A, int B> struct MaxOf { static constexpr int value = A > B ? A : B; };
 
 // MODE_CODE_EXACT: signed codes, group scales applied to the partial sums in fp32.  MODE_TWO_LEVEL: the weight operand
@@ -455,117 +450,9 @@ void launch_one(const LinearArgs& a, dim3 grid, int grid_m, int grid_n, hipStrea
 
 }  // namespace
 
-namespace {
-
-// Microseconds, constant + per 128-deep chunk of K: what a workgroup of the second tiling takes for a tile of 512 x 128 (0: not
-// used), 256 x 256, 256 x 128, and of 256 x 128 with four wavefronts, alone on a compute unit and two at a time; `tail` is the
-// share of a round that a last round of at most 256 of those costs after full ones.  The first tiling is priced at constant +
-// per chunk + flops / rate (PFLOP/s), its 256 x 128 tiles, two of which share a compute unit as well, like the four-wavefront
-// ones where `big` gives their times; the flops are then those of whole token blocks.
-struct TileTimes {
-    double tall, tall_c, square, square_c, half, half_c, alone, alone_c, shared, shared_c, tail;
-    double first, first_c, first_rate;
-    double big_alone, big_alone_c, big_shared, big_shared_c, big_tail;
-};
-constexpr TileTimes PLAIN_TIMES = {0.0, 0.0, 6.0, 1.66, 5.0, 1.08, 5.0, 1.28, 5.0, 1.875, 0.5, 0.0, 0.265, 1.35};   // code-exact, powers of two
-constexpr TileTimes TWO_LEVEL_TIMES = {8.0, 1.48, 10.0, 1.48, 2.0, 1.11, 8.0, 1.20, 8.0, 1.82, 0.5, 0.0, 0.265, 1.35};
-// Fitted to 16 layers (1024 ... 28672 features, 1024 ... 28672 channels) x 20 token counts (65 ... 8192) on every tile and on
-// the first tiling's own choice: the choice is 0.1 % slower than the best of them in the mean, 11 % at most; fitted to half of the
-// layers, 0.25 and 0.02 % on the other half.  One rate for all of the first tiling (1.4) and 3 + 1.37 C for the 256 x 128
-// tiles chose 512 x 128 tiles where those are slower than the others: 4096 tokens on 4096 -> 6144 125 us (256 x 128 tiles 117),
-// 3072 on 28672 -> 8192 812 (749), 5120 on 14336 -> 4096 409 (375); 1.2 % in the mean, 15 % at most.
-constexpr TileTimes ASYM_TIMES = {5.8, 1.76, 7.93, 1.79, 4.75, 1.06, 5.67, 1.56, 7.48, 2.03, 0.69, 6.38, 0.11, 1.45, 5.75, 1.24, 8.36, 2.09, 0.59};
-// These and the two-level ones were chosen on sweeps of five layers; over the sizes above the choice is 1.1 and 1.3 % slower than
-// the best in the mean, a quarter at most (small grids, where the first tiling is taken and 256 x 128 tiles are faster).
-constexpr TileTimes ASYM_TWO_TIMES = {7.0, 1.62, 8.0, 1.65, 3.0, 1.23, 6.0, 1.36, 6.0, 1.94, 0.5, 0.0, 0.265, 1.35};
-
-// `tiles` tiles, two to a compute unit
-double two_per_unit(int64_t tiles, double alone, double shared, double tail) {
-    const int64_t full = tiles / 512, rem = tiles % 512;
-    // the last, partly filled round: alone on their units the workgroups run faster, and after full rounds they start it while
-    // others still finish theirs (measured: about half a shared round then, 0.6 ... 0.7 where the FMAs and the longer
-    // expansion come together)
-    return (double)full * shared + (rem == 0 ? 0.0 : rem > 256 ? shared : full > 0 ? tail * shared : alone);
-}
-
-// The first tiling's shape for a layer; requested values other than 0 are kept.  False: a combination that is not built.
-bool first_tiling_shape(int64_t M, int64_t K, int64_t N, int& mf, int& ks, int& tpw) {
-    static const int cand[W4A8_MFMA_SHAPES][3] = W4A8_MFMA_SHAPE_LIST;
-    if (mf != 0 && ks != 0 && tpw != 0) return true;
-    const int C = (int)(K / 128);
-    const int n_tiles = (int)((N + 15) / 16);
-    int pick = -1, fallback = -1;
-    // 256 tokens x 256 channels (two bands per wavefront, half the LDS reads per MFMA, one workgroup per compute unit)
-    // measured no faster than 256 x 128 at twice the occupancy on any swept shape: on request only.
-    if (tpw == 2 && (mf == 0 || mf == 16) && (ks == 0 || ks == 1)) pick = W4A8_MFMA_SHAPES - 1;
-    for (int q = 0; q < W4A8_MFMA_SHAPES - 1 && pick < 0; ++q) {
-        const int mfv = cand[q][0], ksv = cand[q][1], tpv = cand[q][2];
-        if ((mf && mf != mfv) || (ks && ks != ksv) || (tpw && tpw != tpv)) continue;
-        fallback = q;                                            // the finest shape that matches the request
-        if (mfv > 4 && 16 * mfv >= 2 * M + 64) continue;         // mostly padding
-        if (ksv > 1 && C < 4 * ksv) continue;                    // too few chunks to split
-        const int per_wg = (8 / ksv) * tpv;
-        const int64_t groups = ((M + 16 * mfv - 1) / (16 * mfv)) * (int64_t)((n_tiles + per_wg - 1) / per_wg);
-        if (groups >= 384) { pick = q; break; }
-    }
-    if (pick < 0) pick = fallback;
-    if (pick < 0) return false;
-    mf = cand[pick][0];
-    ks = cand[pick][1];
-    tpw = cand[pick][2];
-    return true;
-}
-
-}  // namespace
-
-// Launch shape of the many-token kernels for a layer; requested values of mf / ks / tpw other than 0 are kept.
-// cfg2d >= 0 on return: the layer goes to the second tiling (linear_mfma2d.hip) with that workgroup tile.
-//  - The second tiling (a 2-D grid of wavefronts over tiles of 256 or 512 tokens, expansion shared through LDS, persistent
-//    workgroups) competes with the first on estimated time.  A persistent workgroup needs a fixed time per tile, so what a
-//    grid costs is rounds x time per tile, and the last, partly filled round costs as much as a full one: 256 x 256 tiles (one workgroup per compute unit, 256 at a time), 256 x 128 tiles
-//    with eight wavefronts (256 at a time) or with four (two workgroups per compute unit, 512 at a time; a tile takes
-//    longer while two share the unit).  Times per tile in microseconds, C = K / 128 chunks, from medians on the
-//    Llama-3 layer shapes with the weights coming from HBM: 6 + 1.66 C, 5 + 1.08 C, 5 + 1.28 C alone and 5 + 1.875 C
-//    shared (half of that for a last round of at most 256 tiles that follows full ones).  The first tiling is priced
-//    at 0.265 C + flops / 1.35 PFLOP/s (the asymmetric format: by rounds as well, see its times).  Against the rule this replaces (256 x 256 or
-//    four-wavefront 256 x 128 tiles once they number 200): 640 tokens on gate|up 125 -> 104 us, 3072 / 4096 tokens on
-//    QKV 113 / 120 -> 101 / 108, 2048 tokens on the O projection 47 -> 42, 192...256 tokens on gate|up 48 -> 42.
-//  - The two-level and the asymmetric formats spend more on a band's expansion (7 operations per four weights instead of 4,
-//    and a table per group), so their tiles take other times, and 512 x 128 tiles, which expand half as many bands per
-//    MFMA, are among the fastest where they fill the chip: gate|up at 2048 tokens on 512 x 128 / 256 x 256 / 256 x 128 /
-//    four-wavefront 256 x 128 tiles / first tiling: asymmetric 254 / 262 / 271 / 257 / 267 us, asymmetric two-level 227 / 238 /
-//    247 / 226 / 237, two-level 229 / 259 / 254 / 251.  The plain formats gain nothing from them (512 x 128 / 256 x 256 /
-//    four-wavefront tiles, quantization included: 239 / 242 / 239, at 8192 tokens 924 / 894 / 944): their expansion hides
-//    behind the FMAs, and their list is without.
-//  - First tiling: tall token blocks amortize the nibble expansion over more MFMAs; two bands per wavefront halve the
-//    LDS reads per MFMA (the activation operand is reused); K-splits shorten the dependent chain of passes (each waits
-//    for the copies of the next) when the grid is too small to fill the chip, at the price of a wider activation block
-//    to copy per pass.  Sweeps over the Llama-3 layer shapes are matched by: the first shape, in the list's order of
-//    preference, that yields about 1.5 workgroups per compute unit.
 bool mfma_launch_shape(int64_t M, int64_t K, int64_t N, int mode, int& mf, int& ks, int& tpw, int& cfg2d) {
-    cfg2d = -1;
-    const bool chosen = mf == 0 && ks == 0 && tpw == 0;
-    if (!first_tiling_shape(M, K, N, mf, ks, tpw)) return false;
-    if (!chosen) return true;
-    const TileTimes& t = mode == MODE_ASYM        ? ASYM_TIMES
-                         : mode == MODE_ASYM_TWO  ? ASYM_TWO_TIMES
-                         : mode == MODE_TWO_LEVEL ? TWO_LEVEL_TIMES
-                                                  : PLAIN_TIMES;
-    const int64_t tm = (M + 255) / 256, t0 = (M + 511) / 512 * ((N + 127) / 128), t1 = tm * ((N + 255) / 256), t2 = tm * ((N + 127) / 128);
-    const double c = (double)(K / 128);
-    const double e0 = (double)((t0 + 255) / 256) * (t.tall + t.tall_c * c);
-    const double e1 = (double)((t1 + 255) / 256) * (t.square + t.square_c * c);
-    const double e2 = (double)((t2 + 255) / 256) * (t.half + t.half_c * c);
-    const double e4 = two_per_unit(t2, t.alone + t.alone_c * c, t.shared + t.shared_c * c, t.tail);
-    const int64_t tokens = t.big_shared_c > 0.0 ? (M + 16 * mf - 1) / (16 * mf) * (16 * mf) : M;
-    const double first = mf == 16 && t.big_shared_c > 0.0
-                             ? two_per_unit(t2, t.big_alone + t.big_alone_c * c, t.big_shared + t.big_shared_c * c, t.big_tail)
-                             : t.first + t.first_c * c + 2.0 * (double)tokens * (double)K * (double)N / (t.first_rate * 1e9);
-    double best = e1 < e2 ? (e1 < e4 ? e1 : e4) : (e2 < e4 ? e2 : e4);
-    const bool tall = t.tall_c > 0.0 && e0 < best;
-    if (tall) best = e0;
-    if (best < first) cfg2d = tall ? 0 : best == e1 ? 1 : best == e2 ? 2 : 4;
-    return true;
+    double microseconds;
+    return choose_many_token_launch(M, K, N, mode, mf, ks, tpw, cfg2d, microseconds);
 }
 
 // mf = 16-token blocks per workgroup (4, 8 or 16), ks = K-split groups (1, 2 or 4), tpw = weight bands per wavefront

@@ -6,21 +6,12 @@
 
 #include "../../include/w4a8.h"
 #include "../../include/w4a8_tuning.h"
+#include "launch_choice.hpp"
 
 namespace w4a8 {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? W4A8_OK : W4A8_ERR_HIP; }
 inline int launch_status() { return hip_status(hipGetLastError()); }
-
-// How the tiled-layout linear kernels read the weights.
-//   MODE_CODE_EXACT  signed codes, fp32 group scales applied to the partial sums
-//   MODE_TWO_LEVEL   signed codes, `scales` = FP8-domain group scales, output scaled by s_x * w_out[n] (w_out[0] when
-//                    per_channel is 0)
-//   MODE_ASYM        unsigned codes, `scales` = the 80-byte records of group scales and zero-points
-//   MODE_POW2        signed codes, power-of-two group scales applied by the matrix unit (block-scaled MFMA)
-//   MODE_ASYM_TWO    unsigned codes and zero-points with FP8-domain group scales in the 80-byte records: the two-level
-//                    reading of the asymmetric format; output scaled like MODE_TWO_LEVEL
-enum WeightMode { MODE_CODE_EXACT = 0, MODE_TWO_LEVEL = 1, MODE_ASYM = 2, MODE_POW2 = 3, MODE_ASYM_TWO = 4 };
 
 // What the launchers of the tiled-layout linear kernels pass down to a launch: the operands of w4a8_linear after
 // validation.
@@ -87,41 +78,12 @@ int launch_linear_mfma_tiled(const uint8_t* x8, int64_t M, int64_t K, int64_t ld
 // many ranges by different workgroups, their float32 partial sums go through `workspace` (mfma2d_splitk_bytes).
 bool mfma2d_tile(int cfg, int& bm, int& bn);
 
-// Row stride (floats) of a K range's partial sums in the workspace, and the bytes `ksplit` ranges take.
-inline int64_t mfma2d_splitk_ldw(int64_t N) { return (N + 63) / 64 * 64; }
-inline size_t mfma2d_splitk_bytes(int64_t M, int64_t N, int ksplit) {
-    return ksplit > 1 ? (size_t)ksplit * (size_t)M * (size_t)mfma2d_splitk_ldw(N) * sizeof(float) : 0;
-}
-
-// The split of K this library uses for a layer of many-token shape when the caller provides a workspace: ksplit = 0 means
-// none.  Few output tiles and a deep K (the down projection of a decoder block at 64...512 tokens): the tiles are multiplied
-// in `ksplit` K ranges by different workgroups, about as many as it takes to give every compute unit one.  Measured on the
-// Llama-3 shapes: 29 -> 22 us at 128 tokens on the 8B down projection (K = 14336), 84 -> 57 us on the 70B one (K = 28672);
-// at K = 8192 four or more ranges still win (70B O projection at 192 / 256 tokens: 36 / 38 -> 32 / 35 us) and two lose;
-// no gain for K = 4096, where the partial sums (written and read once) weigh as much as the weights.
-inline void mfma2d_choose_ksplit(int64_t M, int64_t K, int64_t N, int& cfg, int& ksplit) {
-    cfg = 3;
-    ksplit = 0;
-    const int64_t C = K / 128;
-    if (M > 512 || K < 8192) return;
-    int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);      // 128 x 256 tiles ...
-    if (tiles <= 16) {                                          // ... or 128 x 128 where those are very few
-        cfg = 5;
-        tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    }
-    if (tiles > 128) return;
-    int64_t s = 256 / tiles;
-    if (s > C / 8) s = C / 8;
-    if (s < 2 || (K < 12288 && s < 4)) return;                  // K = 8192: two ranges lose, four or more win (measured)
-    const int64_t cps = (C + s - 1) / s;
-    s = (C + cps - 1) / cps;                                    // no empty range
-    ksplit = s < 2 ? 0 : (int)s;
-}
-
 int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, const float* s_x, const uint8_t* packed,
                          const float* scales, int64_t N, int32_t G, void* y, w4a8_dtype ydt, int64_t ldy, int cfg,
                          int group_m, int workgroups, int mode, const float* y_scale, hipStream_t st, int ksplit = 1,
                          void* workspace = nullptr, const float* w_out = nullptr, int per_channel = 0);
+void launch_linear_pipe(const LinearArgs& a, int cfg, int ydt, dim3 grid, int grid_m, int grid_n, int group_m, int ksplit, int cps,
+                        int64_t split_stride, hipStream_t st);
 void launch_linear_pipe(const LinearArgs& a, int cfg, int ydt, dim3 grid, int grid_m, int grid_n, int group_m, int ksplit, int cps,
                         int64_t split_stride, hipStream_t st);
 int launch_hessian_accumulate(const void* x, w4a8_dtype dt, int64_t T, int64_t K, int64_t ldx, float* h, hipStream_t st);
