@@ -144,28 +144,37 @@ __device__ __forceinline__ float quad_broadcast(float v) {       // lane P of th
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), P * 0x55, 0xF, 0xF, true));
 }
 
-constexpr int ROWS = 64;             // rows of a workgroup's tile; four lanes each inside a block
-constexpr int SEG = 32;              // columns of a block whose rows of U are staged at a time
+typedef float v32f __attribute__((ext_vector_type(32)));
+constexpr int THREADS = 512;
+constexpr int ROWS = 64;             // rows of a workgroup that quantizes a block; four lanes each in its chain
+constexpr int UP_ROWS = 128;         // rows of a workgroup that only updates
+constexpr int SEG = 32;              // columns of a block that are quantized at a stretch, and errors staged at a time
 constexpr int TILE_STRIDE = DPQ_BLOCK + 4;
-constexpr int PART = 36;             // staged U: [column q][lane p of the row][slot]: U[q, 4 * (q / 4 + slot) + p]
-constexpr int SEG_FLOATS = SEG * 4 * PART;
-constexpr int SLICE_FLOATS = SEG * (ROWS + DPQ_BLOCK);           // one slice of the update: errors and U
-constexpr int DPQ_LDS = 2 * SEG_FLOATS > ROWS * TILE_STRIDE ? 2 * SEG_FLOATS : ROWS * TILE_STRIDE;
-static_assert(SLICE_FLOATS <= DPQ_LDS, "the update's slice fits");
+constexpr int PART = 12;             // staged U of a segment: [column q][lane p of the row][slot]: U[q, 4 * (q / 4 + slot) + p], 8 slots
+constexpr int TILE_FLOATS = ROWS * TILE_STRIDE;
+constexpr int SEG_U = SEG * 4 * PART, SEG_E = SEG * ROWS;        // U of a segment, its errors
+constexpr int STAGE_FLOATS = SEG * (UP_ROWS + DPQ_BLOCK);        // one slice of an update: errors and U
+static_assert(2 * SEG_U + 2 * SEG_E <= STAGE_FLOATS && SEG * (ROWS + DPQ_BLOCK) <= STAGE_FLOATS, "the chain's buffers fit");
+
+// Products of one error column with one row of U: a 32 x 32 outer product per half of the wavefront, each product rounded by itself (an FMA
+// with zero), which is what Eq. 12 asks for -- only the sign of a zero product may differ, which changes nothing but the sign of a
+// weight that is zero.  a: lane l has the error of row l % 32 of block l / 32; b: U of column l % 32 of block l / 32.  Result register v:
+// block v / 16, row 8 (v % 16 / 4) + 4 (l / 32) + v % 4, column l % 32.
+__device__ __forceinline__ v32f outer_products(float a, float b) { return __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, v32f{}, 0, 0, 0); }
+__device__ __forceinline__ int product_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
 struct RowState {
-    float w[32];                  // the lane's columns of the block that are left: slot j = column 4 (done + j) + p
+    float w[8];                   // the lane's columns of the segment that are left: slot j = column 4 (done + j) + p
     float sw, y_sw, s, y_s, z;
     uint32_t span;                // NUM_SPAN, or 0 when a divisor of this row asks for the general division
 };
 
-// One weight: column q of the block, U[q, v] for the lane's columns v from q's slot on at `u`, U[q, q] and its reciprocal
-// in `d`.  Q = q % 4 is the lane of the row that owns it, in slot 0 of R.w; LEFT the slots in R.w.
-template <int Q, int LEFT>
+// One weight: column q of the segment, U[q, v] for the lane's columns v from q's slot on at `u`, U[q, q] and its reciprocal
+// in `d`.  Q = q % 4 is the lane of the row that owns it, in slot 0 of R.w.
+template <int Q>
 __device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d, bool diag_plain, int p, float& code) {
-    float4 v[LEFT / 4];
-#pragma unroll
-    for (int j = 0; j < LEFT / 4; ++j) v[j] = *reinterpret_cast<const float4*>(u + 4 * j);   // back by the time e is there
+    const float4 v0 = *reinterpret_cast<const float4*>(u), v1 = *reinterpret_cast<const float4*>(u + 4);   // back by the time e is there
+    const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
     const float w = quad_broadcast<Q>(R.w[0]);
     const bool plain = (__float_as_uint(w) & 0x7FFFFFFFu) - NUM_LO < R.span && diag_plain;
     const float w8 = fp8_value_finite(div_by(w, R.sw, R.y_sw));                           // Eq. 7
@@ -180,8 +189,8 @@ __device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d
         e = __fdiv_rn(__fsub_rn(w, __fmul_rn(g8_hat, R.sw)), d.x);
     }
 #pragma unroll
-    for (int j = 0; j < LEFT; ++j) {                                                      // Eq. 12 inside the block
-        const float next = __fsub_rn(R.w[j], __fmul_rn(e, j % 4 == 0 ? v[j / 4].x : j % 4 == 1 ? v[j / 4].y : j % 4 == 2 ? v[j / 4].z : v[j / 4].w));
+    for (int j = 0; j < 8; ++j) {                                                         // Eq. 12 inside the segment
+        const float next = __fsub_rn(R.w[j], __fmul_rn(e, v[j]));
         // in the weight's own slot: lanes behind it are updated, its own lane keeps the error, those before it theirs
         R.w[j] = j > 0 ? next : p > Q ? next : p == Q ? e : R.w[j];
         asm volatile("" : "+v"(R.w[j]));                         // here, not where the column is next read: the products would pile up
@@ -189,238 +198,288 @@ __device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d
     if (p == Q) code = uq;
 }
 
-// The 32 columns of a segment, LEFT slots in R.w at its start: slot by slot, the codes and errors going out and R.w moving on.
-// A loop of four weights (the whole block unrolled is 70 KB of instructions that every launch fetches anew, 80 us a block).
-template <int LEFT>
-__device__ __forceinline__ void dpq_segment(RowState& R, const DpqArgs& a, const float* u, const float2* diag, const int* cols, bool diag_plain,
-                                            int64_t n, bool row_ok, int c, int p) {
-    u += p * PART;
-#pragma unroll 1
-    for (int t = 0; t < SEG / 4; ++t, u += 16 * PART, diag += 4) {
-        float code = 0.0f;
-        const int col = cols[4 * t + p];
-        dpq_weight<0, LEFT>(R, u, diag[0], diag_plain, p, code);
-        dpq_weight<1, LEFT>(R, u + 4 * PART, diag[1], diag_plain, p, code);
-        dpq_weight<2, LEFT>(R, u + 8 * PART, diag[2], diag_plain, p, code);
-        dpq_weight<3, LEFT>(R, u + 12 * PART, diag[3], diag_plain, p, code);
-        if (row_ok) {
-            a.work[n * a.K + c + 4 * t + p] = R.w[0];
-            a.codes[n * a.K + col] = (uint8_t)code;
-        }
-#pragma unroll
-        for (int j = 0; j + 1 < LEFT; ++j) R.w[j] = R.w[j + 1];
-    }
-}
-
 // What becomes of the first column block's tiles: written to `work` like the others, or quantized with the group's parameters,
 // formed from the tile (groups of one block) or found in the outputs (where dpq_group_kernel put them).
 enum BlockStep { NO_BLOCK = 0, PARAMS_HERE = 1, PARAMS_GIVEN = 2 };
 
-// One launch of the walk.  Workgroups own tiles of 64 rows x 128 columns of the columns from c_first on, the tiles of the
-// first column block coming first:
+// The slices of an update: 32 errors of `Rows` rows from r0 on and the 32 rows of U that go with them, the tile's 128 columns, on their
+// way to LDS.  el[q * Rows + r]: error q of row r; ul[q * 128 + c]: U[c_err + q, v0 + c].
+template <int Rows> struct Slice {
+    static constexpr int EPT = SEG * Rows / THREADS, TPR = SEG / EPT;   // errors per thread, threads per row
+    float e[EPT], u[8];
+    __device__ __forceinline__ void load(const DpqArgs& a, int r0, int c_err, int v0, int q0, int tid) {
+        const float* er = a.work + (int64_t)min(r0 + tid % Rows, a.N - 1) * a.K + c_err + q0 + tid / Rows * EPT;
+        const float* ur = a.u + (int64_t)(c_err + q0 + (tid >> 4)) * a.K + v0 + (tid & 15) * 8;
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) e[j] = er[j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) u[j] = ur[j];
+    }
+    __device__ __forceinline__ void store(float* el, float* ul, int tid) const {
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) el[(tid / Rows * EPT + j) * Rows + tid % Rows] = e[j];
+        float* d = ul + (tid >> 4) * DPQ_BLOCK + (tid & 15) * 8;
+        *reinterpret_cast<float4*>(d) = make_float4(u[0], u[1], u[2], u[3]);
+        *reinterpret_cast<float4*>(d + 4) = make_float4(u[4], u[5], u[6], u[7]);
+    }
+};
+
+// One launch of the walk.  The first block_wgs workgroups own 64 rows of the first column block, from c_first on, the others 128 rows x 128
+// columns of the column blocks:
 //   gather:  the tile comes from the original weights, reordered; otherwise from `work`;
 //   update:  it receives the errors of the block at c_err (Eq. 12 for the columns right of a block: for every column q of
 //            that block, ascending, w <- w - err[n, q] * U[c_err + q, v]);
 //   block:   the tiles of the first column block are then quantized, column by column, the others written to `work`;
 //   ready:   a launch before has brought that many column blocks up to date: the first is only quantized, the other ones skipped.
 // With groups of 128 one launch does the first three: the next block is quantized by the workgroups that bring it up to date
-// while the others update the rest, so the serial part (60 us a block, the update of its own columns included) hides behind
-// the updates for as long as there are many.  With a scale search in a launch of its own the block's columns are brought up
-// to date in a launch before that.  Wider groups need all of their columns up to date before the first is quantized: an
-// update and a block launch each.
-// Update: a thread owns 8 x 4 outputs; per error column three 16-byte LDS reads feed 64 vector operations, which bound it
-// (4096 rows x 3968 columns: 112 us, with 4 x 4 outputs and a pass of its own 219; the vector unit needs 107).
-// Block: lane p of a row's four holds the columns v with v % 4 == p in registers; every lane takes the (identical)
-// quantization step and applies the error to its own columns.  The row of U comes from LDS, 32 columns staged at a time.  32
-// lanes per row, with the weights in LDS, spent most instructions on repeating the quantization step (89 us a block).
-// Measured at 4096 x 4096: 6.7 -> 2.3 ms; at 256 x 4096, where the serial part is all, 3.9 -> 1.9.
-// Three workgroups to a compute unit leave 168 registers, which spills 47 of them, all outside the loops over columns: once
-// per launch and 32 columns.  With two and no spills 256 x 4096 takes 1.79 ms instead of 1.90 and 4096 x 4096 2.32 instead of
-// 2.26, 16384 x 4096 7.13 instead of 6.38.
-__global__ void __launch_bounds__(256, 3) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int row_blocks, int gather, int update, int block,
-                                                          int ready) {
-    __shared__ __attribute__((aligned(16))) float lds[DPQ_LDS];
+// while the others update the rest, so the serial part hides behind the updates for as long as there are many.  With a scale search in a
+// launch of its own the block's columns are brought up to date in a launch before that.  Wider groups need all of their columns up to
+// date before the first is quantized: an update and a block launch each.
+// Update: the products come from the matrix unit, one outer product per error column, so that the vector unit is left with the
+// subtractions: 4096 rows x 3968 columns 112 us with both on the vector unit, TIME_UPDATE now.
+// Block: 32 columns at a time.  Lane p of a row's four holds the columns v with v % 4 == p of a segment in registers; every lane takes the
+// (identical) quantization step and applies the error to its own columns.  The columns of the later segments take the segment's 32
+// errors afterwards, on the matrix unit: those of the next one before it begins, the others by the four wavefronts that have no rows, beside the
+// chain.  A wavefront alone on its SIMD issues one vector operation every five cycles, so what a column costs is their number: 60,
+// with all later columns of the block in registers 100 on average.  32 lanes per row, with the weights in LDS, spent most
+// instructions on repeating the quantization step.
+__global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int block_wgs, int row_blocks, int gather, int update,
+                                                              int block, int ready) {
+    __shared__ __attribute__((aligned(16))) float lds[TILE_FLOATS + STAGE_FLOATS];
     __shared__ float2 diag[2][SEG];
     __shared__ int cols[DPQ_BLOCK];                              // original columns of the block
     __shared__ int general[2];                                   // a diagonal entry of the staged segment asks for the general division
-    const int tid = threadIdx.x;
-    const int rb = blockIdx.x % row_blocks, cb = blockIdx.x / row_blocks;
-    if (ready > 0 && cb == 0) gather = update = 0;
-    const int r0 = rb * ROWS, v0 = c_first + (ready > 0 && cb > 0 ? cb + ready - 1 : cb) * DPQ_BLOCK;
-    const int tr = (tid >> 5) * 8, tc = (tid & 31) * 4;          // K is a multiple of 128: the columns of a tile all exist
-    float w[8][4];
-    {
-        int64_t col[4];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, lc = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float* const stage = lds + TILE_FLOATS;
+
+    if ((int)blockIdx.x >= block_wgs) {
+        // 128 rows x 128 columns, a wavefront 64 x 32 of them
+        const int rb = ((int)blockIdx.x - block_wgs) % row_blocks, cb = ((int)blockIdx.x - block_wgs) / row_blocks + (block_wgs > 0 ? 1 : 0);
+        const int r0 = rb * UP_ROWS, v0 = c_first + (ready > 0 && cb > 0 ? cb + ready - 1 : cb) * DPQ_BLOCK;
+        const int wr = (wave >> 2) * 64, wc = (wave & 3) * 32;
+        const int col = v0 + wc + lc;
+        float w[32];
+        {
+            const int64_t from = (gather && a.perm) ? a.perm[col] : col;
+            const float* src = gather ? a.w : a.work;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) col[j] = (gather && a.perm) ? a.perm[v0 + tc + j] : v0 + tc + j;
-        const float* src = gather ? a.w : a.work;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t n = min(r0 + tr + i, a.N - 1);         // rows past the end repeat the last one; not stored
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[i][j] = src[n * a.K + col[j]];
+            for (int v = 0; v < 32; ++v)                         // rows past the end repeat the last one; not stored
+                w[v] = src[(int64_t)min(r0 + wr + 32 * (v >> 4) + product_row(v & 15, lane), a.N - 1) * a.K + from];
         }
-    }
-    if (update) {
-        float* el = lds;                                         // el[q * 64 + r]: error q of row r of the tile
-        float* ul = lds + SEG * ROWS;                            // ul[q * 128 + c]: U[c_err + q, column c of the tile]
-        const float* erow = a.work + (int64_t)min(r0 + (tid & 63), a.N - 1) * a.K + c_err + (tid >> 6) * 4;
-        const float* urow = a.u + (int64_t)(c_err + (tid >> 5)) * a.K + v0 + tc;
-        float e4[2][4], u4[4][4];
-        auto load = [&](int q0) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) e4[h][j] = erow[q0 + h * 16 + j];
-#pragma unroll
-            for (int h = 0; h < 4; ++h)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) u4[h][j] = urow[(int64_t)(q0 + h * 8) * a.K + j];
-        };
-        load(0);
-        for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
-            __syncthreads();                                     // everyone is done with the slice before
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) el[((tid >> 6) * 4 + h * 16 + j) * ROWS + (tid & 63)] = e4[h][j];
-#pragma unroll
-            for (int h = 0; h < 4; ++h)
-                *reinterpret_cast<float4*>(ul + ((tid >> 5) + h * 8) * DPQ_BLOCK + tc) = make_float4(u4[h][0], u4[h][1], u4[h][2], u4[h][3]);
-            __syncthreads();
-            if (q0 + SEG < DPQ_BLOCK) load(q0 + SEG);
+        if (update) {
+            float *el = stage, *ul = stage + SEG * UP_ROWS;
+            Slice<UP_ROWS> slice;
+            slice.load(a, r0, c_err, v0, 0, tid);
+            for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
+                __syncthreads();                                 // everyone is done with the slice before
+                slice.store(el, ul, tid);
+                __syncthreads();
+                if (q0 + SEG < DPQ_BLOCK) slice.load(a, r0, c_err, v0, q0 + SEG, tid);
 #pragma unroll 4
-            for (int q = 0; q < SEG; ++q) {
-                const float4 ea = *reinterpret_cast<const float4*>(el + q * ROWS + tr), eb = *reinterpret_cast<const float4*>(el + q * ROWS + tr + 4);
-                const float4 uu = *reinterpret_cast<const float4*>(ul + q * DPQ_BLOCK + tc);
-                const float ev[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w}, uv[4] = {uu.x, uu.y, uu.z, uu.w};
+                for (int q = 0; q < SEG; ++q) {
+                    const v32f p = outer_products(el[q * UP_ROWS + wr + lane], ul[q * DPQ_BLOCK + wc + lc]);
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) w[i][j] = __fsub_rn(w[i][j], __fmul_rn(ev[i], uv[j]));
+                    for (int v = 0; v < 32; ++v) w[v] = __fsub_rn(w[v], p[v]);
+                }
             }
         }
-    }
-    if (!block || cb != 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (r0 + tr + i < a.N) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a.work[(int64_t)(r0 + tr + i) * a.K + v0 + tc + j] = w[i][j];
-            }
+        for (int v = 0; v < 32; ++v) {
+            const int n = r0 + wr + 32 * (v >> 4) + product_row(v & 15, lane);
+            if (n < a.N) a.work[(int64_t)n * a.K + col] = w[v];
+        }
         return;
     }
 
-    // the block: lane p of row r of the tile
+    // 64 rows of the block.  w -= the products of 32 staged errors (el: [q][64 rows]) with U (ul: [q][stride]) for the wavefront's 32 x 32
+    // outputs at rows wr.., two errors per instruction
     __builtin_amdgcn_s_setprio(2);                               // ahead of the update's wavefronts on the same SIMD
-    const int r = tid >> 2, p = tid & 3, c0 = c_first;
-    const int64_t n = min(r0 + r, a.N - 1);
-    const bool row_ok = r0 + r < a.N;
-    // the rows of U of segment sg, columns from the segment's first on: thread -> 16 values of row tid / 8
-    float us[16];
-    const float* useg = a.u + (int64_t)(c0 + (tid >> 3)) * a.K + c0 + (tid & 7) * 16;
-    float ud;                                                    // threads 0..31: U[q, q] of the segment's columns
-    auto load_u = [&](int sg) {
-        if (tid < SEG) ud = a.u[(int64_t)(c0 + sg * SEG + tid) * (a.K + 1)];
-        if (sg * SEG + (tid & 7) * 16 < DPQ_BLOCK) {
+    const int r0 = blockIdx.x * ROWS, c0 = c_first;
+    {
+        const int wr = (wave >> 2) * 32, wc = (wave & 3) * 32, col = c0 + wc + lc;
+        if (ready > 0) gather = update = 0;
+        float w[16];
+        const int64_t from = (gather && a.perm) ? a.perm[col] : col;
+        const float* src = gather ? a.w : a.work;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) us[j] = useg[(int64_t)sg * SEG * a.K + sg * SEG + j];
+        for (int v = 0; v < 16; ++v) w[v] = src[(int64_t)min(r0 + wr + product_row(v, lane), a.N - 1) * a.K + from];
+        if (update) {
+            float *el = stage, *ul = stage + SEG * ROWS;
+            Slice<ROWS> slice;
+            slice.load(a, r0, c_err, c0, 0, tid);
+            for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
+                __syncthreads();
+                slice.store(el, ul, tid);
+                __syncthreads();
+                if (q0 + SEG < DPQ_BLOCK) slice.load(a, r0, c_err, c0, q0 + SEG, tid);
+#pragma unroll 4
+                for (int q = 0; q < SEG; q += 2) {
+                    const v32f p = outer_products(el[(q + half) * ROWS + wr + lc], ul[(q + half) * DPQ_BLOCK + wc + lc]);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[v]);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[16 + v]);
+                }
+            }
+            __syncthreads();                                     // the last slice has been read by everyone
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lds[(wr + product_row(v, lane)) * TILE_STRIDE + wc + lc] = w[v];
+    }
+    float* const seg_u = stage;                                  // + (segment & 1) * SEG_U
+    float* const seg_e = stage + 2 * SEG_U;                      // + (segment & 1) * SEG_E: [q][64 rows]
+    // The rows of U of segment sg, columns of the segment, by 256 threads: four values each of row t / 8
+    auto stage_u = [&](int sg, int t) {
+        const int q = t >> 3, first = (t & 7) * 4;
+        const float* ur = a.u + (int64_t)(c0 + sg * SEG + q) * a.K + c0 + sg * SEG + first;
+        float* dst = seg_u + (sg & 1) * SEG_U;
+        const int slot = (t & 7) - (q >> 2);                     // what lies left of the row's own slot goes to a slot that nobody reads
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[(q * 4 + j) * PART + (slot >= 0 ? slot : PART - 1)] = ur[j];
+        // (slots past a row's last are read too, for columns of R.w that are done: values of no account)
+        if (t < SEG) {
+            const float ud = a.u[(int64_t)(c0 + sg * SEG + t) * (a.K + 1)];
+            diag[sg & 1][t] = make_float2(ud, __fdiv_rn(1.0f, ud));
+            const bool odd_one = __builtin_amdgcn_ballot_w64(!plain_divisor(ud)) != 0;
+            if (t == 0) general[sg & 1] = odd_one;
         }
     };
-    load_u(0);
-    __syncthreads();                                             // everyone is done with the update's last slice
+    // tile -= products of segment sg's errors, for the 32 columns of segment to, rows wr .. wr + 31; by one wavefront
+    auto push_errors = [&](int sg, int to, int wr) {
+        const float* el = seg_e + (sg & 1) * SEG_E + half * ROWS + wr + lc;
+        const float* ur = a.u + (int64_t)(c0 + sg * SEG + half) * a.K + c0 + to * SEG + lc;
+        float* t = lds + wr * TILE_STRIDE + to * SEG + lc;
+        float uv[SEG / 2], w[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-        *reinterpret_cast<float4*>(lds + (tr + i) * TILE_STRIDE + tc) = make_float4(w[i][0], w[i][1], w[i][2], w[i][3]);
-    if (tid < 2) general[tid] = 0;
-    if (tid < DPQ_BLOCK) cols[tid] = a.perm ? a.perm[c0 + tid] : c0 + tid;
+        for (int q = 0; q < SEG / 2; ++q) uv[q] = ur[(int64_t)(2 * q) * a.K];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) w[v] = t[product_row(v, lane) * TILE_STRIDE];
+#pragma unroll
+        for (int q = 0; q < SEG / 2; ++q) {
+            const v32f p = outer_products(el[2 * q * ROWS], uv[q]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[v]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[16 + v]);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[product_row(v, lane) * TILE_STRIDE] = w[v];
+    };
+    // wavefronts 0 .. 3: lane p of row r; wavefronts 4 .. 7 prepare what comes next
+    const bool chain = wave < 4;
+    const int r = (tid >> 2) & (ROWS - 1), p = tid & 3;
+    const int64_t n = min(r0 + r, a.N - 1);
+    const bool row_ok = r0 + r < a.N;
+    if (!chain) {
+        stage_u(0, tid - 256);
+    } else if (tid < DPQ_BLOCK) {
+        cols[tid] = a.perm ? a.perm[c0 + tid] : c0 + tid;
+    }
     __syncthreads();
     RowState R;
     float* mine = lds + r * TILE_STRIDE;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) R.w[j] = mine[4 * j + p];
-    R.sw = a.s_w[a.per_channel ? n : 0];
-    const int NG = a.K / a.G, g = c0 / a.G;
-    const int og = a.perm ? a.perm[g * a.G] / a.G : g;           // the original group these columns belong to
-    float s, z;
-    if (block == PARAMS_HERE) {                                  // Eq. 8 on the group's current weights, which are the tile's
-        float lo = 0.0f, hi = 0.0f;                              // minimum and maximum: any order gives the same result
-        bool nan = false;
+    if (chain) {
+        R.sw = a.s_w[a.per_channel ? n : 0];
+        const int NG = a.K / a.G, g = c0 / a.G;
+        const int og = a.perm ? a.perm[g * a.G] / a.G : g;       // the original group these columns belong to
+        float s, z;
+        if (block == PARAMS_HERE) {                              // Eq. 8 on the group's current weights, which are the tile's
+            float lo = 0.0f, hi = 0.0f;                          // minimum and maximum: any order gives the same result
+            bool nan = false;
 #pragma unroll 4
-        for (int j = p; j < DPQ_BLOCK; j += 4) {
-            const float w8 = fp8_value(__fdiv_rn(mine[j], R.sw));
-            lo = fminf(lo, w8);
-            hi = fmaxf(hi, w8);
-            nan |= w8 != w8;
-            mine[j] = w8;                                        // what the search below scores
-        }
-#pragma unroll
-        for (int m = 1; m < 4; m <<= 1) {
-            lo = fminf(lo, __shfl_xor(lo, m));
-            hi = fmaxf(hi, __shfl_xor(hi, m));
-        }
-        group_params(lo, hi, s, z);
-        if (a.mse_grid > 1) {                                    // the search of dpq_group_kernel, a row's lanes sharing the candidates
-            __builtin_amdgcn_wave_barrier();                     // a row's lanes lie in one wavefront, whose LDS accesses run in order
-            float best = __builtin_inff(), bs = s, bz = z;
-            int best_i = a.mse_grid;
-            for (int i = p; i < a.mse_grid; i += 4) {
-                const float shrink = __fsub_rn(1.0f, __fmul_rn((float)i, a.shrink_step));
-                float si, zi, score = 0.0f;
-                group_params(__fmul_rn(shrink, lo), __fmul_rn(shrink, hi), si, zi);
-                add_squared_error(mine, si, zi, __builtin_amdgcn_ballot_w64(!plain_divisor(si) || nan) == 0, score);
-                if (score < best) { best = score; best_i = i; bs = si; bz = zi; }
+            for (int j = p; j < DPQ_BLOCK; j += 4) {
+                const float w8 = fp8_value(__fdiv_rn(mine[j], R.sw));
+                lo = fminf(lo, w8);
+                hi = fmaxf(hi, w8);
+                nan |= w8 != w8;
             }
 #pragma unroll
             for (int m = 1; m < 4; m <<= 1) {
-                const float ob = __shfl_xor(best, m), os = __shfl_xor(bs, m), oz = __shfl_xor(bz, m);
-                const int oi = __shfl_xor(best_i, m);
-                if (ob < best || (ob == best && oi < best_i)) { best = ob; best_i = oi; bs = os; bz = oz; }
+                lo = fminf(lo, __shfl_xor(lo, m));
+                hi = fmaxf(hi, __shfl_xor(hi, m));
             }
-            s = bs;
-            z = bz;
-        }
-        if (p == 0 && row_ok) {
-            a.scales[n * NG + og] = s;
-            a.zeros[n * NG + og] = (uint8_t)z;
-        }
-    } else {
-        s = a.scales[n * NG + og];
-        z = (float)a.zeros[n * NG + og];
-    }
-    R.s = s;
-    R.z = z;
-    R.y_sw = __fdiv_rn(1.0f, R.sw);
-    R.y_s = __fdiv_rn(1.0f, s);
-    R.span = plain_divisor(R.sw) && plain_divisor(s) ? NUM_SPAN : 0u;
-    __syncthreads();                                             // the tile has been read by everyone
-
-    auto stage_u = [&](int sg) {
-        float* dst = lds + (sg & 1) * SEG_FLOATS;
-        const int q = tid >> 3, first = (tid & 7) * 16, col = sg * SEG + first;
-        if (col < DPQ_BLOCK) {
+            group_params(lo, hi, s, z);
+            if (a.mse_grid > 1) {                                // the search of dpq_group_kernel, a row's lanes sharing the candidates
+                float keep[32];                                  // the search scores FP8 values, which stand in the weights' place meanwhile
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {                       // what lies left of the row's own slot goes to a slot that nobody reads
-                const int slot = (first + j) / 4 - q / 4;
-                dst[(q * 4 + (j & 3)) * PART + (slot >= 0 ? slot : PART - 1)] = us[j];
+                for (int j = 0; j < 32; ++j) {
+                    keep[j] = mine[4 * j + p];
+                    mine[4 * j + p] = fp8_value(__fdiv_rn(keep[j], R.sw));
+                }
+                __builtin_amdgcn_wave_barrier();                 // a row's lanes lie in one wavefront, whose LDS accesses run in order
+                float best = __builtin_inff(), bs = s, bz = z;
+                int best_i = a.mse_grid;
+                for (int i = p; i < a.mse_grid; i += 4) {
+                    const float shrink = __fsub_rn(1.0f, __fmul_rn((float)i, a.shrink_step));
+                    float si, zi, score = 0.0f;
+                    group_params(__fmul_rn(shrink, lo), __fmul_rn(shrink, hi), si, zi);
+                    add_squared_error(mine, si, zi, __builtin_amdgcn_ballot_w64(!plain_divisor(si) || nan) == 0, score);
+                    if (score < best) { best = score; best_i = i; bs = si; bz = zi; }
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int j = 0; j < 32; ++j) mine[4 * j + p] = keep[j];
+#pragma unroll
+                for (int m = 1; m < 4; m <<= 1) {
+                    const float ob = __shfl_xor(best, m), os = __shfl_xor(bs, m), oz = __shfl_xor(bz, m);
+                    const int oi = __shfl_xor(best_i, m);
+                    if (ob < best || (ob == best && oi < best_i)) { best = ob; best_i = oi; bs = os; bz = oz; }
+                }
+                s = bs;
+                z = bz;
             }
+            if (p == 0 && row_ok) {
+                a.scales[n * NG + og] = s;
+                a.zeros[n * NG + og] = (uint8_t)z;
+            }
+        } else {
+            s = a.scales[n * NG + og];
+            z = (float)a.zeros[n * NG + og];
         }
-        if (tid < SEG) {
-            diag[sg & 1][tid] = make_float2(ud, __fdiv_rn(1.0f, ud));
-            if (!plain_divisor(ud)) atomicOr(&general[sg & 1], 1);
-        }
-        // (slots past a row's last are read too, for columns of R.w that are done: values of no account)
-    };
-#define W4A8_DPQ_SEGMENT(SG)                                                                                        \
-    {                                                                                                               \
-        stage_u(SG);                                                                                                \
-        __syncthreads();                                                                                            \
-        if (SG < 3) load_u(SG + 1);                                                                                 \
-        const bool diag_plain = general[SG & 1] == 0;                                                               \
-        dpq_segment<32 - 8 * SG>(R, a, lds + (SG & 1) * SEG_FLOATS, diag[SG & 1], cols + SG * SEG, diag_plain, n, row_ok, c0 + SG * SEG, p); \
+        R.s = s;
+        R.z = z;
+        R.y_sw = __fdiv_rn(1.0f, R.sw);
+        R.y_s = __fdiv_rn(1.0f, s);
+        R.span = plain_divisor(R.sw) && plain_divisor(s) ? NUM_SPAN : 0u;
     }
-    W4A8_DPQ_SEGMENT(0) W4A8_DPQ_SEGMENT(1) W4A8_DPQ_SEGMENT(2) W4A8_DPQ_SEGMENT(3)
-#undef W4A8_DPQ_SEGMENT
+    constexpr int SEGS = DPQ_BLOCK / SEG;
+#pragma unroll 1
+    for (int sg = 0; sg < SEGS; ++sg) {
+        if (chain) {
+            const float* u = seg_u + (sg & 1) * SEG_U + p * PART;
+            const float2* d = diag[sg & 1];
+            const bool diag_plain = general[sg & 1] == 0;
+            float* el = seg_e + (sg & 1) * SEG_E;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) R.w[j] = mine[sg * SEG + 4 * j + p];
+            // a loop of four weights: unrolled, the code of a block takes longer to fetch than to run
+#pragma unroll 1
+            for (int t = 0; t < SEG / 4; ++t, u += 16 * PART, d += 4) {
+                float code = 0.0f;
+                const int col = cols[sg * SEG + 4 * t + p];
+                dpq_weight<0>(R, u, d[0], diag_plain, p, code);
+                dpq_weight<1>(R, u + 4 * PART, d[1], diag_plain, p, code);
+                dpq_weight<2>(R, u + 8 * PART, d[2], diag_plain, p, code);
+                dpq_weight<3>(R, u + 12 * PART, d[3], diag_plain, p, code);
+                el[(4 * t + p) * ROWS + r] = R.w[0];
+                if (row_ok) {
+                    a.work[n * a.K + c0 + sg * SEG + 4 * t + p] = R.w[0];
+                    a.codes[n * a.K + col] = (uint8_t)code;
+                }
+#pragma unroll
+                for (int j = 0; j + 1 < 8; ++j) R.w[j] = R.w[j + 1];
+            }
+        } else {
+            if (sg + 1 < SEGS) stage_u(sg + 1, tid - 256);
+            // the segment before this one's errors, for the segments after this one
+            if (sg > 0)
+                for (int i = wave - 4; i < 2 * (SEGS - 1 - sg); i += 4) push_errors(sg - 1, sg + 1 + i / 2, (i & 1) * 32);
+        }
+        __syncthreads();
+        if (sg + 1 < SEGS && wave < 2) push_errors(sg, sg + 1, wave * 32);
+        __syncthreads();
+    }
 }
 
 // Group parameters of the group at columns c0 .. c0 + G - 1, which `work` holds up to date: Eq. 8 on the FP8 values, and with
@@ -519,10 +578,11 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
     a.u = u; a.s_w = s_w; a.per_channel = per_channel; a.perm = perm;
     a.N = (int)N; a.K = (int)K; a.G = (int)G;
     a.codes = codes; a.scales = scales; a.zeros = zeros;
-    const int row_blocks = (int)((N + ROWS - 1) / ROWS), nb = (int)(K / DPQ_BLOCK);
+    const int row_blocks = (int)((N + UP_ROWS - 1) / UP_ROWS), nb = (int)(K / DPQ_BLOCK);
     auto step = [&](int c_first, int column_blocks, int c_err, int gather, int update, int block, int ready) {
-        hipLaunchKernelGGL(dpq_step_kernel, dim3((unsigned)row_blocks * (unsigned)column_blocks), dim3(256), 0, st, a, c_first, c_err,
-                           row_blocks, gather, update, block, ready);
+        const int block_wgs = block != NO_BLOCK ? (int)((N + ROWS - 1) / ROWS) : 0;
+        const unsigned wgs = (unsigned)block_wgs + (unsigned)row_blocks * (unsigned)(column_blocks - (block != NO_BLOCK ? 1 : 0));
+        hipLaunchKernelGGL(dpq_step_kernel, dim3(wgs), dim3(THREADS), 0, st, a, c_first, c_err, block_wgs, row_blocks, gather, update, block, ready);
         return launch_status();
     };
     auto group = [&](int c0) {                                   // the parameters of the group that starts there
@@ -546,7 +606,7 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
         for (int b = 0; b < nb; ++b) {
             // the block's own columns first, with others up to 512 tiles of 64 x 128 (4096 x 4096, 20 candidates: 2.97 ms; 256
             // tiles 3.03, 768 3.08, the own columns alone 3.17); the rest beside the walk
-            const int lead = b == 0 ? 1 : min(nb - b, max(1, 512 / row_blocks));
+            const int lead = b == 0 ? 1 : min(nb - b, max(1, 256 / row_blocks));
             const int c = b * DPQ_BLOCK, c_err = b > 0 ? c - DPQ_BLOCK : 0;
             if (int e = step(c, lead, c_err, b < 2, b > 0, NO_BLOCK, 0)) return e;
             if (int e = group(c)) return e;
