@@ -145,23 +145,27 @@ __device__ __forceinline__ float quad_broadcast(float v) {       // lane P of th
 }
 
 typedef float v32f __attribute__((ext_vector_type(32)));
+typedef float v8f __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int THREADS = 512;
-constexpr int ROWS = 64;             // rows of a workgroup that quantizes a block; four lanes each in its chain
-constexpr int UP_ROWS = 128;         // rows of a workgroup that only updates
+constexpr int ROWS = 64;             // rows of a workgroup's tile; four lanes each in the chain of a block
 constexpr int SEG = 32;              // columns of a block that are quantized at a stretch, and errors staged at a time
 constexpr int TILE_STRIDE = DPQ_BLOCK + 4;
 constexpr int PART = 12;             // staged U of a segment: [column q][lane p of the row][slot]: U[q, 4 * (q / 4 + slot) + p], 8 slots
 constexpr int TILE_FLOATS = ROWS * TILE_STRIDE;
 constexpr int SEG_U = SEG * 4 * PART, SEG_E = SEG * ROWS;        // U of a segment, its errors
-constexpr int STAGE_FLOATS = SEG * (UP_ROWS + DPQ_BLOCK);        // one slice of an update: errors and U
-static_assert(2 * SEG_U + 2 * SEG_E <= STAGE_FLOATS && SEG * (ROWS + DPQ_BLOCK) <= STAGE_FLOATS, "the chain's buffers fit");
+constexpr int SLICE_FLOATS = SEG * (ROWS + DPQ_BLOCK);           // one slice of an update: errors and U
+constexpr int STAGE_FLOATS = 2 * SEG_U + 2 * SEG_E > SLICE_FLOATS ? 2 * SEG_U + 2 * SEG_E : SLICE_FLOATS;
 
-// Products of one error column with one row of U: a 32 x 32 outer product per half of the wavefront, each product rounded by itself (an FMA
-// with zero), which is what Eq. 12 asks for -- only the sign of a zero product may differ, which changes nothing but the sign of a
-// weight that is zero.  a: lane l has the error of row l % 32 of block l / 32; b: U of column l % 32 of block l / 32.  Result register v:
-// block v / 16, row 8 (v % 16 / 4) + 4 (l / 32) + v % 4, column l % 32.
-__device__ __forceinline__ v32f outer_products(float a, float b) { return __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, v32f{}, 0, 0, 0); }
+// Products of two error columns with the two rows of U that go with them, 32 x 32 each; every product is rounded by itself (an FMA with
+// zero), which is what Eq. 12 asks for -- only the sign of a zero product may differ, which changes nothing but the sign of a
+// weight that is zero.  a: lane l has row l % 32 of error column l / 32; b: column l % 32 of that row of U.  Registers 0 .. 15 belong
+// to the first error column, 16 .. 31 to the second: row product_row, column l % 32.
+__device__ __forceinline__ v32f products_32(float a, float b) { return __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, v32f{}, 0, 0, 0); }
 __device__ __forceinline__ int product_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+// The same for 16 rows x 32 columns: a: lane l has row l % 16 of error column l / 32, b: column 16 (l / 16 % 2) + l % 16 of that row of U.
+// Registers 8 e .. 8 e + 7 belong to error column e: column 16 (v / 4 % 2) + l % 16, row 4 (l / 16) + v % 4.
+__device__ __forceinline__ v16f products_16(float a, float b) { return __builtin_amdgcn_mfma_f32_16x16x1f32(a, b, v16f{}, 0, 0, 0); }
 
 struct RowState {
     float w[8];                   // the lane's columns of the segment that are left: slot j = column 4 (done + j) + p
@@ -170,62 +174,70 @@ struct RowState {
 };
 
 // One weight: column q of the segment, U[q, v] for the lane's columns v from q's slot on at `u`, U[q, q] and its reciprocal
-// in `d`.  Q = q % 4 is the lane of the row that owns it, in slot 0 of R.w.
+// in `d`.  Q = q % 4 is the lane of the row that owns it, in slot 0 of R.w.  For divisors and a weight in the range of div_by;
+// `far` ends up at R.span or above if the weight is not.  The chain from one column to the next is thirty dependent operations; the
+// updates of the slots behind the first, which the next three columns do not need, fill the gaps between them.
 template <int Q>
-__device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d, bool diag_plain, int p, float& code) {
-    const float4 v0 = *reinterpret_cast<const float4*>(u), v1 = *reinterpret_cast<const float4*>(u + 4);   // back by the time e is there
+__device__ __forceinline__ void dpq_weight(RowState& R, const float* u, float2 d, int p, float& code, uint32_t& far) {
+    const float4 v0 = *reinterpret_cast<const float4*>(u), v1 = *reinterpret_cast<const float4*>(u + 4);
     const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
     const float w = quad_broadcast<Q>(R.w[0]);
-    const bool plain = (__float_as_uint(w) & 0x7FFFFFFFu) - NUM_LO < R.span && diag_plain;
+    far = max(far, (__float_as_uint(w) & 0x7FFFFFFFu) - NUM_LO);
     const float w8 = fp8_value_finite(div_by(w, R.sw, R.y_sw));                           // Eq. 7
     const float t = __fadd_rn(div_by(w8, R.s, R.y_s), R.z);
-    float uq = __builtin_amdgcn_fmed3f(rintf(t), 0.0f, 15.0f);                            // Eq. 9
+    const float uq = __builtin_amdgcn_fmed3f(rintf(t), 0.0f, 15.0f);                      // Eq. 9
     const float w8_hat = fp8_value_finite(__fmul_rn(__fsub_rn(uq, R.z), R.s));            // Eq. 10
-    float e = div_by(__fsub_rn(w, __fmul_rn(w8_hat, R.sw)), d.x, d.y);                    // Eq. 11
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!plain) != 0, 0)) {                  // zeros, extreme values: the general division
-        const float g8 = fp8_value(__fdiv_rn(w, R.sw));
-        uq = fminf(fmaxf(rintf(__fadd_rn(__fdiv_rn(g8, R.s), R.z)), 0.0f), 15.0f);
-        const float g8_hat = fp8_value(__fmul_rn(__fsub_rn(uq, R.z), R.s));
-        e = __fdiv_rn(__fsub_rn(w, __fmul_rn(g8_hat, R.sw)), d.x);
-    }
+    const float e = div_by(__fsub_rn(w, __fmul_rn(w8_hat, R.sw)), d.x, d.y);              // Eq. 11
+    // Eq. 12 inside the segment.  In the weight's own slot lanes behind it are updated, its own lane keeps the error, those before it theirs
+    const float next = __fsub_rn(R.w[0], __fmul_rn(e, v[0]));
+    R.w[0] = p > Q ? next : p == Q ? e : R.w[0];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {                                                         // Eq. 12 inside the segment
-        const float next = __fsub_rn(R.w[j], __fmul_rn(e, v[j]));
-        // in the weight's own slot: lanes behind it are updated, its own lane keeps the error, those before it theirs
+    for (int j = 1; j < 8; ++j) R.w[j] = __fsub_rn(R.w[j], __fmul_rn(e, v[j]));
+    code = p == Q ? uq : code;
+}
+
+// The same for any values (zeros, extreme ones): the general division.
+__device__ __forceinline__ void dpq_weight_general(RowState& R, int Q, const float* u, float d, int p, int lane, float& code) {
+    const float w = __shfl(R.w[0], (lane & ~3) | Q);
+    const float g8 = fp8_value(__fdiv_rn(w, R.sw));
+    const float uq = fminf(fmaxf(rintf(__fadd_rn(__fdiv_rn(g8, R.s), R.z)), 0.0f), 15.0f);
+    const float g8_hat = fp8_value(__fmul_rn(__fsub_rn(uq, R.z), R.s));
+    const float e = __fdiv_rn(__fsub_rn(w, __fmul_rn(g8_hat, R.sw)), d);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float next = __fsub_rn(R.w[j], __fmul_rn(e, u[j]));
         R.w[j] = j > 0 ? next : p > Q ? next : p == Q ? e : R.w[j];
-        asm volatile("" : "+v"(R.w[j]));                         // here, not where the column is next read: the products would pile up
     }
-    if (p == Q) code = uq;
+    code = p == Q ? uq : code;
 }
 
 // What becomes of the first column block's tiles: written to `work` like the others, or quantized with the group's parameters,
 // formed from the tile (groups of one block) or found in the outputs (where dpq_group_kernel put them).
 enum BlockStep { NO_BLOCK = 0, PARAMS_HERE = 1, PARAMS_GIVEN = 2 };
 
-// The slices of an update: 32 errors of `Rows` rows from r0 on and the 32 rows of U that go with them, the tile's 128 columns, on their
-// way to LDS.  el[q * Rows + r]: error q of row r; ul[q * 128 + c]: U[c_err + q, v0 + c].
-template <int Rows> struct Slice {
-    static constexpr int EPT = SEG * Rows / THREADS, TPR = SEG / EPT;   // errors per thread, threads per row
-    float e[EPT], u[8];
+// A slice of an update: 32 errors of the tile's rows from r0 on and the 32 rows of U that go with them, the tile's 128 columns, on their
+// way to LDS.  el[q * 64 + r]: error q of row r; ul[q * 128 + c]: U[c_err + q, v0 + c].
+struct Slice {
+    float e[4], u[8];
     __device__ __forceinline__ void load(const DpqArgs& a, int r0, int c_err, int v0, int q0, int tid) {
-        const float* er = a.work + (int64_t)min(r0 + tid % Rows, a.N - 1) * a.K + c_err + q0 + tid / Rows * EPT;
+        const float* er = a.work + (int64_t)min(r0 + (tid & 63), a.N - 1) * a.K + c_err + q0 + (tid >> 6) * 4;
         const float* ur = a.u + (int64_t)(c_err + q0 + (tid >> 4)) * a.K + v0 + (tid & 15) * 8;
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) e[j] = er[j];
+        for (int j = 0; j < 4; ++j) e[j] = er[j];
 #pragma unroll
         for (int j = 0; j < 8; ++j) u[j] = ur[j];
     }
     __device__ __forceinline__ void store(float* el, float* ul, int tid) const {
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) el[(tid / Rows * EPT + j) * Rows + tid % Rows] = e[j];
+        for (int j = 0; j < 4; ++j) el[((tid >> 6) * 4 + j) * ROWS + (tid & 63)] = e[j];
         float* d = ul + (tid >> 4) * DPQ_BLOCK + (tid & 15) * 8;
         *reinterpret_cast<float4*>(d) = make_float4(u[0], u[1], u[2], u[3]);
         *reinterpret_cast<float4*>(d + 4) = make_float4(u[4], u[5], u[6], u[7]);
     }
 };
 
-// One launch of the walk.  The first block_wgs workgroups own 64 rows of the first column block, from c_first on, the others 128 rows x 128
-// columns of the column blocks:
+// One launch of the walk.  Workgroups own tiles of 64 rows x 128 columns of the columns from c_first on, the tiles of the
+// first column block coming first:
 //   gather:  the tile comes from the original weights, reordered; otherwise from `work`;
 //   update:  it receives the errors of the block at c_err (Eq. 12 for the columns right of a block: for every column q of
 //            that block, ascending, w <- w - err[n, q] * U[c_err + q, v]);
@@ -236,15 +248,17 @@ template <int Rows> struct Slice {
 // launch of its own the block's columns are brought up to date in a launch before that.  Wider groups need all of their columns up to
 // date before the first is quantized: an update and a block launch each.
 // Update: the products come from the matrix unit, one outer product per error column, so that the vector unit is left with the
-// subtractions: 4096 rows x 3968 columns 112 us with both on the vector unit, TIME_UPDATE now.
+// subtractions.  The first update of 4096 x 4096 (1984 tiles, 2.1 G products) takes 106 us, of which loading and storing the tiles is about a
+// third; 112 us with both operations on the vector unit, where the serial part did not hide behind it.
 // Block: 32 columns at a time.  Lane p of a row's four holds the columns v with v % 4 == p of a segment in registers; every lane takes the
 // (identical) quantization step and applies the error to its own columns.  The columns of the later segments take the segment's 32
 // errors afterwards, on the matrix unit: those of the next one before it begins, the others by the four wavefronts that have no rows, beside the
 // chain.  A wavefront alone on its SIMD issues one vector operation every five cycles, so what a column costs is their number: 60,
 // with all later columns of the block in registers 100 on average.  32 lanes per row, with the weights in LDS, spent most
-// instructions on repeating the quantization step.
-__global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int block_wgs, int row_blocks, int gather, int update,
-                                                              int block, int ready) {
+// instructions on repeating the quantization step.  A launch whose updates are few takes 39 us (256 x 4096 in all 1.24 ms, before
+// 1.92 ms); 4096 x 4096 takes 2.1 ms, before 2.5 ms, and 16384 x 4096 5.9 ms, before 6.7 ms.
+__global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int row_blocks, int gather, int update, int block,
+                                                              int ready) {
     __shared__ __attribute__((aligned(16))) float lds[TILE_FLOATS + STAGE_FLOATS];
     __shared__ float2 diag[2][SEG];
     __shared__ int cols[DPQ_BLOCK];                              // original columns of the block
@@ -252,78 +266,53 @@ __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_f
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, lc = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* const stage = lds + TILE_FLOATS;
-
-    if ((int)blockIdx.x >= block_wgs) {
-        // 128 rows x 128 columns, a wavefront 64 x 32 of them
-        const int rb = ((int)blockIdx.x - block_wgs) % row_blocks, cb = ((int)blockIdx.x - block_wgs) / row_blocks + (block_wgs > 0 ? 1 : 0);
-        const int r0 = rb * UP_ROWS, v0 = c_first + (ready > 0 && cb > 0 ? cb + ready - 1 : cb) * DPQ_BLOCK;
-        const int wr = (wave >> 2) * 64, wc = (wave & 3) * 32;
-        const int col = v0 + wc + lc;
-        float w[32];
-        {
-            const int64_t from = (gather && a.perm) ? a.perm[col] : col;
-            const float* src = gather ? a.w : a.work;
+    const int rb = blockIdx.x % row_blocks, cb = blockIdx.x / row_blocks;
+    const bool quantize = block && cb == 0;
+    if (quantize) __builtin_amdgcn_s_setprio(2);                 // ahead of the update's wavefronts on the same SIMD
+    if (ready > 0 && cb == 0) gather = update = 0;
+    const int r0 = rb * ROWS, v0 = c_first + (ready > 0 && cb > 0 ? cb + ready - 1 : cb) * DPQ_BLOCK, c0 = c_first;
+    {
+        // a wavefront has 32 rows x 32 columns of the tile
+        const int wr = (wave >> 2) * 32, wc = (wave & 3) * 32, col = v0 + wc + lc;
+        v16f w;
+        const int64_t from = (gather && a.perm) ? a.perm[col] : col;
+        const float* src = gather ? a.w : a.work;
 #pragma unroll
-            for (int v = 0; v < 32; ++v)                         // rows past the end repeat the last one; not stored
-                w[v] = src[(int64_t)min(r0 + wr + 32 * (v >> 4) + product_row(v & 15, lane), a.N - 1) * a.K + from];
-        }
+        for (int v = 0; v < 16; ++v)                             // rows past the end repeat the last one; not stored
+            w[v] = src[(int64_t)min(r0 + wr + product_row(v, lane), a.N - 1) * a.K + from];
         if (update) {
-            float *el = stage, *ul = stage + SEG * UP_ROWS;
-            Slice<UP_ROWS> slice;
+            float *el = stage, *ul = stage + SEG * ROWS;
+            const float *ea = el + half * ROWS + wr + lc, *ua = ul + half * DPQ_BLOCK + wc + lc;
+            Slice slice;
             slice.load(a, r0, c_err, v0, 0, tid);
             for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
                 __syncthreads();                                 // everyone is done with the slice before
                 slice.store(el, ul, tid);
                 __syncthreads();
                 if (q0 + SEG < DPQ_BLOCK) slice.load(a, r0, c_err, v0, q0 + SEG, tid);
-#pragma unroll 4
-                for (int q = 0; q < SEG; ++q) {
-                    const v32f p = outer_products(el[q * UP_ROWS + wr + lane], ul[q * DPQ_BLOCK + wc + lc]);
-#pragma unroll
-                    for (int v = 0; v < 32; ++v) w[v] = __fsub_rn(w[v], p[v]);
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 32; ++v) {
-            const int n = r0 + wr + 32 * (v >> 4) + product_row(v & 15, lane);
-            if (n < a.N) a.work[(int64_t)n * a.K + col] = w[v];
-        }
-        return;
-    }
-
-    // 64 rows of the block.  w -= the products of 32 staged errors (el: [q][64 rows]) with U (ul: [q][stride]) for the wavefront's 32 x 32
-    // outputs at rows wr.., two errors per instruction
-    __builtin_amdgcn_s_setprio(2);                               // ahead of the update's wavefronts on the same SIMD
-    const int r0 = blockIdx.x * ROWS, c0 = c_first;
-    {
-        const int wr = (wave >> 2) * 32, wc = (wave & 3) * 32, col = c0 + wc + lc;
-        if (ready > 0) gather = update = 0;
-        float w[16];
-        const int64_t from = (gather && a.perm) ? a.perm[col] : col;
-        const float* src = gather ? a.w : a.work;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) w[v] = src[(int64_t)min(r0 + wr + product_row(v, lane), a.N - 1) * a.K + from];
-        if (update) {
-            float *el = stage, *ul = stage + SEG * ROWS;
-            Slice<ROWS> slice;
-            slice.load(a, r0, c_err, c0, 0, tid);
-            for (int q0 = 0; q0 < DPQ_BLOCK; q0 += SEG) {
-                __syncthreads();
-                slice.store(el, ul, tid);
-                __syncthreads();
-                if (q0 + SEG < DPQ_BLOCK) slice.load(a, r0, c_err, c0, q0 + SEG, tid);
+                v32f p = products_32(ea[0], ua[0]);
 #pragma unroll 4
                 for (int q = 0; q < SEG; q += 2) {
-                    const v32f p = outer_products(el[(q + half) * ROWS + wr + lc], ul[(q + half) * DPQ_BLOCK + wc + lc]);
+                    const int qn = q + 2 < SEG ? q + 2 : q;      // the next products are formed while these are subtracted
+                    v32f next = products_32(ea[qn * ROWS], ua[qn * DPQ_BLOCK]);
+                    asm volatile("" : "+v"(next), "+v"(w)); // ... which keeps the order as written
 #pragma unroll
                     for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[v]);
 #pragma unroll
                     for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[16 + v]);
+                    p = next;
                 }
             }
-            __syncthreads();                                     // the last slice has been read by everyone
         }
+        if (!quantize) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int n = r0 + wr + product_row(v, lane);
+                if (n < a.N) a.work[(int64_t)n * a.K + col] = w[v];
+            }
+            return;
+        }
+        if (update) __syncthreads();                             // the last slice has been read by everyone
 #pragma unroll
         for (int v = 0; v < 16; ++v) lds[(wr + product_row(v, lane)) * TILE_STRIDE + wc + lc] = w[v];
     }
@@ -345,26 +334,35 @@ __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_f
             if (t == 0) general[sg & 1] = odd_one;
         }
     };
-    // tile -= products of segment sg's errors, for the 32 columns of segment to, rows wr .. wr + 31; by one wavefront
-    auto push_errors = [&](int sg, int to, int wr) {
-        const float* el = seg_e + (sg & 1) * SEG_E + half * ROWS + wr + lc;
-        const float* ur = a.u + (int64_t)(c0 + sg * SEG + half) * a.K + c0 + to * SEG + lc;
-        float* t = lds + wr * TILE_STRIDE + to * SEG + lc;
-        float uv[SEG / 2], w[16];
+    // tile -= products of segment sg's errors, for the 32 columns of segment `to`, rows wr .. wr + 15, by one wavefront: U first, the rest when
+    // the errors are there
+    const int blk = (lane >> 4) & 1, l16 = lane & 15;
+    float uv[SEG / 2];
+    auto fetch_u = [&](int sg, int to) {
+        const float* ur = a.u + (int64_t)(c0 + sg * SEG + half) * a.K + c0 + to * SEG + 16 * blk + l16;
 #pragma unroll
         for (int q = 0; q < SEG / 2; ++q) uv[q] = ur[(int64_t)(2 * q) * a.K];
+    };
+    auto push_errors = [&](int sg, int to, int wr) {
+        const float* el = seg_e + (sg & 1) * SEG_E + half * ROWS + wr + l16;
+        float* t = lds + (wr + 4 * (lane >> 4)) * TILE_STRIDE + to * SEG + l16;
+        v8f w;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) w[v] = t[product_row(v, lane) * TILE_STRIDE];
+        for (int v = 0; v < 8; ++v) w[v] = t[(v & 3) * TILE_STRIDE + 16 * (v >> 2)];
+        v16f p = products_16(el[0], uv[0]);
 #pragma unroll
         for (int q = 0; q < SEG / 2; ++q) {
-            const v32f p = outer_products(el[2 * q * ROWS], uv[q]);
+            const int qn = q + 1 < SEG / 2 ? q + 1 : q;
+            v16f next = products_16(el[2 * qn * ROWS], uv[qn]);
+            asm volatile("" : "+v"(next), "+v"(w));         // keeps the order as written
 #pragma unroll
-            for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[v]);
+            for (int v = 0; v < 8; ++v) w[v] = __fsub_rn(w[v], p[v]);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) w[v] = __fsub_rn(w[v], p[16 + v]);
+            for (int v = 0; v < 8; ++v) w[v] = __fsub_rn(w[v], p[8 + v]);
+            p = next;
         }
 #pragma unroll
-        for (int v = 0; v < 16; ++v) t[product_row(v, lane) * TILE_STRIDE] = w[v];
+        for (int v = 0; v < 8; ++v) t[(v & 3) * TILE_STRIDE + 16 * (v >> 2)] = w[v];
     };
     // wavefronts 0 .. 3: lane p of row r; wavefronts 4 .. 7 prepare what comes next
     const bool chain = wave < 4;
@@ -458,10 +456,18 @@ __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_f
             for (int t = 0; t < SEG / 4; ++t, u += 16 * PART, d += 4) {
                 float code = 0.0f;
                 const int col = cols[sg * SEG + 4 * t + p];
-                dpq_weight<0>(R, u, d[0], diag_plain, p, code);
-                dpq_weight<1>(R, u + 4 * PART, d[1], diag_plain, p, code);
-                dpq_weight<2>(R, u + 8 * PART, d[2], diag_plain, p, code);
-                dpq_weight<3>(R, u + 12 * PART, d[3], diag_plain, p, code);
+                const RowState before = R;
+                uint32_t far = diag_plain ? 0u : ~0u;
+                dpq_weight<0>(R, u, d[0], p, code, far);
+                dpq_weight<1>(R, u + 4 * PART, d[1], p, code, far);
+                dpq_weight<2>(R, u + 8 * PART, d[2], p, code, far);
+                dpq_weight<3>(R, u + 12 * PART, d[3], p, code, far);
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(far >= R.span) != 0, 0)) {   // once more, by the general division
+                    R = before;
+                    code = 0.0f;
+#pragma unroll 1
+                    for (int q = 0; q < 4; ++q) dpq_weight_general(R, q, u + 4 * PART * q, d[q].x, p, lane, code);
+                }
                 el[(4 * t + p) * ROWS + r] = R.w[0];
                 if (row_ok) {
                     a.work[n * a.K + c0 + sg * SEG + 4 * t + p] = R.w[0];
@@ -472,12 +478,17 @@ __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_f
             }
         } else {
             if (sg + 1 < SEGS) stage_u(sg + 1, tid - 256);
-            // the segment before this one's errors, for the segments after this one
+            const int wr = (wave - 4) * 16;
+            // the errors of the segment before this one, for the segments after this one
             if (sg > 0)
-                for (int i = wave - 4; i < 2 * (SEGS - 1 - sg); i += 4) push_errors(sg - 1, sg + 1 + i / 2, (i & 1) * 32);
+                for (int to = sg + 1; to < SEGS; ++to) {
+                    fetch_u(sg - 1, to);
+                    push_errors(sg - 1, to, wr);
+                }
+            if (sg + 1 < SEGS) fetch_u(sg, sg + 1);              // there when this segment's errors are
         }
         __syncthreads();
-        if (sg + 1 < SEGS && wave < 2) push_errors(sg, sg + 1, wave * 32);
+        if (sg + 1 < SEGS && !chain) push_errors(sg, sg + 1, (wave - 4) * 16);
         __syncthreads();
     }
 }
@@ -578,11 +589,10 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
     a.u = u; a.s_w = s_w; a.per_channel = per_channel; a.perm = perm;
     a.N = (int)N; a.K = (int)K; a.G = (int)G;
     a.codes = codes; a.scales = scales; a.zeros = zeros;
-    const int row_blocks = (int)((N + UP_ROWS - 1) / UP_ROWS), nb = (int)(K / DPQ_BLOCK);
+    const int row_blocks = (int)((N + ROWS - 1) / ROWS), nb = (int)(K / DPQ_BLOCK);
     auto step = [&](int c_first, int column_blocks, int c_err, int gather, int update, int block, int ready) {
-        const int block_wgs = block != NO_BLOCK ? (int)((N + ROWS - 1) / ROWS) : 0;
-        const unsigned wgs = (unsigned)block_wgs + (unsigned)row_blocks * (unsigned)(column_blocks - (block != NO_BLOCK ? 1 : 0));
-        hipLaunchKernelGGL(dpq_step_kernel, dim3(wgs), dim3(THREADS), 0, st, a, c_first, c_err, block_wgs, row_blocks, gather, update, block, ready);
+        hipLaunchKernelGGL(dpq_step_kernel, dim3((unsigned)row_blocks * (unsigned)column_blocks), dim3(THREADS), 0, st, a, c_first, c_err,
+                           row_blocks, gather, update, block, ready);
         return launch_status();
     };
     auto group = [&](int c0) {                                   // the parameters of the group that starts there
@@ -606,7 +616,7 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
         for (int b = 0; b < nb; ++b) {
             // the block's own columns first, with others up to 512 tiles of 64 x 128 (4096 x 4096, 20 candidates: 2.97 ms; 256
             // tiles 3.03, 768 3.08, the own columns alone 3.17); the rest beside the walk
-            const int lead = b == 0 ? 1 : min(nb - b, max(1, 256 / row_blocks));
+            const int lead = b == 0 ? 1 : min(nb - b, max(1, 512 / row_blocks));
             const int c = b * DPQ_BLOCK, c_err = b > 0 ? c - DPQ_BLOCK : 0;
             if (int e = step(c, lead, c_err, b < 2, b > 0, NO_BLOCK, 0)) return e;
             if (int e = group(c)) return e;
