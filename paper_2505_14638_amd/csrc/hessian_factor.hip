@@ -17,11 +17,11 @@
 //     products (128 deep) in the launch that updates the single column k + 3, which waits for its diagonal tile and
 //     leaves the chip idle otherwise.
 // Every step is one launch over independent tiles, so no kernel waits on another workgroup.
-// Measured at 4096 features, against 64-deep updates on scalar FMAs, a diagonal tile in a launch of its own (112 us each) and
-// an inversion row by row: 11.4 -> 2.75 ms; with the inversion inside the factorization's launches instead of after them
-// (twelve launches that double the inverted blocks, 630 us): 2.41 ms (2.41 to 2.6 over the runs since).  The chain of diagonal tiles bounds it: 22 to 24 us to
-// load, factor and invert one, in 64 launches that take 23 us at the least (38 with the rows of the inverse beside it, 59 with the
-// largest trailing update), and 5.7 us for each panel.
+// 4096 features take 2.0 ms, before the present factor_tile and with half as many wavefronts in flight 2.5 ms.  The 46 GFLOP would
+// take 1.05 ms at the 43 TFLOP/s that the float64 matrix unit reaches on the whole chip.  What a diagonal tile waits for: 5.5 us for its panel,
+// 13 us (64 deep) or 16 us (128 deep) for the launch that updates, factors and inverts it, 1.3 ms over all.  The launches of the middle columns take 20 to 31 us for
+// their products, those of the first up to 50 us; the others wait for the diagonal tile.
+// (Tiles handed to the dies in compact regions, and a higher priority for the workgroup with the diagonal tile, gave nothing.)
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -36,12 +36,10 @@ constexpr int LDT = TB + 2;         // row stride of a whole tile, and of a slic
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
 
-// LDS of a workgroup: two slices while it multiplies; then, if it factors, the tile and the inverses of its four diagonal
-// 16 x 16 blocks
+// LDS of a workgroup: two slices while it multiplies; then, if it factors, the tile
 constexpr int SLICE = TB * LDA;
-constexpr int VD = 16 * 18;         // one such inverse, row stride 18
-constexpr int LDS_DOUBLES = TB * LDT + 4 * VD;
-static_assert(2 * SLICE <= LDS_DOUBLES, "both slices fit");
+constexpr int LDS_DOUBLES = 2 * SLICE;
+static_assert(TB * LDT <= LDS_DOUBLES, "the tile fits");
 
 // scalars[0] = damp * mean(diag(H)); *info = 0.  One workgroup; a fixed summation order.
 __global__ void __launch_bounds__(256) damp_term_kernel(const float* __restrict__ h, int n, double damp, double* __restrict__ scalars,
@@ -94,13 +92,6 @@ __device__ __forceinline__ void block_mac(v4d& acc, const double* a, int lda, co
     }
 }
 
-__device__ __forceinline__ double read_lane(double v, int lane) {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // 1 / sqrt(d) to within an ulp or two: the hardware's estimate (23 bits) and one third-order step.
 // Not finite for d <= 0 and NaN.
 __device__ __forceinline__ double inv_sqrt(double d) {
@@ -109,166 +100,188 @@ __device__ __forceinline__ double inv_sqrt(double d) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// Diagonal tile kb, whose lower triangle lies in `t` (row stride LDT): a[kb, kb] <- its lower Cholesky factor L (zeros
-// above the diagonal); dinv[kb], row-major 64 x 64, and x[kb, kb] <- V = L^-1 (zeros above the diagonal).  A pivot that is not positive is
+// 1 / d likewise
+__device__ __forceinline__ double inverse(double d) {
+    const double y = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// v of lane LANE of each 16 lanes.  What a lane permutation reads must have been written two wait states before; the compiler sees to
+// that only between instructions of its own, so each of these begins with the wait.
+template <int LANE>
+__device__ __forceinline__ double row_broadcast(double v) {
+    double r;
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v), "n"(LANE));
+    return r;
+}
+
+// d[Q + u] += d[J](lane Q + u of each 16) * m for u < COUNT
+template <int J, int Q, int COUNT>
+__device__ __forceinline__ void eliminate_columns(double (&d)[16], double m) {
+#define FMA_ROW_BROADCAST(acc, source, lane) "v_fmac_f64_dpp " acc ", " source ", %[m] row_newbcast:" lane " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (COUNT >= 4) {
+        asm("s_nop 1\n\t" FMA_ROW_BROADCAST("%0", "%[s]", "%[l0]") FMA_ROW_BROADCAST("%1", "%[s]", "%[l1]") FMA_ROW_BROADCAST("%2", "%[s]", "%[l2]")
+                FMA_ROW_BROADCAST("%3", "%[s]", "%[l3]")
+            : "+&v"(d[Q]), "+&v"(d[Q + 1]), "+&v"(d[Q + 2]), "+&v"(d[Q + 3])
+            : [s] "v"(d[J]), [m] "v"(m), [l0] "n"(Q), [l1] "n"(Q + 1), [l2] "n"(Q + 2), [l3] "n"(Q + 3));
+        eliminate_columns<J, Q + 4, COUNT - 4>(d, m);
+    } else if constexpr (COUNT > 0) {
+        asm("s_nop 1\n\t" FMA_ROW_BROADCAST("%0", "%[s]", "%[l0]") : "+v"(d[Q]) : [s] "v"(d[J]), [m] "v"(m), [l0] "n"(Q));
+        eliminate_columns<J, Q + 1, COUNT - 1>(d, m);
+    }
+}
+
+// x[u] += x[u](lane J of each 16) * m
+template <int J>
+__device__ __forceinline__ void eliminate_identity(double (&x)[4], double m) {
+    asm("s_nop 1\n\t" FMA_ROW_BROADCAST("%0", "%0", "%[l]") FMA_ROW_BROADCAST("%1", "%1", "%[l]") FMA_ROW_BROADCAST("%2", "%2", "%[l]")
+            FMA_ROW_BROADCAST("%3", "%3", "%[l]")
+        : "+&v"(x[0]), "+&v"(x[1]), "+&v"(x[2]), "+&v"(x[3])
+        : [m] "v"(m), [l] "n"(J));
+#undef FMA_ROW_BROADCAST
+}
+
+// Pivot J and those after it, of a 16 x 16 block in L~ D L~^T form: d[c] is column c of row i = lane % 16, x[u] column 4 (lane / 16) + u of L~^-1's row
+// i, both rows being in every 16 lanes (d) or spread over them (x).  `pivot` receives the row's own pivot.
+template <int J>
+struct Eliminate {
+    static __device__ __forceinline__ void run(double (&d)[16], double (&x)[4], double& pivot, int i) {
+        const double p = row_broadcast<J>(d[J]);
+        pivot = i == J ? p : pivot;
+        const double m = i > J ? -(d[J] * inverse(p)) : 0.0;          // rows up to the pivot's stay as they are
+        // the next pivot's column first, then whole fours
+        eliminate_columns<J, J + 1, 1>(d, m);
+        eliminate_columns<J, J + 2, 14 - J>(d, m);
+        eliminate_identity<J>(x, m);
+        Eliminate<J + 1>::run(d, x, pivot, i);
+    }
+};
+template <>
+struct Eliminate<15> {
+    static __device__ __forceinline__ void run(double (&d)[16], double (&)[4], double& pivot, int i) {
+        const double p = row_broadcast<15>(d[15]);
+        pivot = i == 15 ? p : pivot;
+    }
+};
+
+// Diagonal tile kb, whose lower triangle lies in `t` (row stride LDT): dinv[kb], row-major 64 x 64, and x[kb, kb] <- V = L^-1 with L its
+// lower Cholesky factor (zeros above the diagonal; L itself is not needed).  A pivot that is not positive is
 // reported through *info (1 + its index in the reversed order, first failure only); the results are then not finite.
-// This is the serial part of the factorization: 64 pivots, each waiting for the one before.  Four panels of 16 columns;
-// one wavefront factors a panel with a row per lane and its 16 columns in registers, the column just finished reaching
-// the other lanes by v_readlane, so that a pivot costs neither a barrier nor a trip through LDS (112 us a tile
-// with two barriers, a square root and a division per pivot, 22 to 24 now); the trailing blocks are then updated by all
-// four on the matrix unit.  V is put together from the inverses of the four 16 x 16
-// diagonal blocks, doubling twice; V's block (i, j) lies in the place of the tile's block (j, i), which L does not use.
-__device__ __forceinline__ void factor_tile(double* t, double* vd, double* __restrict__ a, int n, int kb, double* __restrict__ dinv,
-                                            double* __restrict__ x, int32_t* __restrict__ info) {
+// This is the serial part of the factorization: 64 pivots, each waiting for the one before.  16 at a time: one wavefront
+// brings the 16 x 16 diagonal block up to date with the columns just finished and turns it into the inverse of its factor, the block's rows
+// being in each 16 lanes, so that a pivot reaches the others as an operand of the multiply-add itself (a lane broadcast within
+// 16 lanes): 22 vector operations a pivot, neither a barrier nor a trip through LDS.  The other three meanwhile apply
+// the columns just finished to the rest of the tile, a row of blocks each, and form the rows of V, a block each.
+// With P = V_pp A(r, p)^T = L(r, p)^T no product waits for a transposed operand: the matrix unit's result has the layout of
+// both its operands.  Block (r, c) of the tile is A's, then V's for c <= r, and L(c, r)^T for c > r.
+// 19 thousand cycles a tile, 8 us, half of them for the pivots (150 each); 40 thousand, 17 us, with panels of 64 rows factored by one wavefront, a
+// row per lane and every value broadcast through scalar registers, and the inverse put together afterwards.
+__device__ __forceinline__ void factor_tile(double* t, int n, int kb, double* __restrict__ dinv, double* __restrict__ x, int32_t* __restrict__ info) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
     auto blk = [&](int r, int c) { return t + r * 16 * LDT + c * 16; };
-    for (int jb = 0; jb < 4; ++jb) {
-        if (wave == 0) {
-            double c[16];
-            double* row = t + lane * LDT + jb * 16;
-#pragma unroll
-            for (int j = 0; j < 16; j += 2) {
-                const v2d v = *reinterpret_cast<const v2d*>(row + j);
-                c[j] = v[0];
-                c[j + 1] = v[1];
-            }
-            double d = read_lane(c[0], jb * 16);
-            int bad = -1;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const double rs = inv_sqrt(d);
-                if (!(d > 0.0) && bad < 0) bad = j;
-                double s = d * rs;
-                s = fma(fma(-s, s, d), 0.5 * rs, s);             // sqrt(d)
-                c[j] = (lane == jb * 16 + j) ? s : c[j] * rs;
-                if (j + 1 < 16) {                                // the next pivot first
-                    d = read_lane(fma(-c[j], c[j], c[j + 1]), jb * 16 + j + 1);
-                }
-#pragma unroll
-                for (int q = j + 1; q < 16; ++q) c[q] = fma(-c[j], read_lane(c[j], jb * 16 + q), c[q]);
-            }
-            if (bad >= 0 && lane == 0 && *info == 0) *info = kb * TB + jb * 16 + bad + 1;
-            // rows above the panel belong to finished columns, what lies above the diagonal is not part of L
-            if (lane >= jb * 16) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) row[j] = (jb * 16 + j <= lane) ? c[j] : 0.0;
-            }
-        }
-        __syncthreads();
-        // trailing blocks (r, c), jb < c <= r < 4, numbered row by row
-        int number = 0;
-        for (int r = jb + 1; r < 4; ++r)
-            for (int c = jb + 1; c <= r; ++c, ++number)
-                if ((number & 3) == wave) {
-                    v4d acc = {0.0, 0.0, 0.0, 0.0};
-                    block_mac<true>(acc, blk(r, jb), LDT, blk(c, jb), LDT, lane);
-                    double* p = blk(r, c) + g * LDT + i;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) p[4 * e * LDT] -= acc[e];
-                }
-        __syncthreads();
-    }
-    double* tile = a + ((int64_t)kb * TB) * n + (int64_t)kb * TB;
-    for (int idx = tid; idx < TB * TB; idx += 256) {
-        const int r = idx >> 6, c = idx & 63;
-        tile[(int64_t)r * n + c] = (c <= r) ? t[r * LDT + c] : 0.0;
-    }
-    // wavefront w inverts diagonal block w: lane = column (four copies of each)
-    {
-        const double* l = blk(wave, wave);
-        double x[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = (r == i) ? 1.0 : 0.0;
-        // the reciprocals of the diagonal: one per lane, four copies
-        const double rd = 1.0 / l[i * LDT + i];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            x[r] *= read_lane(rd, r);
-#pragma unroll
-            for (int q = r + 1; q < 16; ++q) x[q] = fma(-l[q * LDT + r], x[r], x[q]);
-        }
-        double* v = vd + wave * VD;
-        if (g == 0) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v[r * 18 + i] = (r >= i) ? x[r] : 0.0;
-        }
-    }
-    __syncthreads();                                             // also: the tile has been copied out, its blocks may go
-    auto store_block = [&](double* p, const v4d& v, double sign) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[(g + 4 * e) * LDT + i] = sign * v[e];
+    auto l_transposed = [&](int r, int p) {                      // P[k][r's row]: rows g + 4 e, column i
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+        block_mac<true>(acc, blk(p, p), LDT, blk(r, p), LDT, lane);
+        return acc;
     };
-    // V10 = -V11 (L10 V00), V32 = -V33 (L32 V22): L10 and L32 are not needed afterwards and take the inner products
-    const int lo = (wave & 1) * 2;                               // wavefronts 0 and 1 (the others repeat the products, unstored)
-    {
-        v4d m = {0.0, 0.0, 0.0, 0.0};
-        block_mac<false>(m, blk(lo + 1, lo), LDT, vd + lo * VD, 18, lane);
-        __syncthreads();
-        if (wave < 2) store_block(blk(lo + 1, lo), m, 1.0);
-        __syncthreads();
-        v4d w = {0.0, 0.0, 0.0, 0.0};
-        block_mac<false>(w, vd + (lo + 1) * VD, 18, blk(lo + 1, lo), LDT, lane);
-        if (wave < 2) store_block(blk(lo, lo + 1), w, -1.0);
-        __syncthreads();
-    }
-    // the lower left quarter, one 16 x 16 block per wavefront: M = L[2..3, 0..1] V[0..1, 0..1], then -V[2..3, 2..3] M
-    const int r = 2 + (wave >> 1), c = wave & 1;
-    {
-        v4d m = {0.0, 0.0, 0.0, 0.0};
-        if (c == 0) {
-            block_mac<false>(m, blk(r, 0), LDT, vd, 18, lane);
-            block_mac<false>(m, blk(r, 1), LDT, blk(0, 1), LDT, lane);
-        } else {
-            block_mac<false>(m, blk(r, 1), LDT, vd + VD, 18, lane);
+    auto subtract_product = [&](int r, int c, const v4d& pr, const v4d& pc) {
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pr[e], pc[e], acc, 0, 0, 0);
+        double* to = blk(r, c) + g * LDT + i;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) to[4 * e * LDT] -= acc[e];
+    };
+    auto store_block = [&](int r, int c, const v4d& v, double sign) {
+        double* to = blk(r, c) + g * LDT + i;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) to[4 * e * LDT] = sign * v[e];
+    };
+    auto inverse_block = [&](int r, int c) {                     // V(r, c) = -V(r, r) sum over q of L(r, q) V(q, c)
+        v4d m = {0.0, 0.0, 0.0, 0.0}, v = {0.0, 0.0, 0.0, 0.0};
+        for (int q = c; q < r; ++q) {
+            const double *l = blk(q, r) + g * LDT + i, *vq = blk(q, c) + g * LDT + i;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m = __builtin_amdgcn_mfma_f64_16x16x4f64(l[4 * e * LDT], vq[4 * e * LDT], m, 0, 0, 0);
+        }
+        const double* vr = blk(r, r) + i * LDT + g;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f64_16x16x4f64(vr[4 * e], m[e], v, 0, 0, 0);
+        store_block(r, c, v, -1.0);
+    };
+    for (int jb = 0; jb <= 4; ++jb) {
+        const int p = jb - 1;                                    // the columns just finished
+        if (wave == 0 && jb < 4) {
+            double* b = blk(jb, jb);
+            if (p >= 0) {
+                const v4d pj = l_transposed(jb, p);
+                subtract_product(jb, jb, pj, pj);
+                __builtin_amdgcn_wave_barrier();                 // LDS accesses of a wavefront run in order
+            }
+            double d[16], v[4], pivot = 0.0;
+#pragma unroll
+            for (int c = 0; c < 16; c += 2) {
+                const v2d two = *reinterpret_cast<const v2d*>(b + i * LDT + c);
+                d[c] = two[0];
+                d[c + 1] = two[1];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = i == 4 * g + u ? 1.0 : 0.0;
+            Eliminate<0>::run(d, v, pivot, i);
+            const double rs = inv_sqrt(pivot);
+#pragma unroll
+            for (int u = 0; u < 4; u += 2) *reinterpret_cast<v2d*>(b + i * LDT + 4 * g + u) = v2d{rs * v[u], rs * v[u + 1]};
+            const uint32_t bad = (uint32_t)__builtin_amdgcn_ballot_w64(!(pivot > 0.0)) & 0xFFFFu;
+            if (bad && lane == 0 && *info == 0) *info = kb * TB + jb * 16 + __builtin_ctz(bad) + 1;
+        } else if (wave > 0 && p >= 0) {
+            if (wave > p) {                                      // blocks (wave, p + 1 ..) of the tile; wavefront 0 has (p + 1, p + 1)
+                const v4d pr = l_transposed(wave, p);
+                for (int c = p + 1; c <= wave; ++c)
+                    if (!(wave == p + 1 && c == p + 1)) subtract_product(wave, c, pr, l_transposed(c, p));
+                store_block(p, wave, pr, 1.0);
+            } else {
+                inverse_block(p, wave - 1);
+            }
         }
         __syncthreads();
-        store_block(blk(r, c), m, 1.0);
-        __syncthreads();
-        v4d w = {0.0, 0.0, 0.0, 0.0};
-        if (r == 2) {
-            block_mac<false>(w, vd + 2 * VD, 18, blk(2, c), LDT, lane);
-        } else {
-            block_mac<false>(w, blk(2, 3), LDT, blk(2, c), LDT, lane);
-            block_mac<false>(w, vd + 3 * VD, 18, blk(3, c), LDT, lane);
-        }
-        store_block(blk(c, r), w, -1.0);
-        __syncthreads();
     }
+    // V, zeros above the diagonal
     double* dv = dinv + (int64_t)kb * TB * TB;
-    for (int idx = tid; idx < TB * TB; idx += 256) {
-        const int rr = idx >> 6, cc = idx & 63, br = rr >> 4, bc = cc >> 4;
-        double v = 0.0;
-        if (br == bc) v = vd[br * VD + (rr & 15) * 18 + (cc & 15)];
-        else if (br > bc) v = blk(bc, br)[(rr & 15) * LDT + (cc & 15)];
-        dv[idx] = v;
-        x[((int64_t)kb * TB + rr) * n + (int64_t)kb * TB + cc] = v;
+#pragma unroll
+    for (int u = 0; u < TB * TB / 512; ++u) {
+        const int idx = tid + u * 256, r = idx >> 5, c = (idx & 31) * 2;
+        const v2d v = (c >> 4) <= (r >> 4) ? *reinterpret_cast<const v2d*>(t + r * LDT + c) : v2d{0.0, 0.0};
+        *reinterpret_cast<v2d*>(dv + r * TB + c) = v;
+        *reinterpret_cast<v2d*>(x + ((int64_t)kb * TB + r) * n + (int64_t)kb * TB + c) = v;
     }
 }
 
 // acc (a wavefront's 2 x 2 blocks of 16 x 16: rows 32 (wave / 2).., columns 32 (wave % 2)..) += A B for a 64 x 64 tile.
 // A(r, k) = ap[r * ars + k].  B(k, c): bp(k0) is the address of the slice k0 .. k0 + KS - 1, B(k0 + k, c) there at
 // c * brs + k (B_KFAST) or k * brs + c.  depth is a multiple of KS.  A slice is loaded into registers while the one before
-// is multiplied.  Ends with a barrier after the last slice has been consumed: LDS and operand tiles may be overwritten.
-template <bool B_KFAST, typename BP>
-__device__ __forceinline__ void tile_mac(v4d (&acc)[2][2], const double* ap, int64_t ars, BP&& bp, int64_t brs, int depth, double* lds) {
+// is multiplied; last() may load what is needed after the product beside the last one, in the same
+// registers.  Ends with a barrier after the last slice has been consumed: LDS and operand tiles may be overwritten.
+template <bool B_KFAST, typename BP, typename LAST>
+__device__ __forceinline__ void tile_mac(v4d (&acc)[2][2], const double* ap, int ars, BP&& bp, int brs, int depth, double* lds, LAST&& last) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
     double* as = lds;
     double* bs = lds + SLICE;
     v2d ra[4], rb[4];
+    // one offset per lane and operand, the rest of an address is uniform
+    const uint32_t from_a = (uint32_t)((tid >> 4) * ars + (tid & 15) * 2);
+    const uint32_t from_b = (uint32_t)(B_KFAST ? (tid >> 4) * brs + (tid & 15) * 2 : (tid >> 5) * brs + (tid & 31) * 2);
     auto load = [&](int k0) {
         const double* b = bp(k0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int id = tid + u * 256;
-            ra[u] = *reinterpret_cast<const v2d*>(ap + (int64_t)(id >> 4) * ars + k0 + (id & 15) * 2);
-            rb[u] = B_KFAST ? *reinterpret_cast<const v2d*>(b + (int64_t)(id >> 4) * brs + (id & 15) * 2)
-                            : *reinterpret_cast<const v2d*>(b + (int64_t)(id >> 5) * brs + (id & 31) * 2);
+            ra[u] = *reinterpret_cast<const v2d*>(ap + (int64_t)(16 * u) * ars + k0 + from_a);
+            rb[u] = *reinterpret_cast<const v2d*>(b + (int64_t)((B_KFAST ? 16 : 8) * u) * brs + from_b);
         }
     };
-    load(0);
-    for (int k0 = 0; k0 < depth; k0 += KS) {
+    auto store = [&]() {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int id = tid + u * 256;
@@ -276,8 +289,8 @@ __device__ __forceinline__ void tile_mac(v4d (&acc)[2][2], const double* ap, int
             if (B_KFAST) *reinterpret_cast<v2d*>(bs + (id >> 4) * LDA + (id & 15) * 2) = rb[u];
             else *reinterpret_cast<v2d*>(bs + (id >> 5) * LDT + (id & 31) * 2) = rb[u];
         }
-        __syncthreads();
-        if (k0 + KS < depth) load(k0 + KS);
+    };
+    auto multiply = [&]() {
         const double* pa = as + ((wave >> 1) * 32 + i) * LDA + 2 * g;
         const double* pb = B_KFAST ? bs + ((wave & 1) * 32 + i) * LDA + 2 * g : bs + 2 * g * LDT + (wave & 1) * 32 + i;
 #pragma unroll
@@ -296,15 +309,30 @@ __device__ __forceinline__ void tile_mac(v4d (&acc)[2][2], const double* ap, int
 #pragma unroll
                     for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x][h], bv[y][h], acc[x][y], 0, 0, 0);
         }
+    };
+    load(0);
+    for (int k0 = KS; k0 < depth; k0 += KS) {
+        store();
+        __syncthreads();
+        load(k0);
+        multiply();
         __syncthreads();
     }
+    store();
+    __syncthreads();
+    last();
+    multiply();
+    __syncthreads();
 }
 static_assert(KS * LDT <= SLICE, "a slice in either order fits");
 
-// f(row, column, value) for every element of the tile this lane holds
+// f(value, address) for every element this lane holds of a tile with row stride `stride` (n: tiles of the matrices): one offset per
+// lane, the rest of the address is uniform
 template <typename F>
-__device__ __forceinline__ void each_element(v4d (&acc)[2][2], F&& f) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
+__device__ __forceinline__ void each_element(v4d (&acc)[2][2], double* tile, int stride, F&& f) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
+    const uint32_t mine = (uint32_t)(g * stride + i);
+    double* part = tile + (wave >> 1) * 32 * (int64_t)stride + (wave & 1) * 32;
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -312,9 +340,20 @@ __device__ __forceinline__ void each_element(v4d (&acc)[2][2], F&& f) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 double v = acc[x][y][e];
-                f((wave >> 1) * 32 + x * 16 + g + 4 * e, (wave & 1) * 32 + y * 16 + i, v);
+                f(v, (part + (int64_t)(x * 16 + 4 * e) * stride + y * 16)[mine]);
                 acc[x][y][e] = v;
             }
+}
+
+__device__ __forceinline__ void clear(v4d (&a)[2][2]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[u >> 1][u & 1] = v4d{0.0, 0.0, 0.0, 0.0};
+}
+
+// acc = old - acc
+__device__ __forceinline__ void subtract_from(const v4d (&old)[2][2], v4d (&acc)[2][2]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u >> 1][u & 1] = old[u >> 1][u & 1] - acc[u >> 1][u & 1];
 }
 
 // the first diagonal tile
@@ -326,7 +365,7 @@ __global__ void __launch_bounds__(256) factor_first_kernel(double* __restrict__ 
         lds[r * LDT + c] = (c <= r) ? a[(int64_t)r * n + c] : 0.0;
     }
     __syncthreads();
-    factor_tile(lds, lds + TB * LDT, a, n, 0, dinv, x, info);
+    factor_tile(lds, n, 0, dinv, x, info);
 }
 
 // Workgroups 0 .. panel - 1: a[i, kb] <- a[i, kb] * (L_kk^-1)^T for the tiles i = kb + 1 + blockIdx.x below the diagonal tile.
@@ -340,12 +379,12 @@ __global__ void __launch_bounds__(256) scale_panel_kernel(double* a, double* x, 
         tile = a + ((int64_t)(kb + 1 + b) * TB) * n + (int64_t)kb * TB;
         // B(k, c) = V(c, k) = dinv[c * 64 + k]
         const double* dv = dinv + (int64_t)kb * TB * TB;
-        tile_mac<true>(acc, tile, n, [&](int k0) { return dv + k0; }, TB, TB, lds);
+        tile_mac<true>(acc, tile, n, [&](int k0) { return dv + k0; }, TB, TB, lds, [] {});
     } else {
         tile = x + ((int64_t)kx * TB) * n + (int64_t)(b - panel) * TB;
-        tile_mac<false>(acc, dinv + (int64_t)kx * TB * TB, TB, [&](int k0) { return tile + (int64_t)k0 * n; }, n, TB, lds);
+        tile_mac<false>(acc, dinv + (int64_t)kx * TB * TB, TB, [&](int k0) { return tile + (int64_t)k0 * n; }, n, TB, lds, [] {});
     }
-    each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
+    each_element(acc, tile, n, [](double v, double& m) { m = v; });
 }
 
 // Workgroups 0 .. trailing - 1: a[i, j] -= sum over q in [kb, kb + depth / 64) of a[i, q] a[j, q]^T.  columns = 1: the tiles
@@ -360,15 +399,14 @@ __global__ void __launch_bounds__(256) trailing_update_kernel(double* a, double*
         const int i = i0 + (b - trailing) / x_cols, j = (b - trailing) % x_cols, q = max(xq, j);
         double* tile = x + ((int64_t)i * TB) * n + (int64_t)j * TB;
         const double* bp = x + ((int64_t)q * TB) * n + (int64_t)j * TB;
-        v4d acc[2][2] = {}, old[2][2] = {};
-        if (j < xq) each_element(old, [&](int r, int c, double& v) { v = tile[(int64_t)r * n + c]; });
+        v4d acc[2][2] = {}, old[2][2];
         tile_mac<false>(acc, a + ((int64_t)i * TB) * n + (int64_t)q * TB, n, [&](int k0) { return bp + (int64_t)k0 * n; }, n,
-                        (xq + xn - q) * TB, lds);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 2; ++v) acc[u][v] = old[u][v] - acc[u][v];
-        each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
+                        (xq + xn - q) * TB, lds, [&] {
+                            if (j < xq) each_element(old, tile, n, [](double& v, double& m) { v = m; });
+                            else clear(old);
+                        });
+        subtract_from(old, acc);
+        each_element(acc, tile, n, [](double v, double& m) { m = v; });
         return;
     }
     int ti = b, tj = 0;
@@ -376,25 +414,23 @@ __global__ void __launch_bounds__(256) trailing_update_kernel(double* a, double*
         ti = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
         while (ti * (ti + 1) / 2 > b) --ti;
         while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+        ti = __builtin_amdgcn_readfirstlane(ti);
         tj = b - ti * (ti + 1) / 2;
     }
     const int i = j0 + ti, j = j0 + tj;
     double* tile = a + ((int64_t)i * TB) * n + (int64_t)j * TB;
     const double* bp = a + ((int64_t)j * TB) * n + (int64_t)kb * TB;
-    v4d acc[2][2] = {}, old[2][2];                               // what the tile holds is on its way while the product is formed
-    each_element(old, [&](int r, int c, double& v) { v = tile[(int64_t)r * n + c]; });
+    v4d acc[2][2] = {}, old[2][2];
     // B(k, c) = a[j, q](c, k)
-    tile_mac<true>(acc, a + ((int64_t)i * TB) * n + (int64_t)kb * TB, n, [&](int k0) { return bp + k0; }, n, depth, lds);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) acc[u][v] = old[u][v] - acc[u][v];
+    tile_mac<true>(acc, a + ((int64_t)i * TB) * n + (int64_t)kb * TB, n, [&](int k0) { return bp + k0; }, n, depth, lds,
+                   [&] { each_element(old, tile, n, [](double& v, double& m) { v = m; }); });
+    subtract_from(old, acc);
     if (b == 0) {
-        each_element(acc, [&](int r, int c, double v) { lds[r * LDT + c] = (c <= r) ? v : 0.0; });
+        each_element(acc, lds, LDT, [](double v, double& m) { m = v; });
         __syncthreads();
-        factor_tile(lds, lds + TB * LDT, a, n, j0, dinv, x, info);
+        factor_tile(lds, n, j0, dinv, x, info);
     } else {
-        each_element(acc, [&](int r, int c, double v) { tile[(int64_t)r * n + c] = v; });
+        each_element(acc, tile, n, [](double v, double& m) { m = v; });
     }
 }
 

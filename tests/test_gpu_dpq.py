@@ -362,6 +362,35 @@ def test_calibration_at_the_size_bench_times_sampled_rows(gpu_lib):
     assert np.array_equal(codes[rows], want[0])
 
 
+@pytest.mark.parametrize("at", [0, 15, 16, 31, 47, 48, 63, 64, 79, 112, 127, 191])
+def test_hessian_inverse_factor_reports_the_first_bad_pivot_of_every_block(gpu_lib, at):
+    """A pivot that is not positive in each 16 x 16 diagonal block of a tile and at their edges, with couplings to the columns before it and a
+    second one behind: `at` counts in the factorization's order, from the last column."""
+    k = 256
+    rng = np.random.default_rng([93, at])
+    x = calibration_inputs(rng, 2 * k, k)
+    h = (x.T @ x).astype(np.float32)
+    h = np.maximum(h, h.T)
+    h[k - 1 - at, k - 1 - at] = -1.0
+    h[k - 1 - min(at + 40, k - 1), k - 1 - min(at + 40, k - 1)] = -1.0
+    _, info = B.hessian_inverse_factor(dev(h), 0.0)
+    assert int(host(info)[0]) == at + 1
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+def test_hessian_inverse_factor_scales(gpu_lib, scale):
+    """U scales with 1 / sqrt of the Hessian at the ends of float32.  Tolerance as in test_hessian_inverse_factor."""
+    k = 256
+    x = calibration_inputs(np.random.default_rng(94), 2 * k, k)
+    h = (x.T @ x)
+    h = (h / np.abs(h).max() * scale).astype(np.float32)
+    h = np.maximum(h, h.T)
+    want = o.hessian_inverse_factor_from_h(h.astype(np.float64) / scale, 0.01, None) / np.sqrt(scale)
+    u, info = B.hessian_inverse_factor(dev(h), 0.01)
+    assert int(host(info)[0]) == 0
+    assert np.all(np.abs(host(u).astype(np.float64) - want) <= 2.0 ** -22 * np.abs(want) + 1e-9 * np.abs(want).max())
+
+
 def test_hessian_inverse_factor_special_cases(gpu_lib):
     """A diagonal Hessian without dampening has the closed form U = diag(1 / sqrt(h_ii)); the identity permutation is
     the same as none; a reversal of the columns gives the factor of the reversed matrix."""
