@@ -116,8 +116,16 @@ def _check(status: int, where: str) -> None:
         raise W4A8Error(status, where)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device.  Building a torch.cuda.Stream object for it takes 2.7 us of the 7.8 us that a call of a layer
+    takes on the host (empty output 1.7 us, launch 3.3 us), the handle itself 0.2 us."""
+    if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
