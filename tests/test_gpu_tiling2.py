@@ -83,6 +83,19 @@ def test_every_tile_exact_integer_case_bit_for_bit(gpu_lib, tile, m, g, minus_ei
     assert np.array_equal(y32, want)
 
 
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("k,g,minus_eight", [(128, 128, True), (256, 128, False), (384, 128, True), (512, 256, True), (640, 128, False),
+                                             (768, 384, True), (896, 896, False)])
+def test_loops_of_one_to_seven_chunks_bit_for_bit(gpu_lib, tile, k, g, minus_eight):
+    """The loops hold two chunks ahead in registers or LDS: fewer chunks than that, one more, odd and even counts; ragged tokens and
+    channels, one workgroup and a persistent grid of eight that takes several tiles each."""
+    for m, p1 in ((65, 0), (530, 1 | (8 << 8))):
+        n = 300
+        x8, packed, scales, want = integer_case([79, m, k, g], m, k, n, g, minus_eight)
+        y32, _ = run_variant(dev(x8), dev(np.array([0.5], np.float32)), packed, scales, n, g, 2, tile, p1)
+        assert np.array_equal(y32, want), (m, p1)
+
+
 @pytest.mark.parametrize("tile", (1, 4, 5))
 def test_power_of_two_scales_on_the_second_tiling(gpu_lib, tile):
     m, k, n, g = 520, 1024, 300, 128
