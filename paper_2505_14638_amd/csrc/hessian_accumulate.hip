@@ -13,11 +13,11 @@
 //     chain this replaces 3.8e-6.
 //   - float32 activations: 32x32x2 float32 MFMA, which takes its two products in order, each one a correctly rounded
 //     FMA -- the same chain per element, and the same bits, as a scalar loop over the tokens.
-// Measured at 8192 tokens x 4096 features, against 64 x 64 tiles of scalar FMAs over both triangles: bf16 4190 -> 355 us
+// Measured at 8192 tokens x 4096 features, against 64 x 64 tiles of scalar FMAs over both triangles: bf16 4190 -> 292 us
 // (LDS reads of the operands bound it: two 16-byte reads per MFMA pair), float32 4040 -> 1410 us (the float32 matrix
 // unit's rate, 153 TFLOP/s measured, takes 900).  The finer tiles even out the load where there are few: a launch is done
 // when the compute unit with the most tiles is.  bf16 takes 128 x 128 tiles from 400 of them on (276 of them at 2944
-// features 279 us, where 64 x 64 take about 220; 528 of them at 4096 features 339 us, 64 x 64 about 430), float32 always 64 x 64.
+// features 279 us, where 64 x 64 take about 220; 528 of them at 4096 features 339 us, now 292, 64 x 64 about 430), float32 always 64 x 64.
 // On few tokens reading and writing H is most of the time, which the finer tiles spread better: up to 512 tokens 64 x 64 (128 x
 // 128 / 64 x 64 tiles: 16 tokens x 5120 features 69 / 39 us, 512 tokens 92 / 64, 4096 features 54 / 48, 14336 features 696 / 637);
 // rows that are not aligned for 4-byte loads up to 32 tokens only (32 tokens x 4096 features 42 / 41, 64 tokens 46 / 47).
@@ -32,7 +32,12 @@ namespace {
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-// How one thread brings its share of a slice from global memory to LDS, per input type.
+// How one thread brings its share of a slice from global memory to LDS, per input type.  load() takes any slice, with zeros for what is
+// past the ends.  load_whole() (bf16, 128 x 128 tiles, aligned rows) takes a slice of existing tokens with one offset per lane (place())
+// on top of a uniform row address, so that a load is one instruction; features past the end repeat the last ones, whose products belong
+// to no element of H.  Range checks and 64-bit addresses for every load kept the vector unit busier than the matrix unit: 8192 tokens x
+// 4096 features 351 -> 292 us, x 14336 features 3.06 -> 2.55 ms.  64 x 64 tiles, which run where tokens are few, gain 4 % by it on many
+// tokens and lose 3 to 7 % on few; float32 ones are bound by the matrix unit.
 template <typename InT, int TILE> struct Slice;
 
 template <int TILE> struct Slice<float, TILE> {
@@ -93,6 +98,21 @@ template <int TILE> struct Slice<uint16_t, TILE> {
     static constexpr int SPLIT = UNITS == 0 ? 2 : 1;             // 64 x 64 tiles: half of the threads per operand
     static constexpr int REGS = UNITS == 0 ? 1 : UNITS;
     uint32_t r[REGS][8];
+    uint32_t at[REGS];
+    __device__ __forceinline__ void place(int64_t K, int64_t ldx, int64_t f0, int tid) {
+#pragma unroll
+        for (int u = 0; u < REGS; ++u) {
+            const int id = (tid & (256 / SPLIT - 1)) + u * 256, o = id / (TILE / 2), f = (id % (TILE / 2)) * 2;
+            at[u] = (uint32_t)(o * 8 * ldx + min((int64_t)f, K - 2 - f0));
+        }
+    }
+    // the slice that begins at the uniform address p (feature f0 of its first token)
+    __device__ __forceinline__ void load_whole(const uint16_t* p, int64_t ldx) {
+#pragma unroll
+        for (int u = 0; u < REGS; ++u)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) r[u][t] = *reinterpret_cast<const uint32_t*>(p + t * ldx + at[u]);
+    }
     template <bool VEC>
     __device__ __forceinline__ void load(const uint16_t* x, int64_t T, int64_t K, int64_t ldx, int64_t t0, int64_t f0, int tid) {
 #pragma unroll
@@ -146,8 +166,11 @@ template <int TILE> struct Slice<uint16_t, TILE> {
     }
 };
 
+constexpr int64_t MAX_LDX = int64_t(1) << 24;   // 32 rows of it below 2^32 bytes
+
+// 128 x 128 tiles: three workgroups to a compute unit, so that the 528 tiles of 4096 features run at the same time
 template <typename InT, int TILE, bool VEC>
-__global__ void __launch_bounds__(256) hessian_accumulate_kernel(const InT* __restrict__ x, int64_t T, int64_t K, int64_t ldx,
+__global__ void __launch_bounds__(256, TILE == 128 ? 3 : 1) hessian_accumulate_kernel(const InT* __restrict__ x, int64_t T, int64_t K, int64_t ldx,
                                                                  float* __restrict__ h, int h_vec) {
     using S = Slice<InT, TILE>;
     constexpr int NB = TILE / 64;                                // 32 x 32 blocks of a wavefront in each direction
@@ -171,7 +194,22 @@ __global__ void __launch_bounds__(256) hessian_accumulate_kernel(const InT* __re
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     S sa, sb;
+    constexpr bool WHOLE = sizeof(InT) == 2 && TILE == 128 && VEC;
+    const bool near = WHOLE && ldx <= MAX_LDX;                   // offsets inside a slice fit 32 bits
+    if constexpr (WHOLE) {
+        if (near) {
+            sa.place(K, ldx, i0, tid);
+            sb.place(K, ldx, j0, tid);
+        }
+    }
     auto load = [&](int64_t t0) {
+        if constexpr (WHOLE) {
+            if (near && t0 + S::TOKENS <= T) {
+                sa.load_whole(x + t0 * ldx + i0, ldx);
+                sb.load_whole(x + t0 * ldx + j0, ldx);
+                return;
+            }
+        }
         if (HALVES) {
             sa.template load<VEC>(x, T, K, ldx, t0, tid < 128 ? i0 : j0, tid);
         } else {

@@ -234,6 +234,13 @@ def test_hessian_accumulate_tile_edges(gpu_lib, t, k, dtype):
     assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("t", [544, 545, 575])
+def test_hessian_accumulate_whole_slices_and_a_tail(gpu_lib, t):
+    """128 x 128 tiles with features past the end in the last ones, whole slices of 32 tokens and none, one or 31 left over; inputs, strides and
+    tolerance of test_hessian_accumulate_tile_edges."""
+    test_hessian_accumulate_tile_edges(gpu_lib, t, 3466, "bf16")
+
+
 @pytest.mark.parametrize("t,k", [(50, 70), (3, 128)])
 def test_hessian_accumulate_float32_is_a_chain_of_fmas(gpu_lib, t, k):
     """float32 activations: every entry is the bits of one FMA per token, in their order.  Integers below 2^15: a product and
