@@ -24,8 +24,7 @@ extern "C" {
  *           per wavefront (1 or 2; 0 = chosen): the workgroup covers 128 * bands / groups channels.  Built shapes
  *           (blocks, groups, bands): (16,1,1) (8,1,1) (8,2,1) (4,1,1) (4,2,1) (4,4,1) (16,1,2)
  *           path 2: param0 = workgroup tile, 0: 512 x 128, 1: 256 x 256, 2: 256 x 128, 3: 128 x 256, 5: 128 x 128 tokens x
- *           channels (eight wavefronts), 4: 256 x 128 with four wavefronts (two workgroups per compute unit); 1 is 512 x 128 for
- *           code-exact weights where the sizes need no more of those;
+ *           channels (eight wavefronts), 4: 256 x 128 with four wavefronts (two workgroups per compute unit);
  *           param1 = token blocks per super-column of the tile order (0 = chosen) plus 256 * workgroups (0 = chosen)
  * Unsupported combinations return W4A8_ERR_SHAPE.
  */

@@ -71,7 +71,7 @@ constexpr TileTimes ASYM_TIMES = {{6.26, 1.46, 0.324}, {8.41, 1.7, 0.258}, {7.3,
 constexpr TileTimes ASYM_TWO_TIMES = {{5.76, 1.29, 0.3}, {6.98, 1.48, 0.291}, {5.63, 0.866, 0.0763}, {7.55, 1.2, 7.47, 1.76, 0.612},
     {{8.95, 1.3, 1.08, 0.687}, {8.22, 0.906, 0.227, 0.516}, {6.96, 0.76, 0.608, 0.469}, {5.85, 0.764, 0.193, 0.412}, {6.46, 0.666, 0.273, 0.357}, {6.27, 0.52, 0.673, 0.403}}};
 
-// Tile 1 of the second tiling: 256 x 256, but 512 x 128 for the code-exact format where the grid needs no more of those.  A
+// 512 x 128 tiles in place of 256 x 256 ones: for the code-exact format where the grid needs no more of them.  A
 // 512 x 128 tile expands half as many bands per MFMA, which that format's FMAs leave no room for (8192 tokens of 4096 -> 28672:
 // 840 us against 858); with power-of-two scales the expansion has room beside the MFMAs and the square's smaller panels win (779 / 764).
 inline bool mfma2d_tall_instead(int64_t M, int64_t N, int mode) {
@@ -158,11 +158,11 @@ inline bool choose_many_token_launch(int64_t M, int64_t K, int64_t N, int mode, 
     tpw = cand[shape][2];
     double& best = microseconds;
     best = PREFER_FIRST * first_cost(shape);
-    // by tile: 512 x 128 for the formats whose expansion is the longer one; 256 x 256, or what stands for it; 256 x 128 with eight
-    // wavefronts and with four
-    const bool plain = mode == MODE_CODE_EXACT || mode == MODE_POW2;
-    const double e[5] = {plain ? INFINITY : t.tall.cost(tiles(512, 128), c),
-                         mfma2d_tall_instead(M, N, mode) ? t.tall.cost(tiles(512, 128), c) : t.square.cost(tiles(256, 256), c),
+    // by tile: 512 x 128 for the formats whose expansion is the longer one, and where it stands for 256 x 256; 256 x 256; 256 x 128
+    // with eight wavefronts and with four
+    const bool plain = mode == MODE_CODE_EXACT || mode == MODE_POW2, tall_instead = mfma2d_tall_instead(M, N, mode);
+    const double e[5] = {plain && !tall_instead ? INFINITY : t.tall.cost(tiles(512, 128), c),
+                         tall_instead ? INFINITY : t.square.cost(tiles(256, 256), c),
                          t.half.cost(tiles(256, 128), c), INFINITY, t.pair.cost(tiles(256, 128), c)};
     for (int q = 0; q < 5; ++q) {
         if (e[q] < best) {

@@ -145,7 +145,7 @@ def test_linear_validation(L):
     assert fn(P, 512, 28672, 28672, P, P, P, 8192, 128, P, B.BF16, 8192, None) == 7
     # the launch shape the library chooses, as w4a8_linear_variant takes it
     assert B.linear_launch_shape(1, 4096, 4096, 128) == (0, 1, 16 | (2 << 8), 0)
-    assert B.linear_launch_shape(8192, 4096, 4096, 128) == (2, 1, 0, 0) and B.linear_launch_shape(2048, 4096, 4096, 128) == (2, 2, 0, 0) and B.linear_launch_shape(3072, 4096, 6144, 128) == (2, 4, 0, 0)
+    assert B.linear_launch_shape(8192, 4096, 4096, 128) == (2, 0, 0, 0) and B.linear_launch_shape(2048, 4096, 4096, 128) == (2, 2, 0, 0) and B.linear_launch_shape(3072, 4096, 6144, 128) == (2, 4, 0, 0)
     assert B.linear_launch_shape(512, 4096, 4096, 128)[0] == 1
     assert B.linear_launch_shape(128, 14336, 4096, 128, True) == (3, 5, 0, 8) and B.linear_launch_shape(128, 14336, 4096, 128)[0] == 1
     assert L.w4a8_linear_launch_shape(128, 14336, 4096, 128, 0, None) == 1 and L.w4a8_linear_launch_shape(0, 14336, 4096, 128, 0, P) == 2
@@ -337,7 +337,10 @@ def test_launch_shapes_of_every_format(L):
                     plain = B.linear_launch_shape(m, k, n, 128)
                     assert ranges == 0 and (path == 0) == (plain[0] == 0) and path in (0, 1, 2)
                     assert path != 1 or (p0, p1 & 0xFF, p1 >> 8) in first_tiling
-                    assert path != 2 or p0 in ((0, 1, 2, 4) if fmt in ("two_level", "asym", "asym_two_level") else (1, 2, 4))
+                    assert path != 2 or p0 in ((0, 1, 2, 4) if fmt != "pow2" else (1, 2, 4))
+                    if fmt == "code_exact" and path == 2 and p0 < 2:            # 512 x 128 where the grid needs no more of them than of 256 x 256
+                        tall, square = -(-m // 512) * -(-n // 128), -(-m // 256) * -(-n // 256)
+                        assert p0 == (0 if tall <= square else 1)
                     assert fmt != "code_exact" or (path, p0, p1, ranges) == plain
     assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, 5, P) == 4
     assert L.w4a8_linear_format_launch_shape(64, 128, 128, 128, -1, P) == 4
