@@ -4,8 +4,9 @@
 //     chunk after that are expanded and published, and the activations, scales and nibbles of later ones are on their way;
 //   - everything from global memory goes to LDS (three activation stages, three slots each of nibbles, scales and records per
 //     wavefront), so that one counted wait per chunk -- all copies but the ones issued in this chunk -- gives each of them at
-//     least a whole chunk to arrive.  A wavefront issues the same number of copies in every chunk; behind the end of K they are copies of no
-//     lanes, which cost no traffic and keep the count.
+//     least a whole chunk to arrive.  A wavefront issues the same number of copies in every chunk.  The last chunks, whose copies would lie
+//     behind the end of K, run in a loop of their own: there those are copies of no lanes, which cost no traffic, and the count leaves
+//     them out (pipe_copies.hpp).
 // The copies are spread over the steps of a chunk: eight wavefronts that issue several at once wait for each other's at the one
 // vector memory path of the compute unit, with their MFMAs behind them (two at a time 86 us where one at a time takes 69).
 // Measured against the loop with operands read at the head of a chunk and one wait for everything at its end, microseconds: 512 tokens of
@@ -16,11 +17,13 @@
 // through its steps in 1300 cycles, the younger one beside it in 1700.
 // With -8 in every group the two-level format takes 3 ... 10 % longer than on the loop this replaces (the operand is formed twice).
 #include "linear_epilogue.hpp"
+#include "pipe_copies.hpp"
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
 #include <math.h>
 
+#include <type_traits>
 #include <utility>
 
 namespace w4a8 {
@@ -40,7 +43,13 @@ __device__ __forceinline__ uint64_t lanes_if(int left) {
     asm("s_cmp_gt_i32 %1, 0\n\ts_cselect_b64 %0, -1, 0" : "=s"(m) : "s"(left) : "scc");
     return m;
 }
-// lds_dma_16 / lds_dma_4 for `lanes`; a copy of no lanes counts as one that has landed.  OFFSET counts in LDS and in memory.
+// lds_dma_16 / lds_dma_4 for all lanes or for `lanes`, possibly none.  OFFSET counts in LDS and in memory.
+template <int OFFSET> __device__ __forceinline__ void lds_dma_16_at(const uint8_t* base, uint32_t offset, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                 :
+                 : "v"(offset), "s"(base), "s"(lds_addr), "i"(OFFSET)
+                 : "memory", "m0");
+}
 template <int OFFSET> __device__ __forceinline__ void lds_dma_16_lanes(uint64_t lanes, const uint8_t* base, uint32_t offset, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4\n\ts_mov_b64 exec, -1"
                  :
@@ -54,10 +63,23 @@ __device__ __forceinline__ void lds_dma_4_lanes(uint64_t lanes, const uint8_t* b
                  : "memory", "m0");
 }
 
+struct All {};                       // in the place of a mask: all lanes
+
 // s_waitcnt vmcnt(N) lgkmcnt(0), known to the compiler
 template <int N> __device__ __forceinline__ void wait_copies_but() {
     static_assert(N < 64, "six bits");
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
+}
+// ... for all copies but those of a chunk that ends, one of the last.  One statement: branches of the compiler's own cost registers.
+template <int NEAR, int FAR> __device__ __forceinline__ void wait_older_copies(int left) {
+    constexpr int SOME = copies_that_may_be_left(NEAR, FAR, 4);
+    static_assert(copies_that_may_be_left(NEAR, FAR, 3) == 0, "the last one below");
+    wait_copies_but<copies_that_may_be_left(NEAR, FAR, 5)>();
+    asm volatile("s_cmp_gt_i32 %0, 4\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(%1)\n\ts_cmp_gt_i32 %0, 3\n\ts_cbranch_scc1 1f\n\t"
+                 "s_waitcnt vmcnt(0)\n1:"
+                 :
+                 : "s"(left), "i"(SOME)
+                 : "memory", "scc");
 }
 
 template <typename OutT, int WGM, int WGN, int WM, int WN, int MODE>
@@ -84,7 +106,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
     constexpr int LDS_BYTES = EC + 3 * EC_SLOT;
     static_assert(LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
     constexpr int DPW = BM / (8 * WAVES);                        // 1 KiB activation pages a wavefront copies per chunk
-    constexpr int COPIES = DPW + 1 + (NEED_S ? 1 : 0) + (NEED_E ? 1 : 0);   // copies a wavefront issues per chunk
+    constexpr int NEAR = DPW + (NEED_S ? 1 : 0), FAR = 1 + (NEED_E ? 1 : 0);   // copies a wavefront issues per chunk
+    constexpr int COPIES = NEAR + FAR;
     constexpr int STEPS = WM * WN;                               // MFMAs per chunk and wavefront
     constexpr int E_FIRST = WN == 2 ? 1 : 2, E_LAST = STEPS - 3;               // steps E_FIRST .. E_LAST share the expansion
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
@@ -140,21 +163,27 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
 
     auto stage_a = [](int s) { return s * A_STAGE + (s == 2 ? B_STAGE : 0); };
     // copies of chunk c, by `lanes`: page q of the activations to the stage at `at`, the scales and the nibbles and records to slot s
-    auto copy_page = [&](int c, int at, auto Q, uint64_t lanes) {
+    auto copy_page = [&](int c, int at, auto Q, auto lanes) {
         constexpr int q = decltype(Q)::value;
-        lds_dma_16_lanes<q * 1024>(lanes, xrow0 + (int64_t)c * 128, xoff[q], lds0 + (uint32_t)at + (uint32_t)(wave * DPW) * 1024);
+        if constexpr (std::is_same_v<decltype(lanes), All>) lds_dma_16_at<q * 1024>(xrow0 + (int64_t)c * 128, xoff[q], lds0 + (uint32_t)at + (uint32_t)(wave * DPW) * 1024);
+        else lds_dma_16_lanes<q * 1024>(lanes, xrow0 + (int64_t)c * 128, xoff[q], lds0 + (uint32_t)at + (uint32_t)(wave * DPW) * 1024);
     };
-    auto copy_all_pages = [&](int c, int at, uint64_t lanes) {
+    auto copy_all_pages = [&](int c, int at, auto lanes) {
         static_for(std::make_integer_sequence<int, DPW>{}, [&](auto Q) { copy_page(c, at, Q, lanes); });
     };
-    auto copy_scales = [&](int g, int s, uint64_t lanes) {
-        if constexpr (NEED_S) lds_dma_4_lanes(lanes, sbytes + (int64_t)g * REC, soff, lds0 + SC + (uint32_t)(s * SC_SLOT + wave * 256));
+    auto copy_scales = [&](int g, int s, auto lanes) {
+        if constexpr (NEED_S && std::is_same_v<decltype(lanes), All>) lds_dma_4(sbytes + (int64_t)g * REC, soff, lds0 + SC + (uint32_t)(s * SC_SLOT + wave * 256));
+        else if constexpr (NEED_S) lds_dma_4_lanes(lanes, sbytes + (int64_t)g * REC, soff, lds0 + SC + (uint32_t)(s * SC_SLOT + wave * 256));
     };
-    auto copy_raw = [&](int c, int s, uint64_t lanes) {
-        lds_dma_16_lanes<0>(lanes, packed + (int64_t)c * 1024, eoff, lds0 + RAW + (uint32_t)(s * RAW_SLOT + wave * 1024));
+    auto copy_raw = [&](int c, int s, auto lanes) {
+        if constexpr (std::is_same_v<decltype(lanes), All>) lds_dma_16_at<0>(packed + (int64_t)c * 1024, eoff, lds0 + RAW + (uint32_t)(s * RAW_SLOT + wave * 1024));
+        else lds_dma_16_lanes<0>(lanes, packed + (int64_t)c * 1024, eoff, lds0 + RAW + (uint32_t)(s * RAW_SLOT + wave * 1024));
     };
-    auto copy_record = [&](int g, int s, uint64_t lanes) {
-        if constexpr (NEED_E) lds_dma_4_lanes(lanes & ((1ull << (REC / 4)) - 1), sbytes + (int64_t)g * REC, roff, lds0 + EC + (uint32_t)(s * EC_SLOT + wave * REC));
+    auto copy_record = [&](int g, int s, auto lanes) {
+        constexpr uint64_t record = (1ull << (REC / 4)) - 1;
+        uint64_t some = record;
+        if constexpr (!std::is_same_v<decltype(lanes), All>) some &= lanes;
+        if constexpr (NEED_E) lds_dma_4_lanes(some, sbytes + (int64_t)g * REC, roff, lds0 + EC + (uint32_t)(s * EC_SLOT + wave * REC));
     };
     auto publish = [&](int stage, int h, uint32_t a, uint32_t b, uint32_t c2, uint32_t d) {
         *reinterpret_cast<uint4*>(lds + (stage ? B1 : B0) + (wn * WN + wm) * 2048 + h * 1024 + lane * 16) = make_uint4(a, b, c2, d);
@@ -201,9 +230,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
     int g3 = 0, left3 = 0;                                       // group of chunk c + 3, and its chunks from c + 3 on
 
     // Multiplies chunk c (in cur) and meanwhile reads chunk c + 1 into nxt, expands the nibbles of chunk c + 2 into the stage that chunk c was
-    // read from, and copies the activations and scales of chunk c + 3 and the nibbles of chunk c + 4.  PAR: parity of c - c_begin.
-    auto chunk = [&](int c, Ops& cur, Ops& nxt, auto PAR) {
+    // read from, and copies the activations and scales of chunk c + 3 and the nibbles of chunk c + 4.  PAR: parity of c - c_begin.  LAST: in the
+    // loop of the last four chunks (with a fifth or sixth where their number asks for it).
+    auto chunk = [&](int c, Ops& cur, Ops& nxt, auto PAR, auto LAST) {
         constexpr int par = decltype(PAR)::value;
+        constexpr bool last = decltype(LAST)::value;
         const int at1 = stage_a(s1), at0 = stage_a(s0);
         u32x4 raw = *reinterpret_cast<const u32x4*>(lds + RAW + s2 * RAW_SLOT + wave * 1024 + lane * 16);
         float es = 0.0f;
@@ -224,7 +255,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
                 }
             }
         }
-        const uint64_t lanes_a = lanes_if(c_end - c - 3), lanes_w = lanes_if(c_end - c - 4);
+        using Lanes = std::conditional_t<last, uint64_t, All>;
+        Lanes lanes_a, lanes_w;
+        if constexpr (last) {
+            lanes_a = lanes_if(c_end - c - 3);
+            lanes_w = lanes_if(c_end - c - 4);
+        }
         const int g4 = left3 > 1 ? g3 : g3 + 1;
         MagTable tab = {0u, 0u, 0u};
         AsymTable atab = {{0u, 0u, 0u, 0u}};
@@ -291,7 +327,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
         s2 = t;
         left3 = left3 > 1 ? left3 - 1 : cpg;
         g3 = g4;
-        wait_copies_but<COPIES>();                               // all but this chunk's copies have landed, reads and writes are done
+        if (last) wait_older_copies<NEAR, FAR>(c_end - c);       // all but this chunk's copies have landed, reads and writes are done
+        else wait_copies_but<COPIES>();
         __syncthreads();
     };
 
@@ -313,8 +350,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
             ez0 = sbytes[(int64_t)(c_begin / cpg) * REC + rbase + 64 + i];
             ez1 = sbytes[(int64_t)(c1 / cpg) * REC + rbase + 64 + i];
         }
-        copy_all_pages(c_begin, stage_a(0), ~0ull);
-        copy_scales(c_begin / cpg, 0, ~0ull);
+        copy_all_pages(c_begin, stage_a(0), All{});
+        copy_scales(c_begin / cpg, 0, All{});
         const uint64_t lanes1 = lanes_if(c_end - c_begin - 1), lanes2 = lanes_if(c_end - c_begin - 2);
         copy_all_pages(c_begin + 1, stage_a(1), lanes1);
         copy_scales((c_begin + 1) / cpg, 1, lanes1);
@@ -330,7 +367,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
         copy_scales((c_begin + 2) / cpg, 2, lanes2);
         copy_raw(c_begin + 3, 0, lanes3);
         copy_record((c_begin + 3) / cpg, 0, lanes3);
-        wait_copies_but<COPIES>();
+        wait_older_copies<NEAR, FAR>(c_end - c_begin + 1);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
@@ -364,9 +401,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2) linear_pipe_kernel(
     for (;;) {
         start_finish();
         __builtin_amdgcn_s_setprio(1);
-        for (int c = c_begin; c < c_end; c += 2) {
-            chunk(c, oa, ob, std::integral_constant<int, 0>{});
-            if (c + 1 < c_end) chunk(c + 1, ob, oa, std::integral_constant<int, 1>{});
+        int c = c_begin;
+        for (; c + 5 < c_end; c += 2) {
+            chunk(c, oa, ob, std::integral_constant<int, 0>{}, std::false_type{});
+            chunk(c + 1, ob, oa, std::integral_constant<int, 1>{}, std::false_type{});
+        }
+        for (; c < c_end; c += 2) {
+            chunk(c, oa, ob, std::integral_constant<int, 0>{}, std::true_type{});
+            if (c + 1 < c_end) chunk(c + 1, ob, oa, std::integral_constant<int, 1>{}, std::true_type{});
         }
         __builtin_amdgcn_s_setprio(0);
         if (!SUM_IN_MFMA) {

@@ -26,3 +26,14 @@ def test_validation_under_address_and_undefined_behavior_sanitizers(tmp_path):
     run = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120, env=env)
     assert run.returncode == 0 and "all checks passed" in run.stdout, run.stdout[-4000:]
     shutil.rmtree(tmp_path, ignore_errors=True)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_the_waits_of_the_pipelined_loop_bring_in_what_the_next_chunk_reads(tmp_path):
+    """Every number of chunks a K range can be short by, whether copies of no lanes are counted or not."""
+    exe = str(tmp_path / "pipe_copies")
+    build = subprocess.run(["g++", "-std=c++17", "-Wall", os.path.join(HERE, "pipe_copies.cpp"), "-o", exe], stdout=subprocess.PIPE,
+                           stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert build.returncode == 0, build.stdout[-4000:]
+    run = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    assert run.returncode == 0 and "all copies have landed" in run.stdout, run.stdout[-4000:]
