@@ -68,6 +68,7 @@ __device__ __forceinline__ void store_tile(const v4f (&acc)[WM][WN], uint8_t* sl
     auto hi = [](uint32_t pair) { return __uint_as_float(pair & 0xFFFF0000u); };
 #pragma unroll
     for (int f = F0; f < F1; f += L::BLOCKS) {
+        wave_lds_fence();                                        // the round before has read its rows
 #pragma unroll
         for (int b = 0; b < L::BLOCKS; ++b) {
             const v4f(&a)[WN] = acc[f + b];
@@ -107,6 +108,7 @@ __device__ __forceinline__ void store_tile(const v4f (&acc)[WM][WN], uint8_t* sl
                     for (int r = 0; r < 4; ++r) *reinterpret_cast<float*>(rows + (4 * kq + r) * RSB + (j * 16 + i) * 4) = so[j] * a[j][r];
             }
         }
+        wave_lds_fence();
 #pragma unroll
         for (int h = 0; h < STORES; ++h) {
             const int row = h * ROWS_PER_STORE + srow;

@@ -315,6 +315,14 @@ __device__ __forceinline__ void lds_dma_4(const uint8_t* base, uint32_t offset, 
 // Waits until every outstanding global load of this wavefront, the copies above included, has completed.
 __device__ __forceinline__ void lds_dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Between a wavefront's LDS writes and the reads of what other lanes of it wrote, and before the place is written again.  The hardware runs a
+// wavefront's LDS accesses in order; this keeps the compiler, which sees one lane's accesses and may take those of different
+// types for unrelated, from moving them past each other.  Emits no instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Stores 16 bytes at an address that is aligned to its elements only (the hardware takes any; the compiler emits one
 // 16-byte store).  Rows of outputs whose stride is no multiple of 16 bytes go out like this: stored element by element, a
 // wavefront's store instruction touched a few bytes of every cache line of its rows.  2944 -> 5003, 4096 tokens, bf16,
