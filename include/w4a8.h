@@ -364,8 +364,8 @@ int w4a8_silu_mul(const void* gu_dev, int64_t M, int64_t F, int64_t ldgu, void* 
  *                             matrix with its rows INTERLEAVED in bands of 16: packed row 32p + i is gate row 16p + i,
  *                             packed row 32p + 16 + i is up row 16p + i (i < 16), so that a workgroup holds both halves
  *                             of the channels it finishes; pack that matrix with w4a8_pack_weights (TILED).
- *                             F % 16 == 0.  The gate and up values are rounded to bf16 before SiLU*mul, as the
- *                             unfused sequence does.
+ *                             F % 16 == 0; any row stride ldh8 >= F.  The gate and up values are rounded to bf16
+ *                             before SiLU*mul, as the unfused sequence does.
  *   w4a8_linear_quantize_in_fp8_out = w4a8_quantize_act of x followed by w4a8_linear_fp8_out, in one kernel: the form of
  *                             w4a8_linear_quantize_in (same limits: M <= 16, M * K <= 65536; same x, x8_out arguments)
  *                             whose output is quantized for the next layer like that of w4a8_linear_fp8_out.

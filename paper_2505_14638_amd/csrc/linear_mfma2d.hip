@@ -570,7 +570,7 @@ int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, 
     }
     const int64_t total = (int64_t)grid_m * grid_n * ksplit;
     if (total > (1 << 30)) return W4A8_ERR_SHAPE;
-    if (ldx8 >= (1 << 23) || ldy >= (1 << 20) || N >= (1 << 20)) return W4A8_ERR_SHAPE;   // 32-bit byte offsets inside a tile
+    if (ldx8 >= (1 << 23) || N >= (1 << 20)) return W4A8_ERR_SHAPE;   // 32-bit byte offsets inside a tile (outputs: 64-bit)
     if (group_m <= 0) {
         // One XCD runs 32 workgroups at a time; per chunk they pull rows * 128 bytes of activations and columns * 64
         // bytes of nibbles through its L2, least for a rectangle with about twice as many columns as rows:

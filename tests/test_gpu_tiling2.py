@@ -228,6 +228,20 @@ def test_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, path, p0, p1, dtype):
         assert torch.equal(buf.view(torch.uint8), before.view(torch.uint8)), f"written outside the rows, offset {off}"
 
 
+@pytest.mark.parametrize("m,k,f", [(8, 512, 160), (100, 1024, 240), (1100, 4096, 6144)])
+def test_silu_mul_rows_a_megabyte_apart(gpu_lib, m, k, f):
+    """The fused gate|up layer takes any row stride of its output, on whichever kernel the sizes lead to."""
+    assert B.linear_launch_shape(m, k, 2 * f, 128)[0] == {8: 0, 100: 1, 1100: 2}[m]
+    gen = torch.Generator(device=DEV).manual_seed(82)
+    sx_d, next_s = dev(np.array([0.01], np.float32)), dev(np.array([0.02], np.float32))
+    x8_d = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), sx_d)
+    packed, scales = B.pack_weights(torch.randn((2 * f, k), generator=gen, device=DEV) * 0.02, 128, B.LAYOUT_TILED)
+    want = B.linear_silu_mul_fp8_out(x8_d, sx_d, packed, scales, f, 128, next_s)
+    far = torch.zeros((m, (1 << 20) + 16), dtype=torch.uint8, device=DEV)
+    B.linear_silu_mul_fp8_out(x8_d, sx_d, packed, scales, f, 128, next_s, out=far[:, :f])
+    assert torch.equal(far[:, :f], want) and int(far[:, f:].max()) == 0
+
+
 @pytest.mark.parametrize("m,k,n,path", [(100, 1024, 480, 1), (600, 1024, 8224, 1), (700, 1024, 16416, 2), (1000, 2048, 6176, 2)])
 def test_fp8_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, m, k, n, path):
     """The E4M3 and the SiLU*mul output of either tiling (256 x 256 and 256 x 128 tiles of the second)."""
