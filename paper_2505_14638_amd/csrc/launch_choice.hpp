@@ -106,6 +106,12 @@ inline bool first_tiling_shape(int64_t M, int64_t K, int64_t N, int& mf, int& ks
     return true;
 }
 
+// 256 x 128 tiles of the formats with a table per channel on few chunks of K run on the loop of linear_mfma2d.hip: its start is shorter than that of
+// linear_pipe.hip, which has three chunks on their way before it begins.  Time against linear_pipe.hip on 1 ... 2, 3 ... 4, 5 ... 6, 7 ... 8,
+// 9 ... 12, 13 ... 20 chunks: asymmetric 0.76, 0.80, 0.84, 0.88, 0.92, 0.98, two-level 0.85, 0.87, 0.90, 0.92, 0.96, 0.99, asymmetric
+// two-level 0.88, 0.91, 0.93, 0.95, 0.98, 1.02.  (The plain formats gain by it up to eight chunks too, but on sizes where the first tiling is faster still.)
+inline bool mfma2d_few_chunks(int64_t C, int mode) { return C <= 12 && mode != MODE_CODE_EXACT && mode != MODE_POW2; }
+
 // Launch shape of the many-token kernels for a layer; requested values of mf / ks / tpw other than 0 are kept
 // (microseconds: the estimate, where all were 0).
 // cfg2d >= 0 on return: the layer goes to the second tiling (linear_mfma2d.hip, linear_pipe.hip) with that workgroup tile.

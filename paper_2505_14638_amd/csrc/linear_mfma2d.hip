@@ -36,7 +36,8 @@
 // a time cover a compact rectangle (one L2 per XCD).  The first loads and copies of the NEXT tile are issued before
 // the epilogue of the current one and finished in its middle: a tile's cold start (two memory round trips) is hidden.
 // Epilogue: every wavefront converts its own sums and stores them through an LDS slab of its own, no barriers (linear_epilogue.hpp).
-// 256 x 128 and 128 x 128 tiles of eight wavefronts have room in registers for the operands of two chunks: linear_pipe.hip.
+// 256 x 128 and 128 x 128 tiles of eight wavefronts have room in registers for the operands of two chunks: linear_pipe.hip, but for 256 x 128 tiles on
+// few chunks of K in the formats with a table per channel (mfma2d_few_chunks).
 // The -8 pattern of the sign-magnitude nibbles comes out of the fast expansion as minus zero; the wavefronts that read a
 // band put it right in their registers on chunks whose group scale carries the packer's mark.
 // Asymmetric formats: the wavefront that expands a band forms the sixteen bytes its nibbles stand for, four lanes sharing the
@@ -532,6 +533,22 @@ void launch_out(const LinearArgs& a, int ydt, dim3 grid, int grid_m, int grid_n,
     else launch_cfg<uint16_t, WGM, WGN, WM, WN>(a, grid, grid_m, grid_n, group_m, sp, st);
 }
 
+// 256 x 128 tiles of the formats that mfma2d_few_chunks names
+void launch_few_chunks(const LinearArgs& a, int ydt, dim3 grid, int grid_m, int grid_n, int group_m, const SplitArgs& sp, hipStream_t st) {
+#define W4A8_FEW_CHUNKS(T, MODEV)                                                                                              \
+    hipLaunchKernelGGL((linear_mfma2d_kernel<T, 4, 2, 4, 4, MODEV>), grid, dim3(512), 0, st, a.x8, a.M, a.ldx8, a.s_x, a.packed, a.scales, \
+                       a.N, a.n_tiles, a.C, a.cpg, a.NG, static_cast<T*>(a.y), a.ldy, grid_m, grid_n, group_m, a.y_scale, sp.ksplit,   \
+                       sp.cps > 0 ? sp.cps : a.C, sp.split_stride, a.w_out, a.per_channel)
+#define W4A8_FEW_CHUNKS_MODE(MODEV)                             \
+    if (ydt == W4A8_F32) W4A8_FEW_CHUNKS(float, MODEV);         \
+    else W4A8_FEW_CHUNKS(uint16_t, MODEV)
+    if (a.mode == MODE_TWO_LEVEL) W4A8_FEW_CHUNKS_MODE(MODE_TWO_LEVEL);
+    else if (a.mode == MODE_ASYM) W4A8_FEW_CHUNKS_MODE(MODE_ASYM);
+    else W4A8_FEW_CHUNKS_MODE(MODE_ASYM_TWO);
+#undef W4A8_FEW_CHUNKS_MODE
+#undef W4A8_FEW_CHUNKS
+}
+
 }  // namespace
 
 // Built workgroup tiles {tokens, channels}: cfg 0 = 512 x 128, 1 = 256 x 256, 2 = 256 x 128, 3 = 128 x 256, 5 = 128 x 128
@@ -591,10 +608,12 @@ int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, 
         a.ldy = mfma2d_splitk_ldw(N);
         kernel_ydt = W4A8_F32;
     }
-    if (cfg == 2 || cfg == 5) launch_linear_pipe(a, cfg, kernel_ydt, grid, grid_m, grid_n, group_m, sp.ksplit, sp.cps > 0 ? sp.cps : C, sp.split_stride, st);
+    const bool few_chunks = cfg == 2 && mfma2d_few_chunks(C, mode);
+    if ((cfg == 2 && !few_chunks) || cfg == 5) launch_linear_pipe(a, cfg, kernel_ydt, grid, grid_m, grid_n, group_m, sp.ksplit, sp.cps > 0 ? sp.cps : C, sp.split_stride, st);
     else switch (cfg) {
         case 0: launch_out<4, 2, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
         case 1: launch_out<2, 4, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
+        case 2: launch_few_chunks(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
         case 3: launch_out<2, 4, 4, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
         default: launch_out<2, 2, 8, 4>(a, kernel_ydt, grid, grid_m, grid_n, group_m, sp, st); break;
     }

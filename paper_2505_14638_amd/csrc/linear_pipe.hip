@@ -9,13 +9,18 @@
 //     them out (pipe_copies.hpp).
 // The copies are spread over the steps of a chunk: eight wavefronts that issue several at once wait for each other's at the one
 // vector memory path of the compute unit, with their MFMAs behind them (two at a time 86 us where one at a time takes 69).
-// Measured against the loop with operands read at the head of a chunk and one wait for everything at its end, microseconds: 512 tokens of
-// 14336 -> 4096, 256 x 128 tiles: code-exact 113 -> 94, powers of two 109 -> 87, asymmetric 125 -> 111, asymmetric
-// two-level 115 -> 101; 128 x 128 tiles 84 -> 69, 81 -> 68, 101 -> 87, 95 -> 81.  1024 tokens of 4096 -> 14336, 256 x 128 tiles 77 -> 66,
-// 69 -> 61, 80 -> 78, 74 -> 68.  What bounds a chunk now (256 x 128, 1970 cycles with the time stamps, 1024 of them MFMAs on 32 of a
-// SIMD's): the copies' issue 200, the expansion and its LDS traffic 300, the barrier and its wait 150; the older wavefront of a SIMD runs
-// through its steps in 1300 cycles, the younger one beside it in 1700.
-// With -8 in every group the two-level format takes 3 ... 10 % longer than on the loop this replaces (the operand is formed twice).
+// Measured against the loop with operands read at the head of a chunk and one wait for everything at its end, in turn on one card, microseconds:
+// 512 tokens of 14336 -> 4096, 256 x 128 tiles: code-exact 114 -> 93, powers of two 111 -> 85, two-level 104 -> 95, asymmetric 126 -> 109,
+// asymmetric two-level 116 -> 100; 128 x 128 tiles 85 -> 66, 82 -> 64, 87 -> 75, 101 -> 85, 95 -> 79.  1024 tokens of 4096 -> 14336,
+// 256 x 128 tiles 81 -> 73, 71 -> 60, 69 -> 69, 83 -> 79, 75 -> 69.  Its start is longer: on few chunks of K the formats with a table per channel
+// stay with linear_mfma2d.hip (mfma2d_few_chunks), and the plain ones take 256 x 128 tiles 2 % longer at four chunks or 11 % (code-exact).
+// What bounds a chunk (256 x 128; 1970 cycles with the time stamps and before the last chunks had a loop of their own): 1024 cycles of MFMAs, 32 of a
+// SIMD's, and as many of the LDS port, one operand of 2 KB per MFMA and wavefront at 128 bytes a cycle, with the copies' and the expansion's
+// writes on top; the copies' issue 200, the expansion and its LDS traffic 300, the barrier and its wait 150; the older wavefront of
+// a SIMD runs through its steps in 1300 cycles, the younger one beside it in 1700.
+// With -8 in every group the two-level format takes up to 5 % longer than on the loop this replaces (the operand is formed twice), and the plain formats 58 %
+// longer than without: every wavefront of a tile's row puts the operand right in its registers.  To let the expanding wavefront do that takes 20 to
+// 26 % off such layers and adds 2 to 5 % to all others.
 #include "linear_epilogue.hpp"
 #include "pipe_copies.hpp"
 #include "w4a8_device.hpp"

@@ -111,6 +111,38 @@ def test_power_of_two_scales_on_the_second_tiling(gpu_lib, tile):
     check_outputs(y32, y16, ref, a, f"power-of-two scales, tile {tile}")
 
 
+@pytest.mark.parametrize("k", [128, 1536, 1664])
+@pytest.mark.parametrize("fmt", ["two_level", "asym", "asym_two_level"])
+def test_256_x_128_tiles_on_either_loop_hold_the_same_bits(gpu_lib, fmt, k):
+    """Formats with a table per channel: up to twelve chunks on one loop, from thirteen on on the other.  Every tile sums in the same order, so 512 x 128
+    tiles (the one loop at any size) and 128 x 128 (the other) hold the same bits; -8 in a third of the groups of the signed format."""
+    m, n, g = 530, 300, 128
+    gen = torch.Generator(device=DEV).manual_seed(84)
+    sx_d = dev(np.array([0.01], np.float32))
+    x8_d = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), sx_d)
+    s = torch.rand((n, k // g), generator=gen, device=DEV) + 0.5
+    w_out = torch.rand(n, generator=gen, device=DEV) + 0.5
+    if fmt == "two_level":
+        low = torch.where(torch.rand((n, k // g), generator=gen, device=DEV) < 0.3, -8, -7).repeat_interleave(g, dim=1)
+        q = torch.randint(-8, 8, (n, k), generator=gen, device=DEV).maximum(low).to(torch.int8)
+        packed, scales = B.pack_weights(q, g, B.LAYOUT_TILED, s)
+    else:
+        u = torch.randint(0, 16, (n, k), generator=gen, device=DEV, dtype=torch.uint8)
+        packed, scales = B.pack_weights_asym(u, g, s, torch.randint(0, 16, (n, k // g), generator=gen, device=DEV, dtype=torch.uint8))
+    for dtype in (torch.float32, torch.bfloat16):
+        y = {}
+        for tile, p1 in ((0, 0), (5, 0), (2, 0), (2, 1 | (8 << 8))):
+            y[tile, p1] = torch.full((m, n), float("nan"), dtype=dtype, device=DEV)
+            if fmt == "two_level":
+                B.linear_two_level_variant(x8_d, sx_d, packed, scales, w_out, n, g, y[tile, p1], tile, p1)
+            else:
+                B.linear_asym_variant(x8_d, sx_d, packed, scales, w_out if fmt == "asym_two_level" else None, n, g, y[tile, p1], 2, tile, p1)
+        want = y.pop((0, 0))
+        assert torch.isfinite(want.float()).all()
+        for key, got in y.items():
+            assert torch.equal(got, want), key
+
+
 def test_default_path_takes_the_second_tiling_on_large_grids(gpu_lib):
     """M = 2048 on a 4096-channel layer (activations as in the benchmark configs: 1 % of the channels x 20): w4a8_linear
     routes to the second tiling -- the same bits as the explicit variant, and as the first tiling (one weight band per
