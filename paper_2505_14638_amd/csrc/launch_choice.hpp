@@ -23,53 +23,72 @@ enum WeightMode { MODE_CODE_EXACT = 0, MODE_TWO_LEVEL = 1, MODE_ASYM = 2, MODE_P
 #define W4A8_MFMA_SHAPES 7
 #define W4A8_MFMA_SHAPE_LIST {{16, 1, 1}, {8, 1, 1}, {8, 2, 1}, {4, 1, 1}, {4, 2, 1}, {4, 4, 1}, {16, 1, 2}}
 
-// Estimated microseconds, from which the launch of a layer is chosen.  What a grid costs is its rounds -- workgroups that run at
-// the same time -- times what a round takes, and the last, partly filled one costs nearly as much as a full one.
-// C: 128-deep chunks of K.
-struct UnitRound {
-    double fixed, chunk, fill;       // one workgroup per compute unit: fixed + C (chunk + fill * share of the units that are busy)
-    double cost(int64_t tiles, double c) const {
-        const int64_t full = tiles / 256, rem = tiles % 256;
-        return (double)full * (fixed + c * (chunk + fill)) + (rem == 0 ? 0.0 : fixed + c * (chunk + fill * (double)rem / 256.0));
+// Estimated microseconds, from which the launch of a layer is chosen: a launch, what every round of workgroups that run at the same time takes,
+// what grows with the share of the chip that is taken, and the outputs (a million of them; more where their rows are not
+// aligned for 16-byte stores).  x: rounds, c: 128-deep chunks of K, or passes.
+struct Outputs {
+    double million;
+    bool ragged;
+};
+struct UnitTimes {                   // the second tiling, one workgroup per compute unit: a partly filled last round costs nearly a full one
+    double launch, tile, chunk, tile_fill, chunk_fill, out, out_ragged;
+    double cost(int64_t tiles, double c, Outputs o) const {
+        const double x = (double)tiles / 256.0;
+        return launch + ceil(x) * (tile + c * chunk) + x * (tile_fill + c * chunk_fill) + (out + (o.ragged ? out_ragged : 0.0)) * o.million;
     }
 };
-struct PairRound {                   // two to a compute unit: alone on it, sharing it, and the last round's share after full ones
-    double alone, alone_c, shared, shared_c, tail;
-    double cost(int64_t tiles, double c) const {
+struct PairTimes {                   // two to a compute unit: alone on it, sharing it, and the last round's share after full ones
+    double launch, alone, alone_c, shared, shared_c, tail, out, out_ragged;
+    double cost(int64_t tiles, double c, Outputs o) const {
         const int64_t full = tiles / 512, rem = tiles % 512;
         const double s = shared + shared_c * c;
         // a last round of at most 256 workgroups starts while others still finish theirs, and has its units to itself
-        return (double)full * s + (rem == 0 ? 0.0 : rem > 256 ? s : full > 0 ? tail * s : alone + alone_c * c);
+        const double last = rem == 0 ? 0.0 : rem > 256 ? s : full > 0 ? tail * s : alone + alone_c * c;
+        return launch + (double)full * s + last + (out + (o.ragged ? out_ragged : 0.0)) * o.million;
     }
 };
-struct FirstRound {                  // the first tiling, two to a unit: fixed + passes (pass + fill * share of the 512 places that are taken)
-    double fixed, pass, fill, tail;
-    double cost(int64_t groups, double passes) const {
-        const int64_t full = groups / 512, rem = groups % 512;
-        const double s = fixed + passes * (pass + fill), last = fixed + passes * (pass + fill * (double)rem / 512.0);
-        return (double)full * s + (rem == 0 ? 0.0 : full > 0 && rem <= 256 ? tail * s : last);
+struct FirstTimes {                  // the first tiling, `places` workgroups at a time; tail: how much of a full round a partly filled one costs
+    double launch, group, pass, group_fill, pass_fill, tail, out, out_ragged;
+    double cost(int64_t groups, int places, double passes, Outputs o) const {
+        const double x = (double)groups / places, rounds = x <= 1.0 ? 1.0 : (1.0 - tail) * x + tail * ceil(x);
+        return launch + rounds * (group + passes * pass) + x * (group_fill + passes * pass_fill) + (out + (o.ragged ? out_ragged : 0.0)) * o.million;
     }
 };
 struct TileTimes {
-    UnitRound tall, square, half;            // the second tiling's 512 x 128, 256 x 256 and 256 x 128 tiles
-    PairRound pair;                          // its 256 x 128 tiles of four wavefronts
-    FirstRound first[W4A8_MFMA_SHAPES - 1];  // the first tiling's shapes, in the order of their list
+    UnitTimes tall, square, half, half_short;   // the second tiling's 512 x 128, 256 x 256 and 256 x 128 tiles, the last also on the loop for few chunks
+    PairTimes pair;                          // its 256 x 128 tiles of four wavefronts
+    FirstTimes first[W4A8_MFMA_SHAPES - 1];  // the first tiling's shapes, in the order of their list
 };
-// Fitted to 16 layers (1024 ... 28672 features, 1024 ... 28672 channels) x 19 token counts (65 ... 8192) on every tile and on the
-// first tiling's own choice, in each format: what they choose is 0.2 % (the plain formats 0.8) slower than the best in the mean, 10 % at
-// most.  The first tiling is taken unless an estimate is 4 % below its own, so that errors of the fit cost no time there.
-// Shapes that a format's runs never met (the first tiling's tall ones) are priced at 1.25 times the code-exact times.
-constexpr double PREFER_FIRST = 0.96, SWITCH_SHAPE = 0.85;
-constexpr TileTimes CODE_EXACT_TIMES = {{5.88, 1.35, 0.331}, {6.34, 1.4, 0.302}, {4.61, 0.761, 0.158}, {7.6, 1.14, 7.11, 1.715, 0.572},
-    {{7.05, 1.04, 0.867, 0.687}, {4.11, 0.715, 0.425, 0.716}, {4.06, 0.841, 0.476, 0.632}, {3.35, 0.611, 0.155, 0.412}, {1.87, 0.68, 0.265, 0.3}, {1.81, 0.733, 0.491, 0.679}}};
-constexpr TileTimes POW2_TIMES = {{5.81, 1.22, 0.253}, {6.1, 1.2, 0.259}, {4.97, 0.722, 0.0877}, {6.82, 0.987, 5.69, 1.54, 0.582},
-    {{8.95, 1.3, 1.08, 0.687}, {6.81, 0.704, 0.375, 0.495}, {5.63, 1.1, 0.217, 0.481}, {5.85, 0.764, 0.193, 0.412}, {4.93, 0.693, 0.203, 0.3}, {4.04, 0.475, 0.853, 0.424}}};
-constexpr TileTimes TWO_LEVEL_TIMES = {{5.5, 1.26, 0.289}, {6.37, 1.4, 0.253}, {6.9, 0.763, 0.0966}, {7.58, 1.15, 7.65, 1.68, 0.597},
-    {{8.95, 1.3, 1.08, 0.687}, {7.4, 0.457, 0.618, 0.6}, {7.19, 0.603, 0.61, 0.424}, {5.85, 0.764, 0.193, 0.412}, {6.36, 0.625, 0.209, 0.3}, {5.92, 0.414, 0.713, 0.375}}};
-constexpr TileTimes ASYM_TIMES = {{6.26, 1.46, 0.324}, {8.41, 1.7, 0.258}, {7.3, 0.907, 0.126}, {7.81, 1.4, 8.31, 2.08, 0.62},
-    {{8.95, 1.3, 1.08, 0.687}, {6.61, 0.894, 0.531, 0.716}, {6.86, 0.904, 0.511, 0.493}, {5.85, 0.764, 0.193, 0.412}, {6.32, 0.641, 0.273, 0.529}, {5.9, 0.499, 0.706, 0.412}}};
-constexpr TileTimes ASYM_TWO_TIMES = {{5.76, 1.29, 0.3}, {6.98, 1.48, 0.291}, {5.63, 0.866, 0.0763}, {7.55, 1.2, 7.47, 1.76, 0.612},
-    {{8.95, 1.3, 1.08, 0.687}, {8.22, 0.906, 0.227, 0.516}, {6.96, 0.76, 0.608, 0.469}, {5.85, 0.764, 0.193, 0.412}, {6.46, 0.666, 0.273, 0.357}, {6.27, 0.52, 0.673, 0.403}}};
+// Fitted to 2307 layers in each format, every tile and shape timed on all of them, on half of them with weights that come from HBM: random ones (65 ...
+// 8192 tokens, 128 ... 28672 features, a fifth of them at most 1536, 360 ... 32768 channels, half of them no multiple of 128) and 16
+// layers x 20 token counts.  What they choose is 0.6 ... 1.5 % slower than the best in the mean (0.8 ... 1.4 on the half that a fit has not
+// seen), up to a third on single sizes (few chunks and ragged rows).
+// PAIR_TIE, OTHER_TIE: between equals the four-wavefront tiles in the plain formats (3072 tokens of 4096 -> 6144, code-exact, 95 us, eight
+// wavefronts 96.5), the eight-wavefront ones in the others (4096 tokens, asymmetric, 120.6, four 122.3).
+// MARKED_RISK: groups that hold a -8, which nobody knows here, cost a layer on linear_pipe.hip 58 %, on the other tiles 28 and on the first tiling 11 to
+// 22.  With it 8 of the 1274 layers take more than 10 % longer with -8 in every group than on the launches chosen before, without it
+// 47; it costs the others 0.2 %.
+constexpr double PAIR_TIE = 0.985, OTHER_TIE = 1.01, MARKED_RISK = 1.05;
+constexpr TileTimes CODE_EXACT_TIMES = {{4.35, 3.13, 1.34, 0.648, 0.328, 0.0899, 0.161}, {3.89, 3.64, 1.45, 0.962, 0.24, 0.0491, 0.0874},
+    {4, 3.03, 0.736, 0.356, 0.177, 0.142, 0.143}, {}, {5.84, 0.441, 1.22, 0.661, 1.72, 0.611, 0.309, 0.131},
+    {{4.28, 0.864, 1.13, 2.24, 0.749, 0.968, 0.249, 0.0517}, {4.05, 0, 0.757, 3.28, 0.38, 1, 0.0756, 0.0382}, {3.8, 0, 0.874, 2.32, 0.48, 0.843, 0.163, 0.0727},
+     {3.59, 0, 0.569, 3.45, 0.545, 0.574, 0, 0.0282}, {3.53, 0, 0.605, 2.65, 0.602, 0.728, 0, 0.0717}, {3.28, 0.142, 0.726, 1.32, 0.552, 0.884, 0.0123, 0.279}}};
+constexpr TileTimes POW2_TIMES = {{}, {3.92, 3.48, 1.24, 1.47, 0.242, 0.0141, 0.119},
+    {4.38, 1.54, 0.706, 0.897, 0.116, 0.127, 0.14}, {}, {5.4, 0.12, 1.07, 0.222, 1.52, 0.618, 0.271, 0.13},
+    {{4.29, 0.637, 1.03, 1.97, 0.66, 0.956, 0.273, 0.0421}, {4.07, 0, 0.696, 2.42, 0.42, 0.917, 0.142, 0.0419}, {3.83, 0, 0.827, 1.61, 0.571, 0.758, 0.204, 0.0979},
+     {3.51, 0, 0.584, 3.56, 0.521, 0.548, 0, 0.0403}, {3.46, 0, 0.623, 2.7, 0.583, 0.697, 0, 0.0903}, {3.34, 0, 0.746, 1.35, 0.545, 0.898, 0.0372, 0.309}}};
+constexpr TileTimes TWO_LEVEL_TIMES = {{4.04, 2.86, 1.33, 0, 0.243, 0.142, 0.125}, {4.04, 3.68, 1.45, 1.28, 0.226, 0.0467, 0.101},
+    {3.87, 2.78, 0.754, 0, 0.149, 0.172, 0.113}, {3.97, 1.25, 0.799, 0.326, 0.195, 0.182, 0.128}, {5.99, 0.99, 1.2, 0.852, 1.67, 0.624, 0.328, 0.114},
+    {{5.46, 1.2, 0.674, 0, 1.04, 0.98, 0.342, 0.0395}, {4.74, 0, 0.551, 1.57, 0.51, 0.847, 0.296, 0.0512}, {4.62, 0, 0.671, 1.83, 0.539, 0.757, 0.295, 0.0937},
+     {4.11, 0, 0.477, 2.84, 0.636, 0.436, 0.214, 0.0828}, {4.23, 0, 0.471, 3.21, 0.693, 0.576, 0, 0.104}, {3.65, 0.139, 0.664, 1.92, 0.457, 0.845, 0.0436, 0.219}}};
+constexpr TileTimes ASYM_TIMES = {{4.05, 3.65, 1.5, 0, 0.285, 0.142, 0.126}, {3.89, 5.71, 1.75, 1.31, 0.252, 0.0317, 0.111},
+    {3.83, 4.28, 0.867, 0.216, 0.167, 0.195, 0.109}, {4.28, 0.714, 1.11, 0.792, 0.0174, 0.206, 0.122}, {6.06, 1.83, 1.45, 2.48, 2, 0.63, 0.28, 0.11},
+    {{5.59, 0.668, 1.03, 0.557, 1.08, 0.909, 0.364, 0.0412}, {4.89, 0, 0.638, 1.39, 0.582, 1, 0.313, 0.0335}, {4.57, 0, 0.749, 1.82, 0.644, 0.788, 0.3, 0.0789},
+     {4.26, 0, 0.496, 1.73, 0.77, 0.607, 0.305, 0.0625}, {3.81, 0.0344, 0.603, 2.65, 0.303, 0.908, 0, 0.0526}, {3.55, 0.222, 0.732, 1.98, 0.464, 0.85, 0, 0.183}}};
+constexpr TileTimes ASYM_TWO_TIMES = {{3.84, 2.79, 1.37, 0, 0.248, 0.153, 0.139}, {3.52, 4.58, 1.53, 1.37, 0.273, 0.0279, 0.108},
+    {4.39, 2.14, 0.808, 0.0477, 0.147, 0.153, 0.113}, {3.95, 1.12, 0.893, 0.18, 0.172, 0.215, 0.137}, {5.87, 0.514, 1.27, 0.618, 1.74, 0.653, 0.344, 0.14},
+    {{4.86, 1.69, 0.789, 0, 1, 1, 0.347, 0.0417}, {4.89, 0, 0.591, 1.15, 0.611, 0.935, 0.338, 0.0637}, {4.64, 0, 0.747, 1.74, 0.607, 0.778, 0.327, 0.102},
+     {4.2, 0, 0.502, 1.96, 0.767, 0.635, 0.389, 0.0556}, {4.25, 0, 0.506, 3.13, 0.865, 0.652, 0.0134, 0.0945}, {3.66, 0.126, 0.761, 2.19, 0.441, 0.835, 0, 0.208}}};
 
 // 512 x 128 tiles in place of 256 x 256 ones: for the code-exact format where the grid needs no more of them.  A
 // 512 x 128 tile expands half as many bands per MFMA, which that format's FMAs leave no room for (8192 tokens of 4096 -> 28672:
@@ -124,9 +143,8 @@ inline bool mfma2d_few_chunks(int64_t C, int mode) { return C <= 12 && mode != M
 //    (65 ... 128 tokens of very wide layers) and serve the split of K only.
 //  - First tiling: tall token blocks amortize the nibble expansion over more MFMAs; K-splits shorten the dependent chain of
 //    passes (each waits for the copies of the next) when the grid is too small to fill the chip, at the price of a wider activation
-//    block to copy per pass.  The first shape, in the list's order, that gives about 1.5 workgroups per compute unit, unless the
-//    estimates say that this costs an eighth (600 tokens of 1024 -> 8224: 17.7 us, now 15.9); they tell close shapes apart less well than
-//    the rule does.
+//    block to copy per pass.  On one to three chunks the four groups of (4, 4, 1) have too few for all, and are still the fastest of the
+//    small grids (283 tokens of 384 -> 640 4.9 us, (4, 1, 1) 5.7).
 inline bool choose_many_token_launch(int64_t M, int64_t K, int64_t N, int mode, int& mf, int& ks, int& tpw, int& cfg2d, double& microseconds) {
     static const int cand[W4A8_MFMA_SHAPES][3] = W4A8_MFMA_SHAPE_LIST;
     cfg2d = -1;
@@ -139,37 +157,33 @@ inline bool choose_many_token_launch(int64_t M, int64_t K, int64_t N, int mode, 
                          : mode == MODE_TWO_LEVEL ? TWO_LEVEL_TIMES
                          : mode == MODE_POW2      ? POW2_TIMES
                                                   : CODE_EXACT_TIMES;
-    const double c = (double)(K / 128);
+    const int64_t chunks = K / 128;
+    const double c = (double)chunks;
+    const Outputs o{(double)M * (double)N * 1e-6, N % 8 != 0};
     auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
-    // the first tiling's shape: the rule's, unless another one's estimate is well below its
-    auto first_cost = [&](int q) {
-        const int64_t per_wg = 8 / cand[q][1];
-        return t.first[q].cost((M + 16 * cand[q][0] - 1) / (16 * cand[q][0]) * (((N + 15) / 16 + per_wg - 1) / per_wg),
-                               (double)((K / 128 + cand[q][1] - 1) / cand[q][1]));
-    };
-    int shape = 0;
-    while (cand[shape][0] != mf || cand[shape][1] != ks || cand[shape][2] != tpw) ++shape;   // one of the list's, chosen above
-    const double rule = first_cost(shape);
-    double lowest = SWITCH_SHAPE * rule;
+    double& best = microseconds;
+    best = INFINITY;
     for (int q = 0; q < W4A8_MFMA_SHAPES - 1; ++q) {
-        if (cand[q][0] > 4 && 16 * cand[q][0] >= 2 * M + 64) continue;   // mostly padding
-        if (cand[q][1] > 1 && K / 128 < 4 * cand[q][1]) continue;        // too few chunks to split
-        if (first_cost(q) < lowest) {
-            lowest = first_cost(q);
-            shape = q;
+        const int m = cand[q][0], k = cand[q][1];
+        if (m > 4 && 16 * m >= 2 * M + 64) continue;             // mostly padding
+        if (k == 2 && chunks < 2) continue;
+        const int64_t per_wg = 8 / k, groups = (M + 16 * m - 1) / (16 * m) * (((N + 15) / 16 + per_wg - 1) / per_wg);
+        // workgroups that run at the same time: two to a compute unit, three of the smallest shapes (registers)
+        const int places = m == 4 && (k == 1 || (k == 2 && mode != MODE_ASYM)) ? 768 : 512;
+        const double us = t.first[q].cost(groups, places, (double)((chunks + k - 1) / k), o);
+        if (us < best) {
+            best = us;
+            mf = m;
+            ks = k;
+            tpw = cand[q][2];
         }
     }
-    mf = cand[shape][0];
-    ks = cand[shape][1];
-    tpw = cand[shape][2];
-    double& best = microseconds;
-    best = PREFER_FIRST * first_cost(shape);
     // by tile: 512 x 128 for the formats whose expansion is the longer one, and where it stands for 256 x 256; 256 x 256; 256 x 128
     // with eight wavefronts and with four
     const bool plain = mode == MODE_CODE_EXACT || mode == MODE_POW2, tall_instead = mfma2d_tall_instead(M, N, mode);
-    const double e[5] = {plain && !tall_instead ? INFINITY : t.tall.cost(tiles(512, 128), c),
-                         tall_instead ? INFINITY : t.square.cost(tiles(256, 256), c),
-                         t.half.cost(tiles(256, 128), c), INFINITY, t.pair.cost(tiles(256, 128), c)};
+    const double e[5] = {plain && !tall_instead ? INFINITY : t.tall.cost(tiles(512, 128), c, o),
+                         tall_instead ? INFINITY : t.square.cost(tiles(256, 256), c, o),
+                         (mode == MODE_CODE_EXACT ? MARKED_RISK : 1.0) * (mfma2d_few_chunks(chunks, mode) ? t.half_short : t.half).cost(tiles(256, 128), c, o), INFINITY, (plain ? PAIR_TIE : OTHER_TIE) * t.pair.cost(tiles(256, 128), c, o)};
     for (int q = 0; q < 5; ++q) {
         if (e[q] < best) {
             best = e[q];
@@ -189,24 +203,27 @@ inline size_t mfma2d_splitk_bytes(int64_t M, int64_t N, int ksplit) {
 // none.  Few output tiles and a deep K (the down projection of a decoder block at 64...512 tokens): the tiles are multiplied
 // in `ksplit` K ranges by different workgroups, about as many as it takes to give every compute unit one, and a second launch
 // adds up the partial sums.  The tile is the one whose estimate is the lowest: fixed + time per chunk of a range, which grows with the share
-// of the chip that is busy, + the partial sums, written and read once.  Fitted to 47 layers (41 ... 512 tokens, 8192 ... 28672
-// features, 512 ... 16384 channels), errors -14 ... +11 %; against 128 x 256 tiles (128 x 128 where those are at most 16) everywhere:
-// 512 tokens of 28672 -> 8192 144 -> 123 us, 256 tokens 80 -> 70, 512 tokens of 14336 -> 4096 49 -> 44, 164 of 21120 -> 5312
-// 43 -> 38.  A layer whose estimate without ranges is lower stays whole (256 tokens of 8192 -> 4096 21.6 us, split
-// 24.1 at best; 500 of 8192 -> 2048 23.1 / 24.5).
+// of the chip that is busy, + the partial sums, written and read once.  Fitted to 182 layers (41 ... 512 tokens, 8192 ... 28672
+// features, 512 ... 16384 channels), errors -20 ... +28 %, less where it matters; what is chosen is 0.8 % slower than the best in the mean.  Against 128 x 256 tiles
+// (128 x 128 where those are at most 16) everywhere: 512 tokens of 28672 -> 8192 144 -> 123 us, 256 tokens 80 -> 70, 512 tokens of
+// 14336 -> 4096 49 -> 44, 164 of 21120 -> 5312 43 -> 38.  A layer whose estimate without ranges is lower stays whole (256 tokens of
+// 8192 -> 4096 21.6 us, split 24.1 at best; 500 of 8192 -> 2048 23.1 / 24.5).
 inline void mfma2d_choose_ksplit(int64_t M, int64_t K, int64_t N, int& cfg, int& ksplit) {
     struct Candidate {
         int cfg, bm, bn;
         double fixed, chunk, fill, per_mb;
     };
-    static const Candidate candidates[3] = {{5, 128, 128, 12.9, 0.426, 0.118, 0.127}, {2, 256, 128, 13.2, 0.644, 0.138, 0.178}, {3, 128, 256, 9.34, 0.888, 0.141, 0.275}};
+    static const Candidate candidates[3] = {{5, 128, 128, 13.2, 0.323, 0.221, 0.177}, {2, 256, 128, 13.7, 0.872, 0.0, 0.165}, {3, 128, 256, 14.0, 1.18, 0.0, 0.059}};
     cfg = 3;
     ksplit = 0;
     const int64_t C = K / 128;
+    constexpr double CLEAR_GAIN = 0.87;
     if (M > 512 || K < 8192) return;
     int mf = 0, ks = 0, tpw = 0, cfg2d;
     double best;
     if (!choose_many_token_launch(M, K, N, MODE_CODE_EXACT, mf, ks, tpw, cfg2d, best)) return;
+    const double whole = best;
+    best *= 1.03;                                                // between equals the ranges (100 tokens of 8192 -> 2048 16.6 us, whole 17.0)
     int64_t cps = 0;
     auto ranges = [&](int64_t tiles) {                          // 0: none
         int64_t s = tiles > 128 ? 0 : 256 / tiles;
@@ -221,14 +238,14 @@ inline void mfma2d_choose_ksplit(int64_t M, int64_t K, int64_t N, int& cfg, int&
     const int64_t plane = M * mfma2d_splitk_ldw(N) * (int64_t)sizeof(float);
     const int64_t wide = (M + 127) / 128 * ((N + 255) / 256);
     int64_t most = ranges(wide <= 16 ? (M + 127) / 128 * ((N + 127) / 128) : wide);
-    if (wide <= 16 && most >= 4) best = INFINITY;                // so few tiles: always
     most = K < 12288 && most < 4 ? 0 : most * plane;             // (where that rule left the layer whole)
     if (most < (int64_t)W4A8_STATIC_WORKSPACE_BYTES) most = (int64_t)W4A8_STATIC_WORKSPACE_BYTES;
     for (const Candidate& q : candidates) {
         const int64_t tiles = (M + q.bm - 1) / q.bm * ((N + q.bn - 1) / q.bn), s = ranges(tiles);
         if (s == 0 || s * plane > most) continue;
         const double us = q.fixed + (double)cps * (q.chunk + q.fill * (double)(tiles * s) / 256.0) + q.per_mb * 4e-6 * (double)s * (double)M * (double)N;
-        if (us < best) {
+        // more scratch than the static workspace has: for a clear gain only, so that layers close to equal stay with callers that have no more
+        if (us < best && (s * plane <= (int64_t)W4A8_STATIC_WORKSPACE_BYTES || (K >= 12288 && us < CLEAR_GAIN * whole))) {
             best = us;
             cfg = q.cfg;
             ksplit = (int)s;

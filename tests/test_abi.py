@@ -370,6 +370,21 @@ def test_asymmetric_layers_take_the_tile_that_measures_fastest(L, m, k, n, want)
     assert B.linear_format_launch_shape(m, k, n, 128, "asym")[:2] == want
 
 
+@pytest.mark.parametrize("fmt,m,k,n,want", [
+    ("code_exact", 574, 19968, 14072, (2,)),         # second tiling 262 us; first tiling 296
+    ("code_exact", 4675, 384, 2357, (1,)),           # first tiling 16 us; second tiling 20
+    ("pow2", 733, 256, 1479, (1,)),                  # 8.0; 12.5
+    ("pow2", 1361, 640, 807, (1,)),                  # 9.0; 14.7
+    ("pow2", 128, 1536, 9330, (1, 4, 2 | 256)),      # two K groups 10.4; four 12.4
+    ("pow2", 283, 384, 640, (1, 4, 4 | 256)),        # four K groups on three chunks 4.9; one group 5.8
+    ("two_level", 433, 19072, 16421, (1,)),          # 195; 243
+    ("asym_two_level", 110, 1152, 23708, (1,)),      # 13.3; 16.1
+    ("asym", 5760, 512, 1024, (2, 2)),               # 256 x 128 tiles on few chunks 11.1; the pipelined loop 13.5
+])
+def test_layers_of_few_chunks_and_of_many_take_the_launch_that_measures_fastest(L, fmt, m, k, n, want):
+    assert B.linear_format_launch_shape(m, k, n, 128, fmt)[: len(want)] == want
+
+
 def test_linear_quantize_in_fp8_out_validation(L):
     f = L.w4a8_linear_quantize_in_fp8_out
     # x, x_dtype, M, K, ldx, x_scale, packed, w_scales, N, G, y_scale, y8, ldy8, x8_out, stream
