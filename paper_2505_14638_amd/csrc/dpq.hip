@@ -92,19 +92,8 @@ __device__ __forceinline__ void group_params(float lo, float hi, float& s, float
     z = fminf(fmaxf(rintf(__fdiv_rn(-lo, s)), 0.0f), 15.0f);
 }
 
-// a / b, correctly rounded, from y = RN(1 / b): the estimate a * y is at most two units off, one correction makes it
-// faithful, and a second one rounds it correctly (Markstein's theorem on the final step of a division by a correctly
-// rounded reciprocal).  Five operations, where the general division takes about ten and several mode switches; valid while
-// neither the residuals nor the quotient leave the normal range, which the callers' range checks see to (a zero's sign may
-// differ, which nothing here depends on).
-__device__ __forceinline__ float div_by(float a, float b, float y) {
-    float q = __fmul_rn(a, y);
-    q = __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
-    return __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
-}
-constexpr float DIV_LO = 0x1p-30f, DIV_HI = 0x1p30f;            // divisors
+// div_by's range: weights; divisors are those of plain_divisor.  (A zero's sign, which it may turn, decides nothing here.)
 constexpr uint32_t NUM_LO = 0x21800000u, NUM_SPAN = 0x5D800000u - 0x21800000u;   // bits of 2^-60, up to 2^60: weights
-__device__ __forceinline__ bool plain_divisor(float b) { return fabsf(b) >= DIV_LO && fabsf(b) <= DIV_HI; }
 
 // fp8_value for a finite t
 __device__ __forceinline__ float fp8_value_finite(float t) {

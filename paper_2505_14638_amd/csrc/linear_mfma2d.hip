@@ -56,14 +56,6 @@ namespace w4a8 {
 namespace {
 
 constexpr int XCDS2 = 8;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order: an unrolled loop whose index is a constant
-// expression inside the body (the scheduling builtins take constants only).
-template <int... I, typename F>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
 
 // A wave-uniform pointer, marked as such: a load from `uniform(p) + lane_offset` (32-bit offset) then takes its base from
 // scalar registers instead of a 64-bit address per lane that the compiler would keep, and advance, in vector registers.

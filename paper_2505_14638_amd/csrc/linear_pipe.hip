@@ -35,12 +35,6 @@ namespace w4a8 {
 namespace {
 
 constexpr int XCDS_P = 8;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <int... I, typename F>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
 
 // All lanes if left > 0, none otherwise.
 __device__ __forceinline__ uint64_t lanes_if(int left) {

@@ -3,10 +3,20 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 namespace w4a8 {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order: an unrolled loop whose index is a constant
+// expression inside the body (the scheduling builtins take constants only).
+template <int... I, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
 
 // Saturate to the E4M3 range (Sec. 4.1: +-448) before the hardware rounding; NaN passes through.
 __device__ __forceinline__ float sat448(float t) {
@@ -388,19 +398,29 @@ template <> struct Load16<uint16_t> {
     static __device__ __forceinline__ float one(const uint16_t* p) { return bf16_bits_to_f32(*p); }
 };
 
-// Eq. 13 under one static scale: h / s correctly rounded, then rounded onto the E4M3 grid.  The reciprocal is formed once; a
-// quotient is then its estimate and two corrections, the second of which rounds it correctly (Markstein), for scales
-// between 2^-30 and 2^30 and quotients the grid can tell from zero and from 448.  Below those the estimate rounds to the same
-// zero, above to the same 448, infinities and NaN included.  Six operations where the general division takes ten and two mode switches.
+// a / b, correctly rounded, from y = RN(1 / b): the estimate a * y is at most two units off, one correction makes it
+// faithful, and a second one rounds it correctly (Markstein's theorem on the final step of a division by a correctly
+// rounded reciprocal).  Five operations, where the general division takes about ten and several mode switches; valid while
+// neither the residuals nor the quotient leave the normal range, which the callers' range checks see to (a zero's sign may
+// differ).
+__device__ __forceinline__ float div_by(float a, float b, float y) {
+    float q = __fmul_rn(a, y);
+    q = __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
+    return __fmaf_rn(__fmaf_rn(-b, q, a), y, q);
+}
+constexpr float DIV_LO = 0x1p-30f, DIV_HI = 0x1p30f;            // divisors
+__device__ __forceinline__ bool plain_divisor(float b) { return fabsf(b) >= DIV_LO && fabsf(b) <= DIV_HI; }
+
+// Eq. 13 under one static scale: h / s correctly rounded, then rounded onto the E4M3 grid, the reciprocal formed once, for plain
+// scales and quotients the grid can tell from zero and from 448.  Below those the estimate rounds to the same
+// zero, above to the same 448, infinities and NaN included.
 struct StaticQuantizer {
     float s, y;
     bool plain;                                                  // wave-uniform
-    __device__ __forceinline__ explicit StaticQuantizer(float scale) : s(scale), y(1.0f / scale), plain(fabsf(scale) >= 0x1p-30f && fabsf(scale) <= 0x1p30f) {}
+    __device__ __forceinline__ explicit StaticQuantizer(float scale) : s(scale), y(1.0f / scale), plain(plain_divisor(scale)) {}
     __device__ __forceinline__ float quotient(float h) const {
         const float q0 = h * y;
-        float q = fmaf(fmaf(-s, q0, h), y, q0);
-        q = fmaf(fmaf(-s, q, h), y, q);
-        return fabsf(q0) < 512.0f ? __builtin_copysignf(q, q0) : q0;
+        return fabsf(q0) < 512.0f ? __builtin_copysignf(div_by(h, s, y), q0) : q0;
     }
     // four values -> four E4M3 bytes
     __device__ __forceinline__ uint32_t four(float a, float b, float c, float d) const {

@@ -84,8 +84,6 @@ int launch_linear_mfma2d(const uint8_t* x8, int64_t M, int64_t K, int64_t ldx8, 
                          void* workspace = nullptr, const float* w_out = nullptr, int per_channel = 0);
 void launch_linear_pipe(const LinearArgs& a, int cfg, int ydt, dim3 grid, int grid_m, int grid_n, int group_m, int ksplit, int cps,
                         int64_t split_stride, hipStream_t st);
-void launch_linear_pipe(const LinearArgs& a, int cfg, int ydt, dim3 grid, int grid_m, int grid_n, int group_m, int ksplit, int cps,
-                        int64_t split_stride, hipStream_t st);
 int launch_hessian_accumulate(const void* x, w4a8_dtype dt, int64_t T, int64_t K, int64_t ldx, float* h, hipStream_t st);
 int launch_gar_permutation(const float* hdiag, int64_t K, int32_t G, int32_t* perm, hipStream_t st);
 // U = upper Cholesky factor of the inverse dampened (and reordered) Hessian; workspace: hessian_factor_workspace_bytes(K)
