@@ -138,6 +138,24 @@ def test_dpq_general_division_and_tile_edges(gpu_lib, n, k, g, grid):
     assert np.array_equal(scales, want[1]) and np.array_equal(zeros, want[2]) and np.array_equal(codes, want[0])
 
 
+@pytest.mark.parametrize("n,k,g", [(40, 256, 128), (130, 512, 256)])
+def test_dpq_products_below_the_normal_range(gpu_lib, n, k, g):
+    """Rows so small that an error times U is a subnormal number: the matrix unit has to round it, not to flush it."""
+    rng = np.random.default_rng([96, n, k, g])
+    w = syn.make_weights(rng, n, k)
+    w[::2] *= np.float32(1e-33)
+    w[1::2] *= np.float32(1e-34)
+    u = o.hessian_inverse_factor(calibration_inputs(rng, 2 * k, k)).astype(np.float32)
+    s_w = (np.abs(w).max(axis=1) / np.float32(448.0)).astype(np.float32)
+    off = np.abs(u[np.triu_indices(k, 1)])
+    assert s_w.min() > 2.0 ** -126 * 0.5 and np.mean(s_w.max() * off.astype(np.float64) < 2.0 ** -126) > 0.5
+    want = o.dpq_quantize(w, u, s_w, g)
+    codes, scales, zeros = (host(t) for t in B.dpq_calibrate(dev(w), dev(u), dev(s_w), g))
+    assert np.array_equal(codes, want[0]) and np.array_equal(scales, want[1]) and np.array_equal(zeros, want[2])
+    # the updates count: without them the codes are others
+    assert np.mean(codes != o.dpq_quantize(w, np.eye(k, dtype=np.float32), s_w, g)[0]) > 0.02
+
+
 def test_scale_search_launches_with_columns_beside_the_walk(gpu_lib):
     """2100 rows x 2560 features, 20 candidates, in reordered columns: the launch before a search brings 15 blocks of columns up
     to date, the others go with the walk.  Rows are independent: some of them against the oracle, bit for bit."""

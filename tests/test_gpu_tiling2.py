@@ -186,6 +186,18 @@ def test_split_k_exact_integer_case_bit_for_bit(gpu_lib, tile, ksplit):
     assert np.array_equal(y32, want)
 
 
+@pytest.mark.parametrize("ksplit", [2, 5])
+@pytest.mark.parametrize("m,k,n,g", [(100, 2048, 200, 128), (65, 1152, 136, 128), (300, 1024, 520, 512)])
+def test_split_k_ragged_on_256_x_128_tiles(gpu_lib, ksplit, m, k, n, g):
+    """The tile that w4a8_linear splits 400 and 512 tokens of a down projection with: uneven ranges, ranges that begin inside a group."""
+    test_split_k_ragged_against_the_oracle(gpu_lib, 2, ksplit, m, k, n, g)
+
+
+@pytest.mark.parametrize("ksplit", [2, 5])
+def test_split_k_exact_integer_case_on_256_x_128_tiles(gpu_lib, ksplit):
+    test_split_k_exact_integer_case_bit_for_bit(gpu_lib, 2, ksplit)
+
+
 @pytest.mark.parametrize("m", [48, 96, 128, 400])
 def test_linear_with_workspace_on_the_down_projection(gpu_lib, m):
     """The Llama-3-8B down projection (K = 14336, N = 4096) at batch sizes where w4a8_linear asks for a workspace (from 41
@@ -292,3 +304,70 @@ def test_fp8_rows_at_odd_addresses_hold_the_same_bits(gpu_lib, m, k, n, path):
         assert torch.equal(out, want)
         out.copy_(before[:, 5 : 5 + width])
         assert torch.equal(buf, before)
+
+
+# ------------------------------------------------------------------------------------- FP8 outputs of the second tiling
+def same_e4m3(a, b):
+    """The same bytes, a NaN being one with either sign."""
+    nan = (a & 0x7F) == 0x7F
+    return torch.equal(nan, (b & 0x7F) == 0x7F) and torch.equal(a.masked_fill(nan, 0x7F), b.masked_fill(nan, 0x7F))
+
+
+@pytest.mark.parametrize("tile,m,k,n", [(0, 257, 128, 30048), (1, 520, 128, 15488), (2, 390, 896, 15488), (4, 390, 128, 34208)])
+def test_fp8_outputs_of_every_tile_equal_the_unfused_sequence(gpu_lib, tile, m, k, n):
+    """Ragged sizes that the launch choice sends to each tile: w4a8_linear_fp8_out against linear (bf16) then quantize_act, and
+    w4a8_linear_silu_mul_fp8_out against linear, silu_mul, quantize_act -- kernels of their own, which divide the general way.  Ordinary
+    scales and ones outside 2^-30 .. 2^30, quotients far beyond 448, gates of hundreds and beyond 2^60, infinities, NaN, a scale of zero."""
+    g = 128
+    assert B.linear_launch_shape(m, k, n, g)[:2] == (2, tile)
+    gen = torch.Generator(device=DEV).manual_seed(83)
+    x8_d = B.quantize_act(torch.randn((m, k), generator=gen, device=DEV), dev(np.array([0.05], np.float32)))
+    x8_d[::37] = 0                                               # outputs of zero: NaN under an infinite activation scale
+    w = torch.randn((n, k), generator=gen, device=DEV) * 0.02
+    packed, scales = B.pack_weights(w, g, B.LAYOUT_TILED)
+    paired, paired_s = B.pack_weights(B.interleave_gate_up(w), g, B.LAYOUT_TILED)
+    seen = set()
+    for s_x in (0.05, 2.0, 2.0 ** -45, 2.0 ** 45, 2.0 ** 62, 3e38, float("inf")):
+        sx_d = dev(np.array([s_x], np.float32))
+        y16 = B.linear(x8_d, sx_d, packed, scales, n, g, B.LAYOUT_TILED, out_dtype=torch.bfloat16)
+        h16 = B.silu_mul(y16)
+        for src, call, args in ((y16, B.linear_fp8_out, (packed, scales, n)), (h16, B.linear_silu_mul_fp8_out, (paired, paired_s, n // 2))):
+            finite = src.float()[torch.isfinite(src.float())]
+            amax = float(finite.abs().max()) if finite.numel() else 1.0
+            for y_scale in (amax / 600.0, amax / 1e6, 1.0, 0.0):  # some saturate, most do, whatever comes, a division by zero
+                ys_d = dev(np.array([max(y_scale, 1e-44) if y_scale else 0.0], np.float32))
+                want = B.quantize_act(src, ys_d)
+                got = call(x8_d, sx_d, *args, g, ys_d)
+                assert same_e4m3(got, want), (call.__name__, s_x, y_scale)
+                seen |= {int((want & 0x7F).min()), int((want & 0x7F).max())}
+    assert {0x00, 0x7E, 0x7F} <= seen
+
+
+@pytest.mark.parametrize("tile,m", [(4, 130), (1, 200)])
+def test_every_bf16_gate_through_the_fused_epilogue(gpu_lib, tile, m):
+    """All 65536 bf16 values as gates (one channel each, by its group scale and the sign of its code) under several up values and output scales: the bytes
+    of linear, silu_mul (the general division) and quantize_act."""
+    f, k = 65536, 128
+    assert B.linear_launch_shape(m, k, 2 * f, 128)[:2] == (2, tile)
+    values = torch.arange(f, dtype=torch.int32, device=DEV)
+    gates = (values << 16).view(torch.float32)
+    x8_d = torch.zeros((m, k), dtype=torch.uint8, device=DEV)
+    x8_d[:, 0] = 0x38                                            # 1.0
+    one = dev(np.array([1.0], np.float32))
+    for shift in range(3):
+        ups = torch.tensor([1.0, 1.171875, 0.0078125, 3.140625, 201.0, 1.0e-3, 1.3046875], device=DEV)[(values + shift * 2) % 7]
+        codes = torch.zeros((2 * f, k), dtype=torch.int8, device=DEV)
+        codes[:f, 0] = 1 - 2 * (values >> 15).to(torch.int8)
+        codes[f:, 0] = 1
+        s = torch.cat([gates.abs(), ups])[:, None].contiguous()
+        packed, scales = B.pack_weights(codes, 128, B.LAYOUT_TILED, s)
+        paired, paired_s = B.pack_weights(B.interleave_gate_up(codes), 128, B.LAYOUT_TILED, B.interleave_gate_up(s))
+        gu = B.linear(x8_d, one, packed, scales, 2 * f, 128, B.LAYOUT_TILED, out_dtype=torch.bfloat16)
+        got_gates = gu[0, :f].float()
+        nan = torch.isnan(gates)
+        assert torch.equal(torch.isnan(got_gates), nan) and torch.equal(got_gates[~nan], gates[~nan])
+        h = B.silu_mul(gu)
+        for y_scale in (1.0, 0.01, 100.0, 1e-4, 1e30):
+            ys_d = dev(np.array([y_scale], np.float32))
+            got = B.linear_silu_mul_fp8_out(x8_d, one, paired, paired_s, f, 128, ys_d)
+            assert same_e4m3(got, B.quantize_act(h, ys_d)), (shift, y_scale)
