@@ -8,8 +8,9 @@
 // the block's 128 errors afterwards, tile by tile.  Every weight still sees the same float32 operations in the same order
 // as in the plain column-by-column statement (w <- w - err_q * U[q, v] for q ascending, product and difference rounded
 // separately), so the integer decisions are reproducible bit for bit; only the time at which an update is applied moves.
-// That rules out the matrix unit (a product there is not rounded by itself): the updates take a multiplication and a
-// subtraction each on the vector unit, 1.75 ms for 4096 x 4096 weights.
+// The products still come from the matrix unit: an outer product of one column and one row has a single term per element, added to
+// an accumulator of zero, so each is rounded by itself, to nearest even, subnormal results included.  The vector
+// unit is left with the subtractions: 4096 x 4096 weights 1.8 ms, with both operations there 2.3.
 #include "w4a8_device.hpp"
 #include "w4a8_internal.hpp"
 
@@ -244,8 +245,9 @@ struct Slice {
 // errors afterwards, on the matrix unit: those of the next one before it begins, the others by the four wavefronts that have no rows, beside the
 // chain.  A wavefront alone on its SIMD issues one vector operation every five cycles, so what a column costs is their number: 60,
 // with all later columns of the block in registers 100 on average.  32 lanes per row, with the weights in LDS, spent most
-// instructions on repeating the quantization step.  A launch whose updates are few takes 39 us (256 x 4096 in all 1.24 ms, before
-// 1.92 ms); 4096 x 4096 takes 2.1 ms, before 2.5 ms, and 16384 x 4096 5.9 ms, before 6.7 ms.
+// instructions on repeating the quantization step.  A launch whose updates are few takes 38 us (256 x 4096 in all 1.22 ms, before
+// 1.89 ms); 4096 x 4096 takes 1.8 ms, before 2.3 ms, and 16384 x 4096 5.7 ms, before 6.4 ms.  Where weights or scales ask for the general division in
+// every step of four (rows of zeros, rows at 1e-30) 4096 x 4096 takes 2.2 ms, before 2.4.
 __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_first, int c_err, int row_blocks, int gather, int update, int block,
                                                               int ready) {
     __shared__ __attribute__((aligned(16))) float lds[TILE_FLOATS + STAGE_FLOATS];
@@ -489,7 +491,7 @@ __global__ void __launch_bounds__(THREADS, 4) dpq_step_kernel(DpqArgs a, int c_f
 // A score is a serial sum, so the parallelism is in the rows and candidates: a workgroup takes `rows` rows and a thread one
 // candidate of one of them, 128 columns in LDS as FP8 values at a time, converted once for all candidates.  With four lanes
 // to a row, inside the walk, and for groups wider than 128 a conversion per candidate, 256 rows x 4096 features took 5.9 ms at
-// 20 candidates in groups of 4096 and 20.6 ms at 100, now 2.3 and 2.2 (32 lanes to a row, a candidate each: 4.5 and 7.3).
+// 20 candidates in groups of 4096 and 20.6 ms at 100, now 1.5 and 1.4 (32 lanes to a row, a candidate each, on the walk before: 4.5 and 7.3, against 2.3 and 2.2).
 constexpr int GROUP_ROWS = 32;
 __global__ void __launch_bounds__(256) dpq_group_kernel(DpqArgs a, int c0, int rows) {
     __shared__ __attribute__((aligned(16))) float w8[GROUP_ROWS * TILE_STRIDE];
@@ -591,10 +593,10 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
     };
     // Groups of 128: a search over few candidates, or one whose passes hide behind the updates of many rows, stays with the walk;
     // otherwise the chip is idle meanwhile and a launch of its own over all rows and candidates pays for itself, at about
-    // 15 us a block.  In place / in a launch of its own, ms: 4096 features, 4 candidates: 256 rows 2.06 / 2.51, 4096 rows
-    // 2.39 / 3.04; 20: 256 rows 2.67 / 2.34, 2048 rows 2.75 / 2.55, 4096 rows 2.86 / 2.97, 8192 rows 3.96 / 4.41; 100: 256
-    // rows 5.70 / 2.27, 8192 rows 6.30 / 5.65, 12288 rows 7.66 / 7.88, 16384 rows 9.02 / 10.1.  1024 features: 4096 rows and 20
-    // candidates 0.67 / 0.62, 8192 rows 0.68 / 0.68, 16384 rows and 100 candidates 1.48 / 1.50.
+    // 15 us a block.  In place / in a launch of its own, ms: 4096 features, 4 candidates: 256 rows 1.43 / 1.76; 12: 256 rows 1.72 / 1.71,
+    // 4096 rows 2.12 / 2.38; 20: 256 rows 2.01 / 1.61, 2048 rows 2.16 / 1.79, 4096 rows 2.33 / 2.35, 8192 rows 3.45 / 3.72; 100: 256
+    // rows 4.98 / 1.53, 8192 rows 5.64 / 4.96, 12288 rows 6.88 / 7.13, 16384 rows 8.63 / 9.32.  14336 features, 4096 rows, 20 candidates
+    // 18.0 / 18.7.  1024 features: 4096 rows and 20 candidates 0.52 / 0.44, 8192 rows 0.54 / 0.50, 16384 rows and 100 candidates 1.34 / 1.36.
     if (G == DPQ_BLOCK && (mse_grid <= 12 || N >= (int64_t)160 * mse_grid)) {
         if (int e = step(0, 1, 0, 1, 0, PARAMS_HERE, 0)) return e;
         for (int b = 1; b < nb; ++b)                             // the first update finds the other columns where they came from
@@ -603,9 +605,9 @@ int launch_dpq_calibrate(const float* w, const float* u, const float* s_w, int p
     }
     if (G == DPQ_BLOCK) {
         for (int b = 0; b < nb; ++b) {
-            // the block's own columns first, with others up to 512 tiles of 64 x 128 (4096 x 4096, 20 candidates: 2.97 ms; 256
-            // tiles 3.03, 768 3.08, the own columns alone 3.17); the rest beside the walk
-            const int lead = b == 0 ? 1 : min(nb - b, max(1, 512 / row_blocks));
+            // the block's own columns first, with others up to 256 tiles of 64 x 128 (4096 x 4096, 20 candidates: 2.35 ms; 512 tiles
+            // 2.41, 768 2.49; 2048 rows 1.79, 1.92, 2.02); the rest beside the walk
+            const int lead = b == 0 ? 1 : min(nb - b, max(1, 256 / row_blocks));
             const int c = b * DPQ_BLOCK, c_err = b > 0 ? c - DPQ_BLOCK : 0;
             if (int e = step(c, lead, c_err, b < 2, b > 0, NO_BLOCK, 0)) return e;
             if (int e = group(c)) return e;
