@@ -17,7 +17,8 @@
 //     products (128 deep) in the launch that updates the single column k + 3, which waits for its diagonal tile and
 //     leaves the chip idle otherwise.
 // Every step is one launch over independent tiles, so no kernel waits on another workgroup.
-// 4096 features take 2.0 ms, before the present factor_tile and with half as many wavefronts in flight 2.5 ms.  The 46 GFLOP would
+// 4096 features take 2.0 ms; before the present factor_tile, and with two workgroups to a unit instead of three (118 + 32 registers
+// per lane in trailing_update_kernel), 2.5 ms.  The 46 GFLOP would
 // take 1.05 ms at the 43 TFLOP/s that the float64 matrix unit reaches on the whole chip.  What a diagonal tile waits for: 5.5 us for its panel,
 // 13 us (64 deep) or 16 us (128 deep) for the launch that updates, factors and inverts it, 1.3 ms over all.  The launches of the middle columns take 20 to 31 us for
 // their products, those of the first up to 50 us; the others wait for the diagonal tile.

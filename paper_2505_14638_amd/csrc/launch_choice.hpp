@@ -92,7 +92,8 @@ constexpr TileTimes ASYM_TWO_TIMES = {{3.84, 2.79, 1.37, 0, 0.248, 0.153, 0.139}
 
 // 512 x 128 tiles in place of 256 x 256 ones: for the code-exact format where the grid needs no more of them.  A
 // 512 x 128 tile expands half as many bands per MFMA, which that format's FMAs leave no room for (8192 tokens of 4096 -> 28672:
-// 840 us against 858); with power-of-two scales the expansion has room beside the MFMAs and the square's smaller panels win (779 / 764).
+// 844 us against 866, and 1 to 5 % less at each of fourteen sizes timed in turn); with power-of-two scales the expansion has room
+// beside the MFMAs and the square's smaller panels win (779 / 764).
 inline bool mfma2d_tall_instead(int64_t M, int64_t N, int mode) {
     return mode == MODE_CODE_EXACT && (M + 511) / 512 * ((N + 127) / 128) <= (M + 255) / 256 * ((N + 255) / 256);
 }
