@@ -757,8 +757,8 @@ def main():
                                           "unit": "TFLOP/s", "frac": round(tfl / FP8_PEAK_TFLOPS, 4),
                                           "traffic": PREFILL_TRAFFIC_BYTES_PER_LAUNCH,
                                           "alg_bytes_per_launch": tot_bytes // len(per_shape),
-                                          "kernel": "linear_mfma2d_kernel (the 2048- and 8192-token shapes and gate|up at 512); "
-                                                    "linear_mfma_kernel (the other 512-token shapes)"}}
+                                          "kernel": "linear_mfma2d_kernel (the 8192-token shapes, QKV at 2048, gate|up); linear_pipe_kernel "
+                                                    "(O at 2048, down at 512 and 2048); linear_mfma_kernel (QKV and O at 512)"}}
         if not args.no_pow2:
             result["prefill"]["pow2_scales"] = {"metric": "the same sweep through w4a8_linear_pow2 (group scales rounded up "
                                                        "to powers of two and applied by the block-scaled MFMA)",
